@@ -4,38 +4,32 @@
 // accumulate, bf16 out, with three fused epilogues (plain / + residual / silu(gate) * up).
 //
 // Orientation.  Both operands are contiguous along k, which is exactly what the two register
-// operands of v_mfma_f32_32x32x16_bf16 want (lane (r, kg) holds 8 consecutive k of row r).  The
+// operands of v_mfma_f32_16x16x32_bf16 want (lane (r, kg) holds 8 consecutive k of row r).  The
 // weight rows go to the A side and the token rows to the B side, i.e. the kernel forms the
-// TRANSPOSED tile out^T[n, m]: in the 32x32 accumulator layout a lane then owns one token and
-// groups of 4 consecutive n, so the epilogue stores 8-byte bf16x4 pieces of an output row.
+// TRANSPOSED tile out^T[n, m]: in the 16x16 accumulator layout a lane then owns one token and
+// 4 consecutive n.  (The 32x32x16 form of the same work holds a 12 % lower rate on this power-managed chip: a loop of nothing
+// but MFMAs on N(0,1) operands, all CUs, 1786 against 2026 TFLOP/s - half as deep, it writes its sums twice as often.)
 //
-// Tiling.  Workgroup = 8 waves, tile = 256 weight rows x 256 tokens, k in steps of 64 through a
-// two-slot LDS ring filled by LDS-direct loads (no registers in between); 4 x 2 waves, each wave
-// 64 weight rows x 128 tokens = 2 x 4 accumulator blocks.  One workgroup barrier per k step: it
-// publishes the slot that landed and frees the other one for the next load.
+// Pipeline of a workgroup.  Both operand tiles come by LDS-direct loads into a ring of k stages, a stage 64 deep (a whole
+// 128-byte line of every row: with 32-deep stages each line came in two halves, -10 %); the ring is refilled as the waves
+// walk through it, across tiles when a workgroup has more than one.  Everything that is not an MFMA is placed between
+// MFMAs: operand reads one step ahead, the loads of the stage that replaces the one just read (4 or 8 per wave and stage;
+// in a burst they block the wave that issues them for hundreds of cycles), and the one barrier per stage sits inside the
+// MFMA stream, where every wave already holds the operands of the next few MFMAs.
+// 8192^3: 974 -> 777 us (1416 TFLOP/s), 11584 x 12288 x 4096: 1010 -> 912 us; what remains is power: with the loads and
+// operand reads taken out the same loop is 20 % faster at the same MFMA count.
 #include "kvra_internal.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace kvra {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) void lds_void;
-
-constexpr int kGemmThreads = 512;
-constexpr int kTileN = 256;    // weight rows per workgroup tile
-constexpr int kTileM = 256;    // tokens per workgroup tile
-constexpr int kTileK = 64;     // k per LDS slot
-// Waves (the last ones of the workgroup, one per SIMD) that issue the global -> LDS loads.  The 64
-// loads of a k step keep the vector memory pipe busy for about 1000 cycles (64 bytes per clock) and
-// a wave sits in its share of them until they are accepted; with every wave issuing 8 loads after
-// the barrier no MFMA starts for the first 500 cycles of a step.  With four issuers their SIMD
-// partners compute at once and have the matrix pipe to themselves meanwhile: +2.5 to 5 %.
-constexpr int kIssuers = 4;
-constexpr int kSlotBytes = (kTileN + kTileM) * kTileK * 2;   // 64 KiB: weight tile then token tile
 
 struct OutSegment {
   __bf16* ptr;   // dense [m, width] matrix that receives output columns [first, end)
@@ -52,202 +46,538 @@ struct GemmArgs {
   OutSegment seg[3];
   int n_seg;
   int m;
-  int n;               // weight rows walked: rows, or 2 * rows in dual mode (32-row blocks alternate w / w2)
+  int n;               // weight rows walked: rows, or 2 * rows in dual mode (blocks of GemmTile::DUAL_ROWS alternate w / w2)
   int k;
   int tiles_n, tiles_m;
   int dual;
 };
 
-__device__ __forceinline__ void gemm_lds_dma16(const void* uniform_base, unsigned lane_byte_off, unsigned lds_byte_addr) {
-  // 64 lanes x 16 bytes -> 1 KiB of consecutive LDS (lane l lands at +16 l); inline assembly so that
-  // completion can be awaited by hand with s_waitcnt vmcnt(n) instead of a full drain per load
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-               :
-               : "v"(lane_byte_off), "s"(uniform_base), "s"(lds_byte_addr)
-               : "memory", "m0");
+// Tile of a workgroup: TN weight rows x TM tokens, k in stages of TK through a ring of ST LDS slots;
+// WN x WM waves over the tile, WK waves over the k of a stage (their sums meet in LDS at the end).
+template <int TN_, int TM_, int TK_, int ST_, int WN_, int WM_, int WK_, int PER_SIMD_, bool WHOLE_ = false>
+struct GemmTile {
+  static constexpr int TN = TN_, TM = TM_, TK = TK_, ST = ST_, WN = WN_, WM = WM_, WK = WK_;
+  static constexpr bool WHOLE = WHOLE_;                    // operands of a whole stage are read ahead (see the kernel)
+  static constexpr int DUAL_ROWS = TN / WN >= 64 ? 32 : 16;   // dual mode: rows of a weight that sit side by side in the tile
+  static constexpr int NW = WN * WM * WK, THREADS = 64 * NW;
+  static constexpr int PER_SIMD = PER_SIMD_;               // waves per SIMD the register budget is cut for
+  static constexpr int NB = TN / WN / 16, MB = TM / WM / 16;   // 16 x 16 blocks of a wave
+  static constexpr int PR = TK / 8;                        // 16-byte pieces per LDS row
+  static constexpr int RPL = 64 / PR;                      // rows one wave load moves
+  static constexpr int WLOADS = TN / RPL, LOADS = (TN + TM) / RPL;
+  static constexpr int L = (LOADS + NW - 1) / NW;          // wave loads per stage and wave (the last may repeat one)
+  static constexpr int STAGE = (TN + TM) * TK * 2;
+  static constexpr int KPW = TK / 32 / WK;                 // 32-deep contraction steps of a wave per stage
+  static constexpr int REDUCE = (WK - 1) * WN * WM * NB * MB * 4 * 64 * 4;
+  static constexpr int LDS = ST * STAGE + REDUCE;
+  static_assert(WHOLE || (KPW % 2 == 0 && KPW >= 2), "two fragment sets alternate");
+  static_assert(TN % (32 * WN) == 0 && TM % (16 * WM) == 0 && LDS <= 160 * 1024 && (ST - 1) * L < 64, "");
+};
+
+// 64 lanes x 16 bytes -> 1 KiB of consecutive LDS (lane l lands at +16 l); inline assembly so that completion can be
+// awaited by hand with s_waitcnt vmcnt(n) instead of a full drain per load.  With on_mask = 0 no lane is enabled and
+// nothing moves: no branch around it, so that it can sit between MFMAs.
+__device__ __forceinline__ void gemm_lds_dma16_if(unsigned long long on_mask, const void* uniform_base,
+                                                  unsigned lane_byte_off, unsigned lds_byte_addr) {
+  unsigned long long saved;
+  asm volatile("s_mov_b32 m0, %3\n\ts_and_saveexec_b64 %0, %4\n\tglobal_load_lds_dwordx4 %1, %2\n\ts_mov_b64 exec, %0"
+               : "=&s"(saved)
+               : "v"(lane_byte_off), "s"(uniform_base), "s"(lds_byte_addr), "s"(on_mask)
+               : "memory", "m0", "scc");
 }
 
-__global__ __launch_bounds__(kGemmThreads, 1) void linear_kernel(GemmArgs a) {
+template <int N>
+__device__ __forceinline__ void wait_loads() {   // at most N vector-memory operations of this wave outstanding
+  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0F70);
+}
+
+// Two accumulator blocks of 16 columns each: a lane holds, for token lane % 16, columns 4 g .. 4 g + 3 of both (g = its
+// 16-lane row).  Trading registers between odd and even rows leaves 8 consecutive columns of the 32 in a lane, from
+// 16 (g % 2) + 8 (g / 2): a store then covers 16 tokens x 64 consecutive bytes in pieces of 16.
+__device__ __forceinline__ void gather_columns(const f32x4& lo, const f32x4& hi, float (&v)[8]) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(lo[e]), __float_as_uint(hi[e]), false, false);
+    v[e] = __uint_as_float(r[0]);
+    v[4 + e] = __uint_as_float(r[1]);
+  }
+}
+
+template <class T>
+__global__ __launch_bounds__(T::THREADS, T::PER_SIMD) void linear_kernel(GemmArgs a) {
+  constexpr int NB = T::NB, MB = T::MB, L = T::L, ST = T::ST, TK = T::TK, KPW = T::KPW, PR = T::PR;
   extern __shared__ u32x4 smem[];
+  char* const lds = reinterpret_cast<char*>(smem);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int r32 = lane & 31, kg = lane >> 5;
-  const int wn = wave & 3, wm = wave >> 2;
+  const int r16 = lane & 15, kg = lane >> 4;
+  const int wn = wave % T::WN, wm = (wave / T::WN) % T::WM, wk = wave / (T::WN * T::WM);
 
-  // workgroup -> tile.  Workgroup ids go round-robin over the 8 XCDs; each XCD takes a contiguous
+  // Workgroup -> tiles.  Workgroup ids go round-robin over the 8 XCDs; each XCD takes a contiguous
   // run of the tile order "bands of 4 weight tiles, token tiles inside a band, weight tile
-  // fastest", so that the 32 workgroups an XCD runs together share 4 weight tiles and 8 token
-  // tiles in its L2.
-  int tn, tm;
-  {
-    const int total = a.tiles_n * a.tiles_m;
-    const int per = (total + 7) >> 3;
-    const int t = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
-    if (t >= total) return;   // whole workgroup leaves before any barrier
+  // fastest", so that the workgroups an XCD runs together share few weight and token tiles in its L2.
+  const int total = a.tiles_n * a.tiles_m;
+  const int per = (total + 7) >> 3;
+  const int t_step = gridDim.x >> 3;
+  const int t_first = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+  const int t_end = min(((blockIdx.x & 7) + 1) * per, total);
+  if (t_first >= t_end) return;   // whole workgroup leaves before any barrier
+  auto place = [&](int t, int* n0, int* m0) {
     const int band = t / (4 * a.tiles_m);
     const int width = min(4, a.tiles_n - 4 * band);
     const int within = t - band * 4 * a.tiles_m;
-    tm = within / width;
-    tn = 4 * band + within % width;
-  }
-  const int n0 = tn * kTileN, m0 = tm * kTileM;
+    *m0 = (within / width) * T::TM;
+    *n0 = (4 * band + within % width) * T::TN;
+  };
+  const int KT = a.k / TK;
+  int stages_left = ((t_end - t_first + t_step - 1) / t_step) * KT;   // not yet computed
+  int loads_left = stages_left;                                       // not yet sent for
 
   // ---- global -> LDS staging -----------------------------------------------------------------
-  // A 256 x 64 bf16 tile is 2048 pieces of 16 bytes = 32 wave loads, NL per issuing wave and operand.
-  // Piece p = (row p / 8, slot p % 8); the lane that owns (row, slot) fetches column piece
-  // slot ^ ((row / 2) % 8) so that the operand reads below (16 rows of one column piece per
-  // quarter wave) spread over all banks.  Rows past the end of a matrix repeat its last row.
-  constexpr int NL = 32 / kIssuers;   // loads per issuing wave and operand
-  const bool issuer = wave >= 8 - kIssuers;
-  const int iw = wave - (8 - kIssuers);
-  unsigned woff[NL], xoff[NL];
-  const __bf16* wsrc[NL];
+  // A stage is the weight rows, then the token rows, PR pieces of 16 bytes each.  The lane that owns (row, slot)
+  // fetches column piece slot ^ f(row), f(row) = row / (16 / PR) mod PR, so that the operand reads below (16 rows
+  // of one column piece per quarter wave) spread over all banks.  Rows past the end of a matrix repeat its last row.
+  const int ld_row = lane / PR;
+  const int ld_piece = (lane % PR) ^ (((wave * T::RPL + ld_row) / (16 / PR)) % PR);
+  constexpr int PERIOD = 16 / PR * PR;   // rows after which f repeats
+  static_assert(T::NW * T::RPL % PERIOD == 0 && T::TN % PERIOD == 0 && (T::RPL % PERIOD == 0 || T::LOADS % T::NW == 0),
+                "f(row) must not depend on which of a wave's loads it is");
+  unsigned off[L];
+  const __bf16* src[L];
+  auto aim = [&](int t) {
+    int n0, m0;
+    place(t, &n0, &m0);
 #pragma unroll
-  for (int i = 0; i < NL; ++i) {
-    const int p = (i * kIssuers + (issuer ? iw : 0)) * 64 + lane;
-    const int row = p >> 3, slot = p & 7;
-    const unsigned piece = static_cast<unsigned>(slot ^ ((row >> 1) & 7));
-    int vrow = min(n0 + row, a.n - 1);                       // row in the walked order
-    int wrow = vrow;
-    const __bf16* src = a.w;
-    if (a.dual) {                                            // 32-row blocks alternate between the two weights
-      const int blk = vrow >> 5;
-      wrow = ((blk >> 1) << 5) + (vrow & 31);
-      // 8-row groups never straddle a 32-row block, so the choice is uniform per load
-      if (__builtin_amdgcn_readfirstlane(blk & 1)) src = a.w2;
-    }
-    wsrc[i] = src;
-    woff[i] = 2u * (static_cast<unsigned>(wrow) * static_cast<unsigned>(a.k) + 8u * piece);
-    const int xrow = min(m0 + row, a.m - 1);
-    xoff[i] = 2u * (static_cast<unsigned>(xrow) * static_cast<unsigned>(a.k) + 8u * piece);
-  }
-  const unsigned lds0 = static_cast<unsigned>(reinterpret_cast<uintptr_t>((lds_void*)smem));
-  auto dma_slot = [&](int kt, int slot) __attribute__((always_inline)) {
-    const long long kofs = static_cast<long long>(kt) * kTileK;
-    if (!issuer) return;
-#pragma unroll
-    for (int i = 0; i < NL; ++i) {
-      const unsigned dst = lds0 + slot * kSlotBytes + (i * kIssuers + iw) * 1024;
-      gemm_lds_dma16(wsrc[i] + kofs, woff[i], dst);
-      gemm_lds_dma16(a.x + kofs, xoff[i], dst + kTileN * kTileK * 2);
-    }
-  };
-
-  f32x16 acc[2][4];
-#pragma unroll
-  for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-    for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[nb][mb][e] = 0.0f;
-
-  const int sw = (r32 >> 1) & 7;   // swizzle of the rows this lane reads (tile rows are multiples of 32 apart)
-  // one k step of 64 on LDS slot S: operand reads of contraction step ks + 1 are issued before the
-  // MFMAs of step ks
-  auto compute = [&](auto slot_tag) __attribute__((always_inline)) {
-    constexpr int S = decltype(slot_tag)::value;
-    const bf16x8* Wt = reinterpret_cast<const bf16x8*>(smem) + S * (kSlotBytes / 16);
-    const bf16x8* Xt = Wt + kTileN * kTileK / 8;
-    auto wread = [&](int nb, int ks) -> bf16x8 { return Wt[(64 * wn + 32 * nb + r32) * 8 + ((2 * ks + kg) ^ sw)]; };
-    auto xread = [&](int mb, int ks) -> bf16x8 { return Xt[(128 * wm + 32 * mb + r32) * 8 + ((2 * ks + kg) ^ sw)]; };
-    bf16x8 fw[2][2], fx[2][4];
-#pragma unroll
-    for (int nb = 0; nb < 2; ++nb) fw[0][nb] = wread(nb, 0);
-#pragma unroll
-    for (int mb = 0; mb < 4; ++mb) fx[0][mb] = xread(mb, 0);
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-      if (ks + 1 < 4) {
-#pragma unroll
-        for (int nb = 0; nb < 2; ++nb) fw[(ks + 1) & 1][nb] = wread(nb, ks + 1);
-#pragma unroll
-        for (int mb = 0; mb < 4; ++mb) fx[(ks + 1) & 1][mb] = xread(mb, ks + 1);
+    for (int i = 0; i < L; ++i) {
+      const int idx = T::LOADS % T::NW == 0 ? i * T::NW + wave : min(i * T::NW + wave, T::LOADS - 1);
+      int row;
+      if (T::WLOADS % T::NW == 0 ? i * T::NW < T::WLOADS : idx < T::WLOADS) {
+        const int first = min(n0 + idx * T::RPL, a.n - 1);   // uniform
+        row = min(n0 + idx * T::RPL + ld_row, a.n - 1);
+        src[i] = a.w;
+        if (a.dual) {                                        // blocks of rows alternate between the two weights
+          constexpr int DR = T::DUAL_ROWS;
+          if ((first / DR) & 1) src[i] = a.w2;
+          row = row / (2 * DR) * DR + row % DR;
+        }
+      } else {
+        row = min(m0 + (idx - T::WLOADS) * T::RPL + ld_row, a.m - 1);
+        src[i] = a.x;
       }
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-        for (int nb = 0; nb < 2; ++nb)
-          acc[nb][mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw[ks & 1][nb], fx[ks & 1][mb], acc[nb][mb], 0, 0, 0);
-      __builtin_amdgcn_sched_barrier(0);
+      off[i] = 2u * (static_cast<unsigned>(row) * static_cast<unsigned>(a.k) + 8u * ld_piece);
+    }
+  };
+  const unsigned lds0 = static_cast<unsigned>(reinterpret_cast<uintptr_t>((lds_void*)smem));
+  int load_t = t_first, load_kt = 0;
+  auto send = [&](int i, unsigned slot_base, unsigned long long on) __attribute__((always_inline)) {
+    const int idx = T::LOADS % T::NW == 0 ? i * T::NW + wave : min(i * T::NW + wave, T::LOADS - 1);
+    gemm_lds_dma16_if(on, src[i] + static_cast<long long>(load_kt) * TK, off[i], slot_base + idx * 1024);
+  };
+  auto sent = [&]() {   // the stage under load_t / load_kt is on its way: on to the next one
+    --loads_left;
+    if (++load_kt == KT) {
+      load_kt = 0;
+      load_t += t_step;
+      if (load_t < t_end) aim(load_t);
     }
   };
 
-  const int KT = a.k / kTileK;
-  dma_slot(0, 0);
-  for (int kt = 0; kt < KT; kt += 2) {
-    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this wave's part of tile kt has landed
-    __syncthreads();                      // ... everybody's has, and slot 1 is no longer being read
-    if (kt + 1 < KT) dma_slot(kt + 1, 1);
-    compute(std::integral_constant<int, 0>{});
-    if (kt + 1 < KT) {
-      __builtin_amdgcn_s_waitcnt(0x0F70);
-      __syncthreads();
-      if (kt + 2 < KT) dma_slot(kt + 2, 0);
-      compute(std::integral_constant<int, 1>{});
-    }
+  // ---- operand reads -------------------------------------------------------------------------
+  const int sw = (r16 / (16 / PR)) % PR;   // f(row) of the rows this lane reads (multiples of 16 apart)
+  static_assert(16 % PERIOD == 0, "blocks of 16 rows share the swizzle");
+  unsigned wofs[KPW], xofs[KPW];
+#pragma unroll
+  for (int j = 0; j < KPW; ++j) {
+    const unsigned piece = static_cast<unsigned>((4 * (wk * KPW + j) + kg) ^ sw);
+    wofs[j] = static_cast<unsigned>(wn * (T::TN / T::WN) + r16) * (TK * 2) + piece * 16;
+    xofs[j] = static_cast<unsigned>(T::TN + wm * (T::TM / T::WM) + r16) * (TK * 2) + piece * 16;
   }
+  constexpr int N = NB * MB, R = NB + MB;   // MFMAs and operand reads of a step; MFMA i: mb = i / NB, nb = i % NB
+  // The weight fragments of a contraction step serve all its MFMAs and are double-buffered.  A token fragment serves NB
+  // consecutive ones; in a long step it is replaced by the next step's as soon as they are issued, in a short one,
+  // where that would be too late for the next step, it is double-buffered too.
+  constexpr int XSETS = N <= 16 ? 2 : 1;
+  bf16x8 fw[T::WHOLE ? 1 : 2][NB], fx[T::WHOLE ? 1 : XSETS][MB];
+  // Small tiles have too few MFMAs in a step to cover the way to LDS and back; there the operands of a whole stage are
+  // read, right after the barrier, while the MFMAs of the stage before run from registers.
+  bf16x8 gw[T::WHOLE ? 2 : 1][KPW][NB], gx[T::WHOLE ? 2 : 1][KPW][MB];
+  // operand read r of contraction step j, in the order the MFMAs want them: w0 x0 w1 .. x1 x2 ..
+  auto fetch = [&](auto set_tag, unsigned slot_ofs, int j, int r) __attribute__((always_inline)) {
+    constexpr int S = decltype(set_tag)::value;
+    if (r == 0 || (r >= 2 && r <= NB)) {
+      const int b = r == 0 ? 0 : r - 1;
+      fw[S][b] = *reinterpret_cast<const bf16x8*>(lds + slot_ofs + wofs[j] + b * 16 * TK * 2);
+    } else {
+      const int b = r == 1 ? 0 : r - NB;
+      fx[S % XSETS][b] = *reinterpret_cast<const bf16x8*>(lds + slot_ofs + xofs[j] + b * 16 * TK * 2);
+    }
+  };
+  // the MFMA after which read r of the next step is issued, spread over those from `first` on
+  auto fetch_at = [](int r, int first) constexpr -> int {
+    const int spread = first + r * (N - first) / R;
+    if (XSETS == 2 || r == 0 || (r >= 2 && r <= NB)) return spread;
+    const int free_at = ((r == 1 ? 0 : r - NB) + 1) * NB - 1;   // the register is still an operand until then
+    return spread > free_at ? spread : free_at;
+  };
+  constexpr int BAR = N * 3 / 8;   // MFMA of a stage's last step before which the waves meet
 
-  // ---- epilogue ------------------------------------------------------------------------------
-  // register e of block (nb, mb): weight row 64 wn + 32 nb + 8 (e/4) + 4 kg + e%4, token
-  // 128 wm + 32 mb + r32 (tile-relative)
-  if (a.dual) {
-    // blocks nb = 0 / 1 are the gate / up rows of the same 32 output columns
-    const int col0 = (n0 >> 1) + 32 * wn;
-    if (n0 + 64 * wn < a.n) {
+  f32x4 acc[NB][MB];
+
+  // ---- pipeline ------------------------------------------------------------------------------
+  aim(t_first);
 #pragma unroll
-      for (int mb = 0; mb < 4; ++mb) {
-        const int tok = m0 + 128 * wm + 32 * mb + r32;
-        if (tok < a.m) {
-          __bf16* orow = a.seg[0].ptr + static_cast<long long>(tok) * a.seg[0].ld + col0 + 4 * kg;
+  for (int s = 0; s < ST; ++s)
+    if (loads_left > 0) {
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            bf16x4 o4;
+      for (int i = 0; i < L; ++i) send(i, lds0 + s * T::STAGE, ~0ull);
+      sent();
+    }
+  if (stages_left >= ST) wait_loads<(ST - 1) * L>();
+  else wait_loads<0>();
+  __syncthreads();
+  unsigned slot = 0;   // byte offset of the slot the current stage sits in
+  unsigned send_slot = 0;
+  unsigned long long on = 0;
+  auto fetch_whole = [&](auto set_tag, unsigned slot_ofs, int q) __attribute__((always_inline)) {   // read q of R * KPW
+    constexpr int S = decltype(set_tag)::value;
+    const int j = q / R, r = q % R;
+    if (r < NB) gw[S][j][r] = *reinterpret_cast<const bf16x8*>(lds + slot_ofs + wofs[j] + r * 16 * TK * 2);
+    else gx[S][j][r - NB] = *reinterpret_cast<const bf16x8*>(lds + slot_ofs + xofs[j] + (r - NB) * 16 * TK * 2);
+  };
+  if constexpr (T::WHOLE) {
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-              const float g = acc[0][mb][4 * q + t], u = acc[1][mb][4 * q + t];
-              o4[t] = static_cast<__bf16>(g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)) * u);
+    for (int q = 0; q < R * KPW; ++q) fetch_whole(std::integral_constant<int, 0>{}, 0, q);
+  } else {
+#pragma unroll
+    for (int r = 0; r < R; ++r) fetch(std::integral_constant<int, 0>{}, 0, 0, r);
+  }
+  // one stage of the whole-stage form: its operands are in set S (or on their way there)
+  auto whole_stage = [&](auto set_tag) __attribute__((always_inline)) {
+    constexpr int S = decltype(set_tag)::value;
+    --stages_left;
+    const unsigned next = slot + T::STAGE == ST * T::STAGE ? 0 : slot + T::STAGE;
+    if (stages_left >= ST - 1) wait_loads<(ST - 2) * L>();
+    else wait_loads<0>();
+    __syncthreads();   // the next stage has landed, and this one's slot has been read
+    on = __builtin_amdgcn_ballot_w64(loads_left > 0);
+    __builtin_amdgcn_sched_barrier(0);
+    constexpr int M = N * KPW, Q = R * KPW;
+#pragma unroll
+    for (int i = 0; i < M; ++i) {
+      const int j = i / N, mb = i % N / NB, nb = i % NB;
+      if constexpr (T::WHOLE)
+        acc[nb][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(gw[S][j][nb], gx[S][j][mb], acc[nb][mb], 0, 0, 0);
+      asm volatile("" : "+v"(acc[nb][mb]));
+#pragma unroll
+      for (int q = 0; q < Q; ++q)
+        if (q * M / Q == i) fetch_whole(std::integral_constant<int, 1 - S>{}, next, q);
+#pragma unroll
+      for (int d = 0; d < L; ++d)
+        if (d * M / L == i) send(d, lds0 + slot, on);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if (on != 0) sent();
+    slot = next;
+  };
+
+  for (int t = t_first; t < t_end; t += t_step) {
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[nb][mb][e] = 0.0f;
+    if constexpr (T::WHOLE) {
+      for (int kt = 0; kt + 1 < KT; kt += 2) {
+        whole_stage(std::integral_constant<int, 0>{});
+        whole_stage(std::integral_constant<int, 1>{});
+      }
+      if (KT & 1) {
+        whole_stage(std::integral_constant<int, 0>{});
+#pragma unroll
+        for (int j = 0; j < KPW; ++j) {
+#pragma unroll
+          for (int nb = 0; nb < NB; ++nb) gw[0][j][nb] = gw[T::WHOLE ? 1 : 0][j][nb];
+#pragma unroll
+          for (int mb = 0; mb < MB; ++mb) gx[0][j][mb] = gx[T::WHOLE ? 1 : 0][j][mb];
+        }
+      }
+    } else {
+    for (int kt = 0; kt < KT; ++kt) {
+      --stages_left;
+      const unsigned next = slot + T::STAGE == ST * T::STAGE ? 0 : slot + T::STAGE;
+#pragma unroll
+      for (int j = 0; j < KPW; ++j) {
+        const bool last = j + 1 == KPW;
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+          if (last && i == BAR) {
+            // The next stage has landed for this wave (all but the ST - 2 stages behind it), after the barrier
+            // for every wave; and every wave holds the last operands of this stage, so its slot is free.  (After
+            // the last stage of all, what is fetched below is never used.)
+            if (stages_left >= ST - 1) wait_loads<(ST - 2) * L>();
+            else wait_loads<0>();
+            __syncthreads();
+            send_slot = lds0 + slot;
+            on = __builtin_amdgcn_ballot_w64(loads_left > 0);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+          const int mb = i / NB, nb = i % NB;
+          acc[nb][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[j & 1][nb], fx[(j & 1) % XSETS][mb], acc[nb][mb], 0, 0, 0);
+          asm volatile("" : "+v"(acc[nb][mb]));   // keeps what follows behind this MFMA
+#pragma unroll
+          for (int r = 0; r < R; ++r)
+            if (fetch_at(r, last ? BAR : 0) == i) {
+              if (last) fetch(std::integral_constant<int, 0>{}, next, 0, r);
+              else if (j & 1) fetch(std::integral_constant<int, 0>{}, slot, j + 1, r);
+              else fetch(std::integral_constant<int, 1>{}, slot, j + 1, r);
             }
-            *reinterpret_cast<bf16x4*>(orow + 8 * q) = o4;
+          // the loads of a stage are spread over one contraction step's worth of MFMAs from the barrier on
+#pragma unroll
+          for (int d = 0; d < L; ++d) {
+            if (last && BAR + d * N / L == i) send(d, send_slot, on);
+            if (j == 0 && BAR + d * N / L == N + i) send(d, send_slot, on);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        if (j == 0 && on != 0) {
+          sent();
+          on = 0;
+        }
+      }
+      slot = next;
+    }
+    }
+
+    // ---- epilogue ----------------------------------------------------------------------------
+    // register e of block (nb, mb): weight row 16 nb + 4 kg + e, token 16 mb + r16 (wave-relative)
+    int n0, m0;
+    place(t, &n0, &m0);
+    if constexpr (T::WK > 1) {
+      // the sums of the other k shares, through LDS
+      float* red = reinterpret_cast<float*>(lds + ST * T::STAGE) + (wm * T::WN + wn) * (NB * MB * 4 * 64) + lane;
+      constexpr int SHARE = T::WN * T::WM * NB * MB * 4 * 64;
+      __syncthreads();   // the region may still be read for the tile before
+      if (wk > 0) {
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+          for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) red[(wk - 1) * SHARE + ((nb * MB + mb) * 4 + e) * 64] = acc[nb][mb][e];
+      }
+      __syncthreads();
+      if (wk > 0) continue;
+#pragma unroll
+      for (int s = 0; s < T::WK - 1; ++s)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+          for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[nb][mb][e] += red[s * SHARE + ((nb * MB + mb) * 4 + e) * 64];
+    }
+    const int nw = n0 + wn * (T::TN / T::WN), mw = m0 + wm * (T::TM / T::WM) + r16;
+    const int lane_col = 16 * (kg & 1) + 8 * (kg >> 1);   // see gather_columns
+    auto store8 = [&](const float (&v)[8], __bf16* o) {
+      bf16x8 b;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) b[e] = static_cast<__bf16>(v[e]);
+      *reinterpret_cast<bf16x8*>(o) = b;
+    };
+    if (a.dual) {
+      // blocks nb = 4 i, 4 i + 1 / 4 i + 2, 4 i + 3 are the gate / up rows of the same 32 output columns
+      if constexpr (NB % 4 == 0) {
+#pragma unroll
+        for (int i = 0; i < NB / 4; ++i) {
+          if (nw + 64 * i >= a.n) continue;
+          const int col0 = ((nw + 64 * i) >> 1) + lane_col;
+#pragma unroll
+          for (int mb = 0; mb < MB; ++mb) {
+            f32x4 act[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+              for (int e = 0; e < 4; ++e) {
+                const float g = acc[4 * i + h][mb][e], u = acc[4 * i + 2 + h][mb][e];
+                act[h][e] = g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)) * u;
+              }
+            float v[8];
+            gather_columns(act[0], act[1], v);
+            const int tok = mw + 16 * mb;
+            if (tok < a.m) store8(v, a.seg[0].ptr + static_cast<long long>(tok) * a.seg[0].ld + col0);
+          }
+        }
+      } else if constexpr (NB == 2) {
+        // 16 rows of each weight: a lane has 4 columns of its token
+        if (nw < a.n) {
+#pragma unroll
+          for (int mb = 0; mb < MB; ++mb) {
+            bf16x4 o;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const float g = acc[0][mb][e], u = acc[1][mb][e];
+              o[e] = static_cast<__bf16>(g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)) * u);
+            }
+            const int tok = mw + 16 * mb;
+            if (tok < a.m)
+              *reinterpret_cast<bf16x4*>(a.seg[0].ptr + static_cast<long long>(tok) * a.seg[0].ld + (nw >> 1) + 4 * kg) = o;
           }
         }
       }
-    }
-  } else {
+    } else {
 #pragma unroll
-    for (int nb = 0; nb < 2; ++nb) {
-      const int nblk = n0 + 64 * wn + 32 * nb;   // first output column of this 32-wide block
-      if (nblk >= a.n) continue;
-      // segment that holds this block (segment edges are multiples of 32)
-      int s = 0;
-      if (a.n_seg > 1 && nblk >= a.seg[0].end) s = 1;
-      if (a.n_seg > 2 && nblk >= a.seg[1].end) s = 2;
-      __bf16* obase = a.seg[s].ptr;
-      const int ld = a.seg[s].ld, col0 = nblk - a.seg[s].first + 4 * kg;
+      for (int nb = 0; nb < NB; nb += 2) {
+        const int nblk = nw + 16 * nb;   // first output column of this pair of blocks
+        if (nblk >= a.n) continue;
+        // segment that holds it (segment edges are multiples of 32)
+        int s = 0;
+        if (a.n_seg > 1 && nblk >= a.seg[0].end) s = 1;
+        if (a.n_seg > 2 && nblk >= a.seg[1].end) s = 2;
+        __bf16* obase = a.seg[s].ptr;
+        const int ld = a.seg[s].ld, col0 = nblk - a.seg[s].first + lane_col;
+        // residual rows first, all of them in flight together (rows past the end repeat the last one)
+        bf16x8 r8[MB];
+        if (a.res != nullptr) {
 #pragma unroll
-      for (int mb = 0; mb < 4; ++mb) {
-        const int tok = m0 + 128 * wm + 32 * mb + r32;
-        if (tok < a.m) {
-          __bf16* orow = obase + static_cast<long long>(tok) * ld + col0;
-          const __bf16* rrow = a.res ? a.res + static_cast<long long>(tok) * ld + col0 : nullptr;
+          for (int mb = 0; mb < MB; ++mb)
+            r8[mb] = *reinterpret_cast<const bf16x8*>(a.res + static_cast<long long>(min(mw + 16 * mb, a.m - 1)) * ld + col0);
+        } else {
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            bf16x4 o4;
-            if (rrow != nullptr) {
-              const bf16x4 r4 = *reinterpret_cast<const bf16x4*>(rrow + 8 * q);
+          for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-              for (int t = 0; t < 4; ++t) o4[t] = static_cast<__bf16>(acc[nb][mb][4 * q + t] + static_cast<float>(r4[t]));
-            } else {
+            for (int e = 0; e < 8; ++e) r8[mb][e] = static_cast<__bf16>(0.0f);
+        }
 #pragma unroll
-              for (int t = 0; t < 4; ++t) o4[t] = static_cast<__bf16>(acc[nb][mb][4 * q + t]);
-            }
-            *reinterpret_cast<bf16x4*>(orow + 8 * q) = o4;
-          }
+        for (int mb = 0; mb < MB; ++mb) {
+          float v[8];
+          gather_columns(acc[nb][mb], acc[nb + 1][mb], v);
+          const int tok = mw + 16 * mb;
+#pragma unroll
+          for (int e = 0; e < 8; ++e) v[e] += static_cast<float>(r8[mb][e]);
+          if (tok < a.m) store8(v, obase + static_cast<long long>(tok) * ld + col0);
         }
       }
     }
   }
 }
+
+// Few tokens: a pass over the weights, bound by how fast they come from memory.  A workgroup owns 16 weight rows and all
+// (up to 16) tokens; its 8 waves share out k in chunks of 64, and both operands go from global memory straight into MFMA
+// fragments, since no wave needs what another one loads: no LDS and no barrier until the sums of the eight shares meet at
+// the end.  The loads of kRowsAhead chunks (of a 4096-deep row: all there are) are in flight together.
+constexpr int kRowsThreads = 512, kRowsWaves = 8, kRowsAhead = 8;
+
+__global__ __launch_bounds__(kRowsThreads, 2) void linear_rows_kernel(GemmArgs a) {
+  __shared__ f32x4 part[kRowsWaves][64];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r16 = lane & 15, kg = lane >> 4;
+  const int n0 = blockIdx.x * 16;   // n is a multiple of 32
+  const char* const w = reinterpret_cast<const char*>(a.w) +
+                        2 * (static_cast<long long>(n0 + r16) * a.k + 8 * kg);
+  const char* const x = reinterpret_cast<const char*>(a.x) +
+                        2 * (static_cast<long long>(min(r16, a.m - 1)) * a.k + 8 * kg);
+  f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+  const int chunks = a.k / 64;
+  auto steps = [&](int c, auto count_tag) __attribute__((always_inline)) {
+    constexpr int COUNT = decltype(count_tag)::value;
+    bf16x8 fw[COUNT][2], fx[COUNT][2];
+#pragma unroll
+    for (int u = 0; u < COUNT; ++u)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const long long at = (static_cast<long long>(c) + u * kRowsWaves) * 128 + h * 64;
+        fw[u][h] = *reinterpret_cast<const bf16x8*>(w + at);
+        fx[u][h] = *reinterpret_cast<const bf16x8*>(x + at);
+      }
+#pragma unroll
+    for (int u = 0; u < COUNT; ++u)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[u][h], fx[u][h], acc, 0, 0, 0);
+  };
+  int c = wave;
+  for (; c + (kRowsAhead - 1) * kRowsWaves < chunks; c += kRowsAhead * kRowsWaves) steps(c, std::integral_constant<int, kRowsAhead>{});
+  for (; c < chunks; c += kRowsWaves) steps(c, std::integral_constant<int, 1>{});
+  part[wave][lane] = acc;
+  __syncthreads();
+  if (wave != 0 || r16 >= a.m) return;
+  // 4 columns of a token per lane
+  f32x4 v = part[0][lane];
+#pragma unroll
+  for (int u = 1; u < kRowsWaves; ++u) v += part[u][lane];
+  int s = 0;
+  if (a.n_seg > 1 && n0 >= a.seg[0].end) s = 1;
+  if (a.n_seg > 2 && n0 >= a.seg[1].end) s = 2;
+  const long long at = static_cast<long long>(r16) * a.seg[s].ld + n0 - a.seg[s].first + 4 * kg;
+  if (a.res != nullptr) {
+    const bf16x4 r = *reinterpret_cast<const bf16x4*>(a.res + at);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] += static_cast<float>(r[e]);
+  }
+  bf16x4 o;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) o[e] = static_cast<__bf16>(v[e]);
+  *reinterpret_cast<bf16x4*>(a.seg[s].ptr + at) = o;
+}
+
+namespace {
+
+template <class T>
+int launch_tile(GemmArgs& a, hipStream_t stream) {
+  a.tiles_n = (a.n + T::TN - 1) / T::TN;
+  a.tiles_m = (a.m + T::TM - 1) / T::TM;
+  const int per = (a.tiles_n * a.tiles_m + 7) / 8;
+  constexpr int PER_CU = T::PER_SIMD * 4 / T::NW;
+  const unsigned grid = 8u * static_cast<unsigned>(std::min(per, 32 * PER_CU));
+  return launch_kernel(linear_kernel<T>, dim3(grid), dim3(T::THREADS), a, stream, T::LDS);
+}
+
+int launch_rows(GemmArgs& a, hipStream_t stream) {
+  return launch_kernel(linear_rows_kernel, dim3(static_cast<unsigned>(a.n / 16)), dim3(kRowsThreads), a, stream);
+}
+
+// ---- which kernel a shape gets ----------------------------------------------------------------------
+// A tile is good when it is large (LDS and L2 traffic per MFMA: at 256 x 256 the matrix pipes are busy 85 % of a step, at
+// 128 x 128 the loads take as long as the MFMAs) and when the tiles of the problem fill whole rounds of the 256 CUs; which
+// of the two wins changes with every few hundred tokens.  So the choice is made on a cost: T = fixed + KT * (rounds * step +
+// full * step_full) + rounds * per_round, in microseconds, KT = k / 64, rounds over the CUs of the fullest XCD, full = how
+// many rounds keep more than half the CUs busy (the clock drops then; the last round counts by how far it is beyond the half).
+// The constants are a non-negative least-squares fit to 4000 launches timed on MI355X (1 to 5824 tokens, 13 (n, k) pairs of 256
+// to 22016 x 256 to 11008, plain / residual / SwiGLU); choosing by the fit costs 2 % against choosing by hindsight, 10 % and
+// more in 12 of 300 shapes.  Tiles that were measured and never needed: 256 x 128, 192 x 128, 128 x 64, 64 x 32.
+struct TileChoice {
+  int tn, tm, tk, per_cu;
+  bool dual;
+  float fixed, per_round, step, step_full;
+  int (*launch)(GemmArgs&, hipStream_t);
+};
+
+const TileChoice kTiles[] = {
+    {256, 256, 64, 1, true, 6.59f, 0.00f, 1.245f, 0.208f, launch_tile<GemmTile<256, 256, 64, 2, 4, 2, 1, 2>>},
+    {256, 192, 64, 1, true, 5.44f, 0.00f, 1.084f, 0.137f, launch_tile<GemmTile<256, 192, 64, 2, 4, 2, 1, 2>>},
+    {192, 256, 64, 1, false, 5.84f, 0.00f, 1.012f, 0.202f, launch_tile<GemmTile<192, 256, 64, 2, 2, 4, 1, 2>>},
+    {192, 192, 64, 1, true, 3.76f, 1.97f, 0.714f, 0.173f, launch_tile<GemmTile<192, 192, 64, 3, 3, 4, 1, 3>>},
+    {128, 256, 64, 1, true, 4.29f, 1.28f, 0.679f, 0.155f, launch_tile<GemmTile<128, 256, 64, 3, 2, 4, 1, 2>>},
+    {128, 192, 64, 1, true, 4.04f, 0.83f, 0.536f, 0.155f, launch_tile<GemmTile<128, 192, 64, 4, 2, 4, 1, 2>>},
+    {128, 128, 64, 1, true, 4.73f, 0.00f, 0.420f, 0.106f, launch_tile<GemmTile<128, 128, 64, 5, 2, 4, 1, 2, true>>},
+    {64, 128, 64, 1, true, 3.51f, 0.85f, 0.303f, 0.042f, launch_tile<GemmTile<64, 128, 64, 6, 1, 8, 1, 2, true>>},
+    {64, 64, 64, 2, true, 4.16f, 0.00f, 0.241f, 0.205f, launch_tile<GemmTile<64, 64, 64, 5, 1, 4, 1, 2, true>>},
+    {64, 64, 128, 1, true, 3.48f, 0.89f, 0.179f, 0.029f, launch_tile<GemmTile<64, 64, 128, 4, 2, 2, 2, 2, true>>},
+    {32, 64, 128, 1, true, 3.32f, 0.79f, 0.137f, 0.023f, launch_tile<GemmTile<32, 64, 128, 5, 1, 4, 2, 2, true>>},
+    {32, 32, 128, 1, true, 3.28f, 0.78f, 0.112f, 0.001f, launch_tile<GemmTile<32, 32, 128, 8, 1, 2, 4, 2, true>>},
+};
+
+float tile_cost(const TileChoice& c, const GemmArgs& a) {
+  const int per_xcd = ((a.n + c.tn - 1) / c.tn * ((a.m + c.tm - 1) / c.tm) + 7) / 8, slots = 32 * c.per_cu;
+  const int rounds = (per_xcd + slots - 1) / slots;
+  const float last = static_cast<float>(per_xcd - (rounds - 1) * slots) / slots;
+  const float full = rounds - 1 + std::max(0.0f, 2.0f * last - 1.0f);
+  return c.fixed + a.k / 64 * (rounds * c.step + full * c.step_full) + rounds * c.per_round;
+}
+
+}  // namespace
 
 int launch_linear(const void* x, const void* w, const void* w2, const void* residual,
                   void* const* out, const int* seg_cols, int n_seg,
@@ -274,11 +604,21 @@ int launch_linear(const void* x, const void* w, const void* w2, const void* resi
   a.m = static_cast<int>(m);
   a.n = static_cast<int>(a.dual ? 2 * n_out : n_out);
   a.k = static_cast<int>(k);
-  a.tiles_n = (a.n + kTileN - 1) / kTileN;
-  a.tiles_m = (a.m + kTileM - 1) / kTileM;
-  const int total = a.tiles_n * a.tiles_m;
-  const unsigned grid = 8u * static_cast<unsigned>((total + 7) / 8);
-  return launch_kernel(linear_kernel, dim3(grid), dim3(kGemmThreads), a, stream, 2 * kSlotBytes);
+  // Up to 8 tokens (16 where there are fewer than 8192 weight rows) the direct kernel is the fastest, except for SwiGLU
+  // where 32 x 32 tiles keep up: at 1 token 8.4 / 19.1 / 22.1 us for n x k = 4096 x 4096 / 12288 x 4096 / 4096 x 11008
+  // (weights at 4.0 / 5.3 / 4.1 TB/s) against 10.4 / 23.3 / 25.6; at 16 tokens 10.2 / 24.8 / 26.8 against 11.4 / 23.6 / 28.5.
+  if (!a.dual && a.m <= (a.n < 8192 ? 16 : 8)) return launch_rows(a, stream);
+  const TileChoice* best = nullptr;
+  float best_cost = 0.0f;
+  for (const TileChoice& c : kTiles) {
+    if ((a.dual && !c.dual) || a.k % c.tk != 0) continue;
+    const float cost = tile_cost(c, a);
+    if (best == nullptr || cost < best_cost) {
+      best = &c;
+      best_cost = cost;
+    }
+  }
+  return best->launch(a, stream);
 }
 
 // ---- RMSNorm ------------------------------------------------------------------------------------

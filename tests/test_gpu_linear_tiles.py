@@ -1,0 +1,59 @@
+"""kvra_linear over the range of its launch rule: every tile shape of the ring kernel (sizes at which the rule picks it,
+ragged in tokens and columns), one k stage only, several tiles per workgroup, odd numbers of stages, and the direct
+kernel for few tokens at the edges of its range.
+
+Bar as for every single operator: fp32 arithmetic and one rounding to bf16, |err| <= 2^-8 |want| + 1e-4 against the
+fp64 oracle (half a unit in the last place is at most 2^-8 of the value; the fp32 sums over k <= 5632 unit-variance terms
+are good to 1e-5)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import kvra_oracle as orc
+from paper_2405_05329_amd import kvra, synth
+from gpu_pipeline import to_bits, to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("m,n,k,mode", [
+    (2221, 5408, 192, "residual"), (1435, 4128, 192, "swiglu"),      # 256 x 256
+    (4093, 2144, 192, "plain"), (849, 4960, 192, "swiglu"),          # 256 x 192
+    (2691, 4384, 192, "residual"),                                   # 192 x 256
+    (2317, 3360, 192, "residual"), (649, 5472, 192, "swiglu"),       # 192 x 192
+    (3789, 1568, 320, "plain"), (389, 5472, 384, "swiglu"),          # 128 x 256
+    (813, 4768, 192, "residual"), (527, 3424, 192, "swiglu"),        # 128 x 192
+    (321, 5728, 192, "plain"), (195, 4384, 192, "swiglu"),           # 128 x 128
+    (325, 4896, 192, "residual"), (197, 3680, 192, "swiglu"),        # 64 x 128
+    (77, 96, 192, "residual"), (77, 96, 192, "swiglu"),              # 64 x 64, k stages of 64
+    (77, 4576, 384, "plain"), (131, 1376, 384, "swiglu"),            # 64 x 64, k shared out over two waves
+    (97, 2080, 384, "residual"), (77, 1440, 384, "swiglu"),          # 32 x 64
+    (39, 96, 384, "residual"), (39, 32, 384, "swiglu"),              # 32 x 32
+    (5000, 4096, 64, "residual"), (4001, 2080, 64, "swiglu"),        # one stage per tile, several tiles per workgroup
+    (6001, 4128, 128, "plain"),                                      # several large tiles per workgroup
+    (1, 32, 64, "plain"), (16, 544, 320, "residual"), (8, 8224, 128, "plain"), (9, 8224, 128, "residual"),
+    (5, 1056, 5632, "residual"), (17, 544, 320, "plain"), (1, 64, 128, "swiglu"),   # few tokens
+])
+def test_linear_tiles(m, n, k, mode):
+    x = synth.normal_bf16(5, 23, 0, (m, k))
+    w = synth.normal_bf16(5, 23, 1, (n, k), std=k ** -0.5)
+    xf, wf = orc.bf16_bits_to_f64(x), orc.bf16_bits_to_f64(w)
+    want = orc.linear(xf, wf)
+    w2 = res = None
+    if mode == "residual":
+        r = synth.normal_bf16(5, 23, 2, (m, n))
+        res = to_dev(r)
+        want = want + orc.bf16_bits_to_f64(r)
+    elif mode == "swiglu":
+        u = synth.normal_bf16(5, 23, 3, (n, k), std=k ** -0.5)
+        w2 = to_dev(u)
+        want = orc.silu(want) * orc.linear(xf, orc.bf16_bits_to_f64(u))
+    pad = 64                                           # rows before and after the output that no launch may touch
+    buf = torch.full((m + 2 * pad, n), 7.0, dtype=torch.bfloat16, device="cuda")
+    kvra.kvra_linear(to_dev(x), to_dev(w), w2, res, buf[pad:pad + m], m, n, k)
+    torch.cuda.synchronize()
+    got = orc.bf16_bits_to_f64(to_bits(buf))
+    assert np.all(got[:pad] == 7.0) and np.all(got[pad + m:] == 7.0), "wrote outside the output"
+    err = np.abs(got[pad:pad + m] - want)
+    worst = np.max(err - (2.0 ** -8 * np.abs(want) + 1e-4))
+    assert worst <= 0, f"{mode} {m}x{n}x{k}: exceeds the one-rounding bound by {worst:.3e} (max err {err.max():.3e})"
