@@ -1,13 +1,25 @@
 // kvra_chunk_attn: flash-style tiled causal attention of one chunk against prefix+chunk keys
 // (Sec. 4.1, Fig. 5(b); App. C listing, weights and output steps) for gfx950.
 //
-// Orientation.  Each wave owns 32 query rows and computes the TRANSPOSED score tile
-//   S^T[key, query] = K_tile . Q^T        (v_mfma_f32_32x32x16_bf16, A = K from LDS, B = Q in VGPRs)
-// so that one lane holds 32 scores of a single query: row max / row sum are in-lane reductions
-// plus one exchange between the two lane halves.  The accumulator layout of S^T is, register
+// Orientation.  Each wave owns 32 query rows, two blocks of 16, and computes the TRANSPOSED score tile
+//   S^T[key, query] = K_tile . Q^T        (v_mfma_f32_16x16x32_bf16, A = K from LDS, B = Q in VGPRs)
+// so that one lane holds scores of one query of either block: row sums are in-lane additions, the exchange between the
+// four lanes that share a row is left to the end.  The accumulator layout of S^T is, register
 // for register, the B-operand layout of the second product
 //   O^T[d, query] += V_tile^T . P^T       (A = V^T via ds_read_b64_tr_b16, B = P in VGPRs)
 // so P never visits LDS.
+//
+// Why 16x16x32 and not 32x32x16 (same bytes read, same registers).  The chip is power-managed, and the 16x16x32 form,
+// which reads and writes its sums half as often, does the same work at 12 % less energy: MFMAs alone on N(0,1) operands, all
+// CUs, 2026 against 1786 TFLOP/s; the tile loop clocks 1.97 instead of 1.65 GHz.  The price is issue: an MFMA keeps its
+// SIMD from issuing vector instructions for 8 cycles whatever its size (80 vector instructions of a softmax: 529 cycles
+// alone, 704 beside 32x32x16 MFMAs, 997 beside 16x16x32 ones), and there are twice as many.  So the form only pays
+// with a lean VALU block: staging without any bookkeeping (buffer loads whose hardware bounds check stands for "past the end
+// of the cache" and "past the piece"), no branch for waves that are done (they leave the loop), one copy of the softmax
+// code.  Both together: 12928 + 1280 tokens, 32 heads x 128: 240 -> 224 us; 16384 causal: 1735 -> 1592 us; 71 heads x 64 on
+// one KV head, 8192 causal: 599 -> 565 us.  The softmax laid between the wave's own P.V MFMAs instead (every wave always
+// has both kinds to issue) is 11 % slower: the SIMD serves its older wave first, and a wave whose next
+// instruction is an MFMA that has to wait holds back its exponentials too.
 //
 // Rows.  With grouped queries (G = n_q_heads / n_kv_heads > 1) the G heads that share a KV head
 // are folded into the row index: virtual row v = token * G + head_in_group.  One K/V tile in LDS
@@ -15,8 +27,8 @@
 // tile wide whatever G is.
 //
 // Schedule.  A workgroup is 8 waves = two groups of 4 (one wave of each group per SIMD).  Per key
-// tile a wave runs an MFMA block (P.V of the previous tile, then K.Q^T of this one: 32 MFMAs at
-// d = 128) and a VALU block (softmax of this tile, staging of future K/V tiles).  While one group
+// tile a wave runs an MFMA block (P.V of the previous tile, then K.Q^T of this one: 64 MFMAs)
+// and a VALU block (softmax of this tile, staging of future K/V tiles).  While one group
 // keeps the matrix pipe busy its SIMD partner does the exponentials on the vector ALU
 // ("ping-pong").  At d = 64 there is a workgroup barrier after each block and the second group
 // starts one barrier late.  At d = 128 there is one barrier per tile step: the first group runs
@@ -55,9 +67,10 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+typedef __attribute__((address_space(3))) bf16x8 lds_bf16x8;
 typedef __attribute__((address_space(3))) void lds_void;
 
 constexpr int kWaves = 8;              // waves per workgroup
@@ -253,33 +266,28 @@ __device__ __forceinline__ float load_coherent(const float* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// The value held by lane ^ 32, and by lane ^ 16.
 __device__ __forceinline__ float other_half(float x) {
-  // value held by lane ^ 32
   auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
   return __uint_as_float((threadIdx.x & 32) ? r[0] : r[1]);
 }
+__device__ __forceinline__ float other_row(float x) {
+  auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float((threadIdx.x & 16) ? r[0] : r[1]);
+}
 
 // 64 lanes x 16 bytes from global memory straight into 1 KiB of consecutive LDS starting at
-// lds_byte_addr (lane l lands at +16 l).  Global address = uniform base + per-lane byte offset.
+// lds_byte_addr (lane l lands at +16 l).  Global address = base of the buffer resource + per-lane byte offset; a lane whose
+// offset lies beyond the resource's size gets zeros, so a tile that straddles the end of what may be read, or lies
+// beyond it, needs no other care.
 // Written as inline assembly on purpose: the compiler guards every LDS-direct load it knows about
 // with a full vmcnt(0) wait (it cannot tell the ring slots apart), which would serialise the
 // prefetch; here completion is awaited by hand, once per block, with s_waitcnt vmcnt(n).
-__device__ __forceinline__ void lds_dma16(const void* uniform_base, unsigned lane_byte_off, unsigned lds_byte_addr) {
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+__device__ __forceinline__ void lds_dma16(u32x4 resource, unsigned lane_byte_off, unsigned lds_byte_addr) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds"
                :
-               : "v"(lane_byte_off), "s"(uniform_base), "s"(lds_byte_addr)
+               : "v"(lane_byte_off), "s"(resource), "s"(lds_byte_addr)
                : "memory", "m0");
-}
-
-// The same under a wave-uniform switch: with on_mask = 0 the instruction is issued with no lanes
-// enabled and moves nothing (no branch around it, so that it can sit in straight-line code).
-__device__ __forceinline__ void lds_dma16_if(unsigned long long on_mask, const void* uniform_base,
-                                             unsigned lane_byte_off, unsigned lds_byte_addr) {
-  unsigned long long saved;
-  asm volatile("s_mov_b32 m0, %3\n\ts_and_saveexec_b64 %0, %4\n\tglobal_load_lds_dwordx4 %1, %2\n\ts_mov_b64 exec, %0"
-               : "=&s"(saved)
-               : "v"(lane_byte_off), "s"(uniform_base), "s"(lds_byte_addr), "s"(on_mask)
-               : "memory", "m0", "scc");
 }
 
 // One piece of work: the queries of row tile pc.qt of kv head pc.g against key tiles [pc.jt0, pc.jt1).
@@ -295,10 +303,11 @@ __device__ __forceinline__ void attend(const AttnArgs& a, u32x4* smem, int* last
                                        ) {
   const int g = pc.g, qt = pc.qt, jt0 = pc.jt0, jt1 = pc.jt1;
   constexpr int BN = key_tile(D);
-  constexpr int MB = BN / 32;              // 32-key blocks of a tile
+  constexpr int KB = BN / 16;              // 16-key blocks of a tile
   constexpr int CPR = D / 8;               // 16-byte pieces per K/V row
-  constexpr int KS = D / 16;               // contraction steps of S^T = K Q^T
-  constexpr int DB = D / 32;               // 32-row blocks of O^T
+  constexpr int KS = D / 32;               // contraction steps of S^T = K Q^T
+  constexpr int DB = D / 16;               // 16-row blocks of O^T
+  constexpr int QB = 2;                    // 16-query blocks of a wave
   constexpr int RPB = 256 / (D * 2);       // rows per 256-byte LDS bank span
   constexpr int TILE = BN * CPR;           // 16-byte pieces per tile
   constexpr int LOADS = TILE / kThreads;   // pieces each thread moves per tile
@@ -313,7 +322,7 @@ __device__ __forceinline__ void attend(const AttnArgs& a, u32x4* smem, int* last
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform by construction
-  const int n = lane & 31, kg = lane >> 5;
+  const int n = lane & 15, g4 = lane >> 4;
   const int phase = wave >> 2;             // 0: first group, 1: second group (one barrier late)
 
   const int VR = a.chunk * a.G;            // virtual rows of this kv head
@@ -322,28 +331,37 @@ __device__ __forceinline__ void attend(const AttnArgs& a, u32x4* smem, int* last
   const int row_hi = min(row_lo + a.rows_per_wg, VR);   // exclusive
   const int v0 = row_lo + wave * 32;
   const bool wave_active = v0 < row_hi;
-  int vr = v0 + n;
-  const bool row_valid = vr < row_hi;
-  if (!row_valid) vr = row_hi - 1;
-  const int r = vr / a.G;
-  const int h = g * a.G + (vr - r * a.G);
-  const int qpos = a.prefix + r;
+  // token and head of this lane's row in either query block (rows past the end repeat the last one); worked out again
+  // where it is needed, so that nothing of it sits in registers during the tile loop
+  auto row_of = [&](int qb, int* r, int* h) __attribute__((always_inline)) -> bool {
+    int vr = v0 + 16 * qb + n;
+    const bool valid = vr < row_hi;
+    if (!valid) vr = row_hi - 1;
+    *r = vr / a.G;
+    *h = g * a.G + (vr - *r * a.G);
+    return valid;
+  };
   const int wmin = a.prefix + min(v0, row_hi - 1) / a.G;        // wave-uniform
   const int wmax = a.prefix + min(v0 + 31, row_hi - 1) / a.G;   // wave-uniform
   const int nt = jt1 - jt0;                                     // key tiles this fragment walks
   // key tiles of the fragment this wave needs (its rows see keys up to wmax)
   const int jw = wave_active ? min(max(wmax / BN + 1 - jt0, 0), nt) : 0;
 
-  // Q fragment: B operand of S^T, lane (n, kg) holds Q[row n][16 ks + 8 kg .. +7], times
+  // Q fragments: B operand of S^T, lane (n, g4) holds Q[row n][32 ks + 8 g4 .. +7], times
   // scale * log2(e) (rounded to bf16 again)
-  bf16x8 qf[KS];
-  {
+  bf16x8 qf[KS][QB];
+  int qpos[QB];
+#pragma unroll
+  for (int qb = 0; qb < QB; ++qb) {
+    int r, h;
+    row_of(qb, &r, &h);
+    qpos[qb] = a.prefix + r;
     const __bf16* qrow = a.q + (static_cast<long long>(r) * a.H + h) * D;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
-      const bf16x8 raw = *reinterpret_cast<const bf16x8*>(qrow + 16 * ks + 8 * kg);
+      const bf16x8 raw = *reinterpret_cast<const bf16x8*>(qrow + 32 * ks + 8 * g4);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) qf[ks][e] = static_cast<__bf16>(static_cast<float>(raw[e]) * a.c_log2);
+      for (int e = 0; e < 8; ++e) qf[ks][qb][e] = static_cast<__bf16>(static_cast<float>(raw[e]) * a.c_log2);
     }
   }
 
@@ -352,97 +370,85 @@ __device__ __forceinline__ void attend(const AttnArgs& a, u32x4* smem, int* last
   // base + 16 l.  Piece p of a tile = (row p / CPR, slot p % CPR); the XOR swizzles that keep the
   // MFMA operand reads free of bank conflicts are applied on the global side: the lane that owns
   // slot (row, slot) fetches column piece  slot ^ f(row)  of that row.
-  //   K is read 16 bytes per lane down 16+ consecutive rows of one column piece;
-  //   V is read (transposing) 8 bytes per lane over 4 consecutive rows x 64 bytes.
-  int ld_row[LOADS];
-  unsigned ld_kcc[LOADS], ld_vcc[LOADS], koff[LOADS], voff[LOADS];
-  const unsigned row_stride = static_cast<unsigned>(a.Hkv) * D;   // elements between cache rows
+  //   K is read 16 bytes per lane down 16 consecutive rows of one column piece;
+  //   V is read (transposing) 8 bytes per lane over 16 consecutive rows x 32 bytes.
+  unsigned koff[LOADS], voff[LOADS];                              // bytes
+  const unsigned row_bytes = static_cast<unsigned>(a.Hkv) * D * 2;   // between cache rows
 #pragma unroll
   for (int i = 0; i < LOADS; ++i) {
     const int p = (i * kWaves + wave) * 64 + lane;
-    ld_row[i] = p / CPR;
-    const int slot = p % CPR;
-    ld_kcc[i] = static_cast<unsigned>(slot ^ ((ld_row[i] / RPB) % CPR)) * 8;
-    ld_vcc[i] = static_cast<unsigned>(slot ^ (4 * ((ld_row[i] / RPB) % (D / 32)))) * 8;
-    koff[i] = 2u * (static_cast<unsigned>(ld_row[i]) * row_stride + ld_kcc[i]);   // bytes
-    voff[i] = 2u * (static_cast<unsigned>(ld_row[i]) * row_stride + ld_vcc[i]);
+    const int row = p / CPR, slot = p % CPR;
+    koff[i] = static_cast<unsigned>(row) * row_bytes + static_cast<unsigned>(slot ^ ((row / RPB) % CPR)) * 16;
+    voff[i] = static_cast<unsigned>(row) * row_bytes + static_cast<unsigned>(slot ^ (2 * ((row / RPB) % (CPR / 2)))) * 16;
   }
-  // offsets for the one tile that straddles the end of the cache: rows past the end repeat the last valid row
-  unsigned koff_last[LOADS], voff_last[LOADS];
-  {
-    const int lim_last = (total - 1) % BN;
-#pragma unroll
-    for (int i = 0; i < LOADS; ++i) {
-      koff_last[i] = 2u * (static_cast<unsigned>(min(ld_row[i], lim_last)) * row_stride + ld_kcc[i]);
-      voff_last[i] = 2u * (static_cast<unsigned>(min(ld_row[i], lim_last)) * row_stride + ld_vcc[i]);
-    }
-  }
-  const __bf16* kbase = a.k + static_cast<long long>(g) * D;
-  const __bf16* vbase = a.v + static_cast<long long>(g) * D;
+  const unsigned long long kbase = reinterpret_cast<unsigned long long>(a.k + static_cast<long long>(g) * D);
+  const unsigned long long vbase = reinterpret_cast<unsigned long long>(a.v + static_cast<long long>(g) * D);
+  const unsigned tile_bytes = BN * row_bytes;
+  const int rows_end = min(total, jt1 * BN);                         // no row beyond is read
 
-  // tile kt of K (or V) -> ring slot buf; rows past the end of the cache repeat the last valid row
-  auto dma_tile = [&](const __bf16* head_base, const unsigned (&off)[LOADS], const unsigned (&cc)[LOADS],
-                      int kt, u32x4* dst) {
-    const __bf16* base = head_base + static_cast<long long>(jt0 + kt) * BN * row_stride;
-    const int lim = total - 1 - (jt0 + kt) * BN;
-    if (lim >= BN - 1) {   // whole tile inside the cache: the precomputed offsets (a real branch, wave-uniform)
-#pragma unroll
-      for (int i = 0; i < LOADS; ++i) {
-        const unsigned lds_addr = static_cast<unsigned>(reinterpret_cast<uintptr_t>(
-            (lds_void*)(dst + (i * kWaves + wave) * 64)));
-        lds_dma16(base, off[i], lds_addr);
-      }
-    } else {
-#pragma unroll
-      for (int i = 0; i < LOADS; ++i) {
-        const unsigned o32 = 2u * (static_cast<unsigned>(min(ld_row[i], lim)) * row_stride + cc[i]);
-        const unsigned lds_addr = static_cast<unsigned>(reinterpret_cast<uintptr_t>(
-            (lds_void*)(dst + (i * kWaves + wave) * 64)));
-        lds_dma16(base, o32, lds_addr);
-      }
-    }
+  auto uniform = [](unsigned v) __attribute__((always_inline)) -> unsigned {   // a scalar register for what all lanes agree on
+    return static_cast<unsigned>(__builtin_amdgcn_readfirstlane(static_cast<int>(v)));
   };
-  // staging step s moves K tile s+1 and V tile s; returns the number of loads it issued
-  auto stage = [&](int s) -> int {
-    int cnt = 0;
-    if (s + 1 < nt) { dma_tile(kbase, koff, ld_kcc, s + 1, ldsK((s + 1) % kStages)); cnt += LOADS; }
-    if (s < nt) { dma_tile(vbase, voff, ld_vcc, s, ldsV(s % kStages)); cnt += LOADS; }
-    return cnt;
+  // buffer resource over the rows of tile t of K or V that exist (t counts from the piece's first tile)
+  auto tile_resource = [&](unsigned long long head_base, int t) __attribute__((always_inline)) -> u32x4 {
+    const unsigned long long at = head_base + static_cast<unsigned long long>(jt0 + t) * tile_bytes;
+    const int rows = min(max(rows_end - (jt0 + t) * BN, 0), BN);
+    return u32x4{uniform(static_cast<unsigned>(at)), uniform(static_cast<unsigned>(at >> 32) & 0xFFFFu),
+                 uniform(rows * row_bytes), 0x00020000u};
+  };
+  // tile t of K (or V) -> ring slot dst
+  auto dma_tile = [&](unsigned long long head_base, const unsigned (&off)[LOADS], int t, u32x4* dst) __attribute__((always_inline)) {
+    const u32x4 res = tile_resource(head_base, t);
+#pragma unroll
+    for (int i = 0; i < LOADS; ++i)
+      lds_dma16(res, off[i], static_cast<unsigned>(reinterpret_cast<uintptr_t>((lds_void*)(dst + (i * kWaves + wave) * 64))));
   };
 
-  f32x16 o[DB];
+  f32x4 o[DB][QB];
 #pragma unroll
   for (int db = 0; db < DB; ++db)
 #pragma unroll
-    for (int e = 0; e < 16; ++e) o[db][e] = 0.0f;
+    for (int qb = 0; qb < QB; ++qb)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[db][qb][e] = 0.0f;
   // exponent reference of the row (in base-2 score units); trails the running max by a bounded
   // amount (see kSumLimit).  kNoKeyYet marks a row that has not met a visible key yet (possible
   // when a fragment starts beyond the row's last key): its scores are formed against 0 and its
   // first visible keys send the wave through the exact path, which sets the reference.
-  float m = kNoKeyYet;
-  float l = 0.0f;        // running row sum of this lane's half of the keys
+  float m[QB], l[QB];    // l: running row sum of this lane's quarter of the keys
   // start value of the score accumulators: minus the exponent reference (0 while the row has none),
   // so that the MFMAs deliver  s c - m  directly (c is folded into the Q fragment)
-  f32x16 sref;
+  f32x4 sref[QB];
 #pragma unroll
-  for (int e = 0; e < 16; ++e) sref[e] = 0.0f;
+  for (int qb = 0; qb < QB; ++qb) {
+    m[qb] = kNoKeyYet;
+    l[qb] = 0.0f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) sref[qb][e] = 0.0f;
+  }
 
-  // lane-constant parts of the LDS read addresses
-  const int k_sw = (n / RPB) % CPR;                       // K swizzle of row 32 mb + n
-  const int vi = lane & 15, vmh = (lane >> 4) & 1;        // position inside the 16-lane transpose block
-  const int v_row0 = 4 * kg + (vi >> 2);                  // + 32 mb + 16 s + 8 e
-  const int v_sw = 4 * ((v_row0 / RPB) % (D / 32));
-  const int v_cc0 = 2 * vmh + ((vi & 3) >> 1);            // + 4 db
-  const int v_sub = (vi & 1) * 4;                         // element offset inside the 16-byte piece
+  // lane-constant parts of the LDS read addresses, in bytes: K row 16 kb + n, column piece 4 ks + g4; V row
+  // 32 kk + 16 b + 4 g4 + n / 4 (n is the position in the 16-lane transpose block), columns 16 db + 4 (n % 4)
+  const unsigned k_base = static_cast<unsigned>(reinterpret_cast<uintptr_t>((lds_void*)ldsK(0)));
+  const unsigned v_base = static_cast<unsigned>(reinterpret_cast<uintptr_t>((lds_void*)ldsV(0)));
+  unsigned k_addr[KS], v_addr[DB];
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks)
+    k_addr[ks] = k_base + static_cast<unsigned>(n * CPR + ((4 * ks + g4) ^ ((n / RPB) % CPR))) * 16;
+#pragma unroll
+  for (int db = 0; db < DB; ++db) {
+    const int row = 4 * g4 + (n >> 2);
+    v_addr[db] = v_base + static_cast<unsigned>(row * CPR + ((2 * db + ((n & 3) >> 1)) ^ (2 * ((row / RPB) % (CPR / 2))))) * 16 + (n & 1) * 8;
+  }
+  // opaque: everything else is an immediate offset from these, not a register of its own
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(k_addr[ks]));
+#pragma unroll
+  for (int db = 0; db < DB; ++db) asm volatile("" : "+v"(v_addr[db]));
 
-  // Staging state of the tile loop.  At tile step j this wave (st = j + phase) sends off its pieces of
-  // K tile st + 2 and V tile st + 1: two running pointers, advanced by one tile per step, and the
-  // LDS byte addresses of the ring slots in the order this wave meets them (slot_k[r] is where the K
-  // tile goes at a step with j % kStages == r; the V tile of that step goes to slot_v[r]).
-  const long long tile_elems = static_cast<long long>(BN) * row_stride;
-  const __bf16* kp = kbase + (jt0 + 2 + phase) * tile_elems;
-  const __bf16* vp = vbase + (jt0 + 1 + phase) * tile_elems;
-  const int kt_ragged = (total % BN != 0) ? (total - 1) / BN - jt0 : -1;   // the tile that straddles the end
+  // Staging of the tile loop.  At tile step j this wave (st = j + phase) sends off its pieces of K tile st + 2 and V tile
+  // st + 1; slot_k[r] is the LDS byte address that K tile goes to at a step with j % kStages == r, slot_v[r] that of
+  // the V tile.
   unsigned slot_k[kStages], slot_v[kStages];
 #pragma unroll
   for (int r = 0; r < kStages; ++r) {
@@ -453,9 +459,10 @@ __device__ __forceinline__ void attend(const AttnArgs& a, u32x4* smem, int* last
   // ---- prologue: K tiles 0..2 and V tiles 0..1 on their way into LDS -----------------------------
   // the first MFMA block multiplies a zero P by the ring slot "before" V tile 0: make it finite
   for (int i = tid; i < TILE; i += kThreads) ldsV(kStages - 1)[i] = u32x4{0u, 0u, 0u, 0u};
-  dma_tile(kbase, koff, ld_kcc, 0, ldsK(0));
-  stage(0);
-  stage(1);
+#pragma unroll
+  for (int t = 0; t < 3; ++t) dma_tile(kbase, koff, t, ldsK(t));
+#pragma unroll
+  for (int t = 0; t < 2; ++t) dma_tile(vbase, voff, t, ldsV(t));
   // every load so far (the Q fragment included) is drained here: a load left pending across the
   // loop entry would make the compiler guard the loop's MFMAs with vmcnt waits
   __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
@@ -463,19 +470,30 @@ __device__ __forceinline__ void attend(const AttnArgs& a, u32x4* smem, int* last
   if (!ONE_BARRIER && phase == 1) __syncthreads();   // second group runs one barrier behind the first
   KVRA_TRACE_STAMP(trace_rec, 1);
 
-  f32x16 s[MB];
-  bf16x8 pf[MB][2];
+  f32x4 s[KB][QB];
+  u32x4 pf[KB / 2][QB];   // P of the last tile, two bf16 to a register
 #pragma unroll
-  for (int mb = 0; mb < MB; ++mb)
+  for (int kk = 0; kk < KB / 2; ++kk)
 #pragma unroll
-    for (int si = 0; si < 2; ++si)
-#pragma unroll
-      for (int e = 0; e < 8; ++e) pf[mb][si][e] = static_cast<__bf16>(0.0f);
+    for (int qb = 0; qb < QB; ++qb)
+      pf[kk][qb] = u32x4{0u, 0u, 0u, 0u};
 
-  // steps whose staging needs no bookkeeping (see the VALU block): K tile st + 2 and V tile st + 1 both exist
-  // and neither straddles the end of the cache
-  const int bulk_lo = 1 - phase;
-  const int bulk_hi = min(nt - 2, kt_ragged >= 0 ? kt_ragged - 2 : nt) - phase;
+  bool none_unset = false;   // every row of the wave has an exponent reference
+
+  // V fragment i = (kk, db) of the tile in the ring slot at byte offset slot; contraction slot 8 g4 + 4 b + t of P.V step kk
+  // is key 32 kk + 16 b + 4 g4 + t on both operands
+  constexpr int NV = KB / 2 * DB;
+  auto vread = [&](int i, unsigned slot) __attribute__((always_inline)) -> bf16x8 {
+    const int kk = i / DB, db = i % DB;
+    s16x8 vf;
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      const s16x4 t = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+          (lds_s16x4*)static_cast<uintptr_t>(v_addr[db] + slot + (32 * kk + 16 * b) * CPR * 16));
+      vf[4 * b + 0] = t[0]; vf[4 * b + 1] = t[1]; vf[4 * b + 2] = t[2]; vf[4 * b + 3] = t[3];
+    }
+    return __builtin_bit_cast(bf16x8, vf);
+  };
 
   // One tile step; RS = j % kStages is a compile-time value so that every LDS operand address is
   // a loop-invariant per-lane register plus an immediate.
@@ -483,34 +501,17 @@ __device__ __forceinline__ void attend(const AttnArgs& a, u32x4* smem, int* last
     constexpr int RS = decltype(rs_tag)::value;
     // ================= MFMA block =================
     // P.V of tile j-1 followed by K.Q^T of tile j as ONE software-pipelined stream of operand reads
-    // and MFMAs: the LDS read of op i + PF is issued before the MFMA of op i, and the compiler is
-    // told not to move anything across the steps.  The block runs whole for j <= jw: at j = 0 the
-    // P fragment is zero and the "previous" V slot was zero-filled, at j = jw the scores it forms
-    // are never looked at (the price is one tile's worth of MFMAs per wave, the gain is a single
-    // straight-line block).
-    if (j <= jw) {
-      const short* Vb = reinterpret_cast<const short*>(ldsV((RS + kStages - 1) % kStages));
-      const bf16x8* Kb = reinterpret_cast<const bf16x8*>(ldsK(RS));
-      // contraction slot 4e + t of P.V step (mb, si) is key 32 mb + 16 si + 8 e + 4 kg + t on both operands
-      auto vread = [&](int idx) -> bf16x8 {
-        const int mb = idx / (2 * DB), si = (idx / DB) % 2, db = idx % DB;
-        s16x8 vf;
-#pragma unroll
-        for (int e = 0; e < 2; ++e) {
-          const int row = 32 * mb + 16 * si + 8 * e + v_row0;
-          const int slot = (4 * db + v_cc0) ^ v_sw;
-          const short* p = Vb + (row * CPR + slot) * 8 + v_sub;
-          const s16x4 t = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)p);
-          vf[4 * e + 0] = t[0]; vf[4 * e + 1] = t[1]; vf[4 * e + 2] = t[2]; vf[4 * e + 3] = t[3];
-        }
-        return __builtin_bit_cast(bf16x8, vf);
+    // and MFMAs: the LDS read of fragment i + PF is issued before the MFMAs of fragment i, and the compiler is
+    // told not to move anything across the steps.  At j = 0 the P fragment is zero and the "previous" V slot was
+    // zero-filled.
+    {
+      constexpr unsigned VSLOT = (RS + kStages - 1) % kStages * TILE * 16;
+      constexpr int N = NV + KB * KS;
+      auto frag = [&](int i) __attribute__((always_inline)) -> bf16x8 {
+        if (i < NV) return vread(i, VSLOT);
+        const int ks = (i - NV) / KB, kb = (i - NV) % KB;
+        return *(lds_bf16x8*)static_cast<uintptr_t>(k_addr[ks] + RS * TILE * 16 + 16 * kb * CPR * 16);
       };
-      auto kread = [&](int idx) -> bf16x8 {
-        const int ks = idx / MB, mb = idx % MB;
-        return Kb[(32 * mb + n) * CPR + ((2 * ks + kg) ^ k_sw)];
-      };
-      constexpr int N0 = 2 * MB * DB, N = N0 + MB * KS;
-      auto frag = [&](int i) -> bf16x8 { return (i < N0) ? vread(i) : kread(i - N0); };
       bf16x8 fq[PF];
 #pragma unroll
       for (int i = 0; i < PF; ++i) fq[i] = frag(i);
@@ -519,13 +520,16 @@ __device__ __forceinline__ void attend(const AttnArgs& a, u32x4* smem, int* last
       for (int i = 0; i < N; ++i) {
         const bf16x8 cur = fq[i % PF];
         if (i + PF < N) fq[i % PF] = frag(i + PF);
-        if (i < N0) {
-          const int mb = i / (2 * DB), si = (i / DB) % 2, db = i % DB;
-          o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cur, pf[mb][si], o[db], 0, 0, 0);
-        } else
-        {
-          const int q = i - N0;
-          s[q % MB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cur, qf[q / MB], q < MB ? sref : s[q % MB], 0, 0, 0);
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) {
+          if (i < NV) {
+            o[i % DB][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cur, __builtin_bit_cast(bf16x8, pf[i / DB][qb]), o[i % DB][qb], 0, 0, 0);
+            asm volatile("" : "+v"(o[i % DB][qb]));
+          } else {
+            const int q = i - NV;
+            s[q % KB][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cur, qf[q / KB][qb], q < KB ? sref[qb] : s[q % KB][qb], 0, 0, 0);
+            asm volatile("" : "+v"(s[q % KB][qb]));
+          }
         }
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -536,133 +540,143 @@ __device__ __forceinline__ void attend(const AttnArgs& a, u32x4* smem, int* last
     // staging: this wave's step is j + phase (the late group is one tile ahead in tile numbers);
     // tiles K(st+2), V(st+1) start their trip now and are awaited one period later
     const int st = j + phase;
-    // The 2 LOADS loads are handed out one at a time and spread over the softmax below.  A tile
-    // beyond the fragment is "loaded" with no lane enabled: no branch, so the loads can sit in
-    // straight-line code.  The ragged last tile of the cache takes the clamped offsets.
-    // At head_dim 64, where this block is the longer of the two, only the steps near either end of the piece
-    // work any of this out: in the bulk of the steps, [bulk_lo, bulk_hi), both tiles exist and neither is
-    // the ragged one (a wave-uniform branch around scalar work: every scalar instruction of this block is
-    // issue time the matrix pipe waits for; measured +1.5 % at head_dim 64, -1 % at 128, where it stays out).
-    bool k_on = true, v_on = true, k_rag = false, v_rag = false;
-    if (D != 64 || j < bulk_lo || j >= bulk_hi) {
-      k_on = st >= 1 && st + 2 < nt;
-      v_on = st >= 1 && st + 1 < nt;
-      k_rag = st + 2 == kt_ragged;
-      v_rag = st + 1 == kt_ragged;
-    }
-    const int issued = (k_on ? LOADS : 0) + (v_on ? LOADS : 0);
-    const unsigned long long k_mask = __builtin_amdgcn_ballot_w64(k_on), v_mask = __builtin_amdgcn_ballot_w64(v_on);
+    // (handed out one at a time between the exponentials; what does not exist is "loaded" as zeros: no branch, no
+    // bookkeeping - every instruction of this block, scalar ones too, is time the matrix pipe waits for)
+    const u32x4 k_res = tile_resource(kbase, st + 2), v_res = tile_resource(vbase, st + 1);
     auto stage_piece = [&](int idx) __attribute__((always_inline)) {
       __builtin_amdgcn_sched_barrier(0);
       if (idx < LOADS)
-        lds_dma16_if(k_mask, kp, k_rag ? koff_last[idx] : koff[idx], slot_k[RS] + idx * (kWaves * 64 * 16));
+        lds_dma16(k_res, koff[idx], slot_k[RS] + idx * (kWaves * 64 * 16));
       else
-        lds_dma16_if(v_mask, vp, v_rag ? voff_last[idx - LOADS] : voff[idx - LOADS],
-                     slot_v[RS] + (idx - LOADS) * (kWaves * 64 * 16));
+        lds_dma16(v_res, voff[idx - LOADS], slot_v[RS] + (idx - LOADS) * (kWaves * 64 * 16));
       __builtin_amdgcn_sched_barrier(0);
     };
-    if (j >= jw) {
-#pragma unroll
-      for (int idx = 0; idx < 2 * LOADS; ++idx) stage_piece(idx);
-    }
-    if (j < jw) {
-      // register e of block mb is key  j*BN + 32 mb + 8 (e/4) + 4 kg + e%4  of query n
+    {
+      // register e of block (kb, qb) is key  j*BN + 16 kb + 4 g4 + e  of query 16 qb + n
       if ((jt0 + j) * BN + BN - 1 > wmin) {
-        int rel = qpos - (jt0 + j) * BN - 4 * kg;   // largest still-visible key offset (minus 4 kg)
-        // opaque to the optimiser: otherwise the 32 compares below become 32 loop-carried
-        // counters that are kept up to date (and kept in registers) on every tile
-        asm volatile("" : "+v"(rel));
         const float ninf = -INFINITY;
-        // compare and select one element at a time through vcc (written out: left to itself the
-        // compiler keeps all 32 lane masks alive in scalar registers, which spills others)
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
+        for (int qb = 0; qb < QB; ++qb) {
+          int rel = qpos[qb] - (jt0 + j) * BN - 4 * g4;   // largest still-visible key offset (minus 4 g4)
+          // opaque to the optimiser: otherwise the compares below become loop-carried
+          // counters that are kept up to date (and kept in registers) on every tile
+          asm volatile("" : "+v"(rel));
+          // compare and select one element at a time through vcc (written out: left to itself the
+          // compiler keeps all the lane masks alive in scalar registers, which spills others)
 #pragma unroll
-          for (int e = 0; e < 16; ++e) {
-            float x = s[mb][e];
-            asm volatile("v_cmp_gt_i32 vcc, %1, %2\n\tv_cndmask_b32 %0, %0, %3, vcc"
-                         : "+v"(x)
-                         : "n"(32 * mb + 8 * (e / 4) + (e % 4)), "v"(rel), "v"(ninf)
-                         : "vcc");
-            s[mb][e] = x;
-          }
+          for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              float x = s[kb][qb][e];
+              asm volatile("v_cmp_gt_i32 vcc, %1, %2\n\tv_cndmask_b32 %0, %0, %3, vcc"
+                           : "+v"(x)
+                           : "n"(16 * kb + e), "v"(rel), "v"(ninf)
+                           : "vcc");
+              s[kb][qb][e] = x;
+            }
+        }
       }
       // ---- online softmax (base 2) with a lazily moved exponent reference -------------------
-      // weights of this tile: p = exp2(s) against the reference in force (MOVED: exp2(s - delta)
-      // against one that was just raised by delta), rounded to bf16 in pairs for the P.V product;
-      // the row sum adds the unrounded values.  Returns this lane's part of the row sum.  The first
-      // pass also carries the staging loads, one every few exponentials.
-      auto weights = [&](auto moved_tag, const float delta) __attribute__((always_inline)) -> float {
-        constexpr bool MOVED = decltype(moved_tag)::value;
-        typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-        float sum0 = 0.0f, sum1 = 0.0f;
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-          for (int e = 0; e < 16; e += 2) {
-            if constexpr (!MOVED) {
-              constexpr int PAIRS = MB * 8, EVERY = PAIRS / (2 * LOADS);
-              const int pair = mb * 8 + e / 2;
-              if (pair % EVERY == 0) stage_piece(pair / EVERY);
-            }
-            const float p0 = __builtin_amdgcn_exp2f(MOVED ? s[mb][e] - delta : s[mb][e]);
-            const float p1 = __builtin_amdgcn_exp2f(MOVED ? s[mb][e + 1] - delta : s[mb][e + 1]);
-            const bf16x2 pp = {static_cast<__bf16>(p0), static_cast<__bf16>(p1)};
-            if ((e / 2) % 2) sum1 += p0 + p1;
-            else sum0 += p0 + p1;
-            pf[mb][e / 8][e % 8] = pp[0];
-            pf[mb][e / 8][e % 8 + 1] = pp[1];
-          }
-        return sum0 + sum1;
-      };
-      // Optimistic pass: no row maximum is formed.  As long as the scores stay within reach of m the
+      // weights of this tile: p = exp2(s) against the reference in force, rounded to bf16 in pairs for the P.V
+      // product; the row sums add the unrounded values.  Between them the staging loads, one every few exponentials.
+      // Optimistic: no row maximum is formed.  As long as the scores stay within reach of m the
       // weights are modest; a lane whose partial sum gets out of hand, or whose row has no reference
-      // yet, sends the whole wave through the exact path: row maximum, m, l, O and the accumulator
-      // start value re-based to it, weights formed again.
-      float psum = weights(std::false_type{}, 0.0f);
-      const bool unset = m == kNoKeyYet;
-      if (__builtin_amdgcn_ballot_w64(!(psum < kSumLimit) || unset) != 0) {
-        float tmax = s[0][0];   // relative to the reference in force
+      // yet, sends the whole wave round again: row maximum, m, l, O, the scores and the accumulator
+      // start value re-based to it, weights formed again (and the same loads issued again: the same bytes to the same
+      // place).  Once round again is enough: the weights are at most 1 then.
+      constexpr int PAIRS = QB * KB * 2;
+      float psum[QB][2];
+      for (bool again = false;;) {
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
+        for (int pair = 0; pair < PAIRS; ++pair) {
+          if (pair % (PAIRS / (2 * LOADS)) == 0) stage_piece(pair / (PAIRS / (2 * LOADS)));
+          typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+          const int kb = pair / (2 * QB), qb = pair / 2 % QB, e = 2 * (pair % 2);
+          const float p0 = __builtin_amdgcn_exp2f(s[kb][qb][e]);
+          const float p1 = __builtin_amdgcn_exp2f(s[kb][qb][e + 1]);
+          const bf16x2 pp = {static_cast<__bf16>(p0), static_cast<__bf16>(p1)};
+          if (kb == 0) psum[qb][pair % 2] = p0 + p1;
+          else psum[qb][pair % 2] += p0 + p1;
+          pf[kb / 2][qb][2 * (kb % 2) + e / 2] = __builtin_bit_cast(unsigned, pp);
+        }
+        bool out_of_hand = false;
 #pragma unroll
-          for (int e = 0; e < 16; ++e) tmax = fmaxf(tmax, s[mb][e]);
-        tmax = fmaxf(tmax, other_half(tmax));
-        // a row without reference takes its maximum as one, once it has met a visible key
-        const bool seen = tmax > -INFINITY;
-        const float delta = unset ? (seen ? tmax : 0.0f) : fmaxf(tmax, 0.0f);
-        const float alpha = unset ? 1.0f : __builtin_amdgcn_exp2f(-delta);
-        if (unset) { if (seen) m = tmax; }
-        else m += delta;
-        l *= alpha;
+        for (int qb = 0; qb < QB; ++qb) out_of_hand |= !(psum[qb][0] + psum[qb][1] < kSumLimit);
+        if (again || (__builtin_amdgcn_ballot_w64(out_of_hand) == 0 && none_unset)) break;
+        again = true;
 #pragma unroll
-        for (int db = 0; db < DB; ++db)
+        for (int qb = 0; qb < QB; ++qb) {
+          float tmax = s[0][qb][0];   // relative to the reference in force
 #pragma unroll
-          for (int e = 0; e < 16; ++e) o[db][e] *= alpha;
+          for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) sref[e] -= delta;
-        psum = weights(std::true_type{}, delta);
+            for (int e = 0; e < 4; ++e) tmax = fmaxf(tmax, s[kb][qb][e]);
+          tmax = fmaxf(tmax, other_half(tmax));
+          tmax = fmaxf(tmax, other_row(tmax));
+          // a row without reference takes its maximum as one, once it has met a visible key
+          const bool seen = tmax > -INFINITY, unset = m[qb] == kNoKeyYet;
+          const float delta = unset ? (seen ? tmax : 0.0f) : fmaxf(tmax, 0.0f);
+          const float alpha = unset ? 1.0f : __builtin_amdgcn_exp2f(-delta);
+          if (unset) { if (seen) m[qb] = tmax; }
+          else m[qb] += delta;
+          l[qb] *= alpha;
+#pragma unroll
+          for (int db = 0; db < DB; ++db)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[db][qb][e] *= alpha;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) sref[qb][e] -= delta;
+#pragma unroll
+          for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s[kb][qb][e] -= delta;
+        }
+        none_unset = __builtin_amdgcn_ballot_w64(m[0] == kNoKeyYet || m[1] == kNoKeyYet) == 0;
       }
-      l += psum;
+#pragma unroll
+      for (int qb = 0; qb < QB; ++qb) l[qb] += psum[qb][0] + psum[qb][1];
     }
-    kp += tile_elems;
-    vp += tile_elems;
     // everything issued before this block (tiles K(st+1), V(st)) must have landed before the barrier
-    if (issued == 2 * LOADS) __builtin_amdgcn_s_waitcnt(0x0F70 | (2 * LOADS));
-    else if (issued == LOADS) __builtin_amdgcn_s_waitcnt(0x0F70 | LOADS);
-    else __builtin_amdgcn_s_waitcnt(0x0F70);
+    __builtin_amdgcn_s_waitcnt(0x0F70 | (2 * LOADS));
     if (!ONE_BARRIER || phase == 0) __syncthreads();
   };
-  for (int j0 = 0; j0 <= nt; j0 += kStages) {
+  for (int j0 = 0; j0 < jw; j0 += kStages) {
     tile_step(j0, std::integral_constant<int, 0>{});
-    if (j0 + 1 <= nt) tile_step(j0 + 1, std::integral_constant<int, 1>{});
-    if (j0 + 2 <= nt) tile_step(j0 + 2, std::integral_constant<int, 2>{});
+    if (j0 + 1 < jw) tile_step(j0 + 1, std::integral_constant<int, 1>{});
+    if (j0 + 2 < jw) tile_step(j0 + 2, std::integral_constant<int, 2>{});
   }
   static_assert(kStages == 3, "the unrolled loop above is written for a ring of three");
+  // P.V of the last tile this wave looks at; from here on the wave only takes its share of the staging for the others
+  if (jw > 0) {
+    const unsigned slot = static_cast<unsigned>((jw - 1) % kStages) * TILE * 16;
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const bf16x8 cur = vread(i, slot);
+#pragma unroll
+      for (int qb = 0; qb < QB; ++qb)
+        o[i % DB][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cur, __builtin_bit_cast(bf16x8, pf[i / DB][qb]), o[i % DB][qb], 0, 0, 0);
+    }
+  }
+  for (int j = jw; j <= nt; ++j) {
+    if (!ONE_BARRIER || phase == 1) __syncthreads();
+    const int st = j + phase;
+    dma_tile(kbase, koff, st + 2, ldsK((st + 2) % kStages));
+    dma_tile(vbase, voff, st + 1, ldsV((st + 1) % kStages));
+    __builtin_amdgcn_s_waitcnt(0x0F70 | (2 * LOADS));
+    if (!ONE_BARRIER || phase == 0) __syncthreads();
+  }
   if (!ONE_BARRIER && phase == 0) __syncthreads();   // both groups execute the same number of barriers
+  // the zeros behind the last tile have landed for every wave: the next piece may fill the ring
+  __builtin_amdgcn_s_waitcnt(0x0F70);
+  __syncthreads();
   KVRA_TRACE_STAMP(trace_rec, 2);
 
   // ---- epilogue: O / l, bf16, store -----------------------------------------------------------
+#pragma unroll
+  for (int qb = 0; qb < QB; ++qb) {        // the whole row's sum, in each of the row's four lanes
+    l[qb] += other_half(l[qb]);
+    l[qb] += other_row(l[qb]);
+  }
   if (pc.slot >= 0) {
     // [wave][register][lane]: every store is 256 consecutive bytes per wave.  The pieces of a unit are
     // handed from workgroup to workgroup without a fence (a device-scope fence writes back and invalidates
@@ -670,7 +684,7 @@ __device__ __forceinline__ void attend(const AttnArgs& a, u32x4* smem, int* last
     // gone): the partial results are written with device-coherent stores, the wave waits until all of
     // them have been acknowledged, and only then, after a workgroup barrier, are the unit's key tiles
     // added to its counter; the piece that completes the count reads the others with device-coherent loads.
-    constexpr int WAVE_FLOATS = (DB * 16 + 2) * 64;
+    constexpr int O_FLOATS = DB * QB * 4 * 64, WAVE_FLOATS = O_FLOATS + 2 * 64;
     float* group_slots = a.scratch + static_cast<long long>(x) * slots_per_group(a) * kPartialFloats(D);
     int* counter = a.counters + x * kMaxSlots + pc.seg;
     // A piece looks at the unit's counter first: if every other piece has already been counted, it is the
@@ -690,11 +704,12 @@ __device__ __forceinline__ void attend(const AttnArgs& a, u32x4* smem, int* last
     if (!all_others_counted) {
       float* p = group_slots + static_cast<long long>(pc.slot) * kPartialFloats(D) + wave * WAVE_FLOATS + lane;
 #pragma unroll
-      for (int db = 0; db < DB; ++db)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) store_coherent(p + (db * 16 + e) * 64, o[db][e]);
-      store_coherent(p + (DB * 16) * 64, m);
-      store_coherent(p + (DB * 16 + 1) * 64, l);
+      for (int i = 0; i < DB * QB * 4; ++i) store_coherent(p + i * 64, o[i / 8][i / 4 % 2][i % 4]);
+      // m and l of row 16 qb + n at lane 16 qb + n
+      if (g4 < QB) {
+        store_coherent(p + O_FLOATS, g4 == 0 ? m[0] : m[1]);
+        store_coherent(p + O_FLOATS + 64, g4 == 0 ? l[0] : l[1]);
+      }
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       __syncthreads();
       if (tid == 0) {
@@ -714,39 +729,53 @@ __device__ __forceinline__ void attend(const AttnArgs& a, u32x4* smem, int* last
     // This piece's own partial result is not read back: what it stored is what its registers hold, so taking
     // it from there when its turn in the order comes gives the same bits and saves one of the unit's reads.
     const float* mine = group_slots + wave * WAVE_FLOATS + lane;
-    f32x16 own_o[DB];
+    f32x4 own_o[DB][QB];
+    float own_m[QB], own_l[QB];
 #pragma unroll
-    for (int db = 0; db < DB; ++db) own_o[db] = o[db];
-    const float own_m = m, own_l = l;
-    m = kNoKeyYet;
-    l = 0.0f;
+    for (int qb = 0; qb < QB; ++qb) {
+      own_m[qb] = m[qb];
+      own_l[qb] = l[qb];
+      m[qb] = kNoKeyYet;
+      l[qb] = 0.0f;
 #pragma unroll
-    for (int db = 0; db < DB; ++db)
+      for (int db = 0; db < DB; ++db) {
+        own_o[db][qb] = o[db][qb];
 #pragma unroll
-      for (int e = 0; e < 16; ++e) o[db][e] = 0.0f;
+        for (int e = 0; e < 4; ++e) o[db][qb][e] = 0.0f;
+      }
+    }
     auto merge_in = [&](int slot) {
       const float* p = mine + static_cast<long long>(slot) * kPartialFloats(D);
-      float po[DB * 16];
-      float pm, pl;
+      float po[DB * QB * 4];
+      float pm[QB], pl[QB];
       if (slot == pc.slot) {
 #pragma unroll
-        for (int i = 0; i < DB * 16; ++i) po[i] = own_o[i / 16][i % 16];
-        pm = own_m;
-        pl = own_l;
+        for (int i = 0; i < DB * QB * 4; ++i) po[i] = own_o[i / 8][i / 4 % 2][i % 4];
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) {
+          pm[qb] = own_m[qb];
+          pl[qb] = own_l[qb];
+        }
       } else {
 #pragma unroll
-        for (int i = 0; i < DB * 16; ++i) po[i] = load_coherent(p + i * 64);
-        pm = load_coherent(p + (DB * 16) * 64);
-        pl = load_coherent(p + (DB * 16 + 1) * 64);
+        for (int i = 0; i < DB * QB * 4; ++i) po[i] = load_coherent(p + i * 64);
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) {
+          pm[qb] = load_coherent(p - lane + n + 16 * qb + O_FLOATS);
+          pl[qb] = load_coherent(p - lane + n + 16 * qb + O_FLOATS + 64);
+        }
       }
-      const float mn = fmaxf(m, pm);
-      const float wa = __builtin_amdgcn_exp2f(m - mn), wb = __builtin_amdgcn_exp2f(pm - mn);
-      m = mn;
-      l = fmaf(pl, wb, l * wa);
 #pragma unroll
-      for (int db = 0; db < DB; ++db)
+      for (int qb = 0; qb < QB; ++qb) {
+        const float mn = fmaxf(m[qb], pm[qb]);
+        const float wa = __builtin_amdgcn_exp2f(m[qb] - mn), wb = __builtin_amdgcn_exp2f(pm[qb] - mn);
+        m[qb] = mn;
+        l[qb] = fmaf(pl[qb], wb, l[qb] * wa);
 #pragma unroll
-        for (int e = 0; e < 16; ++e) o[db][e] = fmaf(po[db * 16 + e], wb, o[db][e] * wa);
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) o[db][qb][e] = fmaf(po[(db * QB + qb) * 4 + e], wb, o[db][qb][e] * wa);
+      }
     };
     if (pc.seg < a.cut) merge_in(a.slots + a.segments + seg_to_unit(a, pc.seg));
     static_assert(kMaxSlots <= 256, "four votes of 64 lanes cover the table");
@@ -768,19 +797,27 @@ __device__ __forceinline__ void attend(const AttnArgs& a, u32x4* smem, int* last
       if (64 * (k + 1) >= a.slots) break;
     }
   }
-  const float lsum = l + other_half(l);
-  if (wave_active && row_valid) {
-    const float inv = 1.0f / lsum;
-    __bf16* orow = a.out + (static_cast<long long>(r) * a.H + h) * D;
+  // Register e of block (db, qb) is column 16 db + 4 g4 + e of row n.  Two blocks side by side trade registers between
+  // odd and even 16-lane rows: a lane then holds 8 consecutive of the 32 columns, from 16 (g4 % 2) + 8 (g4 / 2), and a
+  // store covers 16 rows x 64 consecutive bytes.
+  const int col0 = 16 * (g4 & 1) + 8 * (g4 >> 1);
 #pragma unroll
-    for (int db = 0; db < DB; ++db)
+  for (int qb = 0; qb < QB; ++qb) {
+    int r, h;
+    const bool row_valid = row_of(qb, &r, &h);
+    const float inv = 1.0f / l[qb];
+    __bf16* orow = a.out + (static_cast<long long>(r) * a.H + h) * D + col0;
 #pragma unroll
-      for (int r4 = 0; r4 < 4; ++r4) {
-        bf16x4 w;
+    for (int db = 0; db < DB; db += 2) {
+      bf16x8 w;
 #pragma unroll
-        for (int t = 0; t < 4; ++t) w[t] = static_cast<__bf16>(o[db][4 * r4 + t] * inv);
-        *reinterpret_cast<bf16x4*>(orow + 32 * db + 8 * r4 + 4 * kg) = w;
+      for (int e = 0; e < 4; ++e) {
+        auto t = __builtin_amdgcn_permlane16_swap(__float_as_uint(o[db][qb][e] * inv), __float_as_uint(o[db + 1][qb][e] * inv), false, false);
+        w[e] = static_cast<__bf16>(__uint_as_float(t[0]));
+        w[4 + e] = static_cast<__bf16>(__uint_as_float(t[1]));
       }
+      if (wave_active && row_valid) *reinterpret_cast<bf16x8*>(orow + 16 * db) = w;
+    }
   }
 }
 
