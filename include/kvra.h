@@ -89,6 +89,8 @@ int kvra_append_kv(const void* k_in, const void* v_in, void* q_inout,
  *   scale    multiplies Q K^T before the softmax (1/sqrt(head_dim) by convention); finite, > 0
  *   out      [chunk_len, n_q_heads, head_dim] bf16                        (device, write)
  *
+ * Two kernels, chosen by expected time: workgroups of 256 query rows that walk the keys together (the plan of
+ * kvra_chunk_attn_plan), and, for launches of few rows, workgroups of 32 query rows whose waves share out the keys.
  * bf16 MFMA products with fp32 accumulation, fp32 online softmax, P rounded to bf16 before P V.
  * scale (times log2 e) is multiplied into Q before the score product and that Q rounded to bf16.
  * Errors: KVRA_EINVAL, KVRA_EUNSUPPORTED, KVRA_ELAUNCH.
@@ -145,8 +147,8 @@ int64_t kvra_chunk_attn_noalloc_scratch_bytes(void);
  * every such unit has exactly two pieces); the gangs take the first gangs * gang_heads heads of the group, and
  * free slots that fit no gang share the tails of the other heads as above, or stay idle if there is none.  Taken
  * while it ends at most a tenth later, in tile steps, than the evenly shared plan.
- *   kvra_chunk_attn takes this plan with the CU count of the current device; while it has no scratch (see
- * the conventions at the top) it takes the plan in which no unit is cut.
+ *   kvra_chunk_attn takes this plan with the CU count of the current device, unless it expects its kernel for few
+ * rows to be faster; while it has no scratch (see the conventions at the top) it takes the plan in which no unit is cut.
  * Errors: KVRA_EINVAL (plan NULL, n_cus < 1, sizes as for kvra_chunk_attn), KVRA_EUNSUPPORTED.
  */
 typedef struct kvra_attn_plan {

@@ -54,7 +54,7 @@
 // order (the usual log-sum-exp merge) and writes the rows.  No workgroup waits for another one.  Where a
 // group's free slots can form gangs of one slot per row tile, the tails of a head are run side by side by a
 // gang instead (gang mode, see plan_chunk_attn), so that they share the K/V stream as the heads do.
-#include "kvra_internal.h"
+#include "kvra_attn_device.h"
 
 #include <algorithm>
 #include <mutex>
@@ -62,16 +62,6 @@
 #include <vector>
 
 namespace kvra {
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef short s16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-typedef __attribute__((address_space(3))) bf16x8 lds_bf16x8;
-typedef __attribute__((address_space(3))) void lds_void;
 
 constexpr int kWaves = 8;              // waves per workgroup
 constexpr int kThreads = 64 * kWaves;
@@ -82,7 +72,6 @@ constexpr int kStages = 3;             // LDS ring depth for K and for V tiles
 // barriers per tile step: one at head_dim 128 (measured +4..5 %), two at head_dim 64 (one: -4 %)
 constexpr bool one_barrier(int D) { return D == 128; }
 constexpr float kSumLimit = 1048576.0f; // a lane's partial row sum over one tile beyond which the reference is moved
-constexpr float kNoKeyYet = -1e30f;    // exponent reference of a row before its first visible key
 
 struct AttnArgs {
   const __bf16* q;
@@ -256,39 +245,6 @@ __host__ __device__ __forceinline__ void for_each_piece_of_segment(const AttnArg
 }
 
 constexpr int kPartialFloats(int D) { return kWaves * (D / 32 * 16 + 2) * 64; }   // per scratch slot
-
-// A store that is visible to the whole device once it has been acknowledged, and a load that sees such
-// stores (they go past whatever a non-coherent cache level holds).
-__device__ __forceinline__ void store_coherent(float* p, float v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ float load_coherent(const float* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// The value held by lane ^ 32, and by lane ^ 16.
-__device__ __forceinline__ float other_half(float x) {
-  auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return __uint_as_float((threadIdx.x & 32) ? r[0] : r[1]);
-}
-__device__ __forceinline__ float other_row(float x) {
-  auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return __uint_as_float((threadIdx.x & 16) ? r[0] : r[1]);
-}
-
-// 64 lanes x 16 bytes from global memory straight into 1 KiB of consecutive LDS starting at
-// lds_byte_addr (lane l lands at +16 l).  Global address = base of the buffer resource + per-lane byte offset; a lane whose
-// offset lies beyond the resource's size gets zeros, so a tile that straddles the end of what may be read, or lies
-// beyond it, needs no other care.
-// Written as inline assembly on purpose: the compiler guards every LDS-direct load it knows about
-// with a full vmcnt(0) wait (it cannot tell the ring slots apart), which would serialise the
-// prefetch; here completion is awaited by hand, once per block, with s_waitcnt vmcnt(n).
-__device__ __forceinline__ void lds_dma16(u32x4 resource, unsigned lane_byte_off, unsigned lds_byte_addr) {
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds"
-               :
-               : "v"(lane_byte_off), "s"(resource), "s"(lds_byte_addr)
-               : "memory", "m0");
-}
 
 // One piece of work: the queries of row tile pc.qt of kv head pc.g against key tiles [pc.jt0, pc.jt1).
 // pc.slot < 0: the piece covers all the keys the tile needs, O / l goes to a.out.  Otherwise the
@@ -1293,6 +1249,46 @@ int cached_plan(int64_t prefix_len, int64_t chunk_len, int n_q_heads, int n_kv_h
   return KVRA_OK;
 }
 
+// Which kernel a launch gets: 0 = the tiled one with `plan`, else attn_rows_kernel with that many workgroups per slice.
+// The one with the lower expected time, in microseconds, from least-squares fits to 330 launches timed on MI355X (1 to 2500
+// tokens behind 0 to 24000, ten head shapes of 2 to 71 heads, both head sizes):
+//   tiled   one per tile step of the busiest slot + 10 where units are cut + 16 per CU's worth of partial results
+//   rows    fixed + per wave tile of K/V that a CU's eight waves go through + per further round of workgroups + for the merge
+//           through the scratch and its reads
+// The rows kernel gives way to the tiled one from about 4 (head_dim 128) to 9 (64) key tiles per wave on, where reading K/V
+// once for 32 rows costs more than a chain of tile steps does.  Choosing by the fit costs 0.3 % against choosing by hindsight;
+// taking the rows kernel 1.1 times its expected time keeps the worst of the 330 within 2 % of the tiled kernel.  Before -> after:
+// 1 token behind 16384, 32 heads x 128: 64 -> 46 us; 77 behind 5824: 37 -> 30; 300 behind 1699, 8 heads on 2: 31 -> 15;
+// 160 tokens, 2 heads x 64: 11 -> 4.7; 1 token behind 5000, 71 heads on 1: 26 -> 9.
+int rows_splits(const AttnPlan& plan, int64_t prefix_len, int64_t chunk_len, int n_q_heads, int n_kv_heads, int head_dim,
+                int cus, int64_t scratch_bytes) {
+  const int64_t slices = (chunk_len * (n_q_heads / n_kv_heads) + 31) / 32, units = slices * n_kv_heads;
+  if (cus < 1 || units > 64 * static_cast<int64_t>(cus)) return 0;
+  const int64_t tiles = (prefix_len + chunk_len + 63) / 64;   // of the last slice
+  // as many workgroups per slice as leave one per CU, none without a key tile for each of its waves; the scratch is used only
+  // where the tiled launch would use it too (calls that need none may overlap on different streams)
+  int64_t splits = 1;
+  if (units <= kCounterInts && plan.partial_pieces > 0)
+    splits = std::min(std::min<int64_t>(cus / units, (tiles + 7) / 8),
+                      std::min<int64_t>(32, scratch_bytes / (units * attn_rows_slot_bytes(head_dim))));
+  splits = std::max<int64_t>(splits, 1);
+  const float rounds = static_cast<float>((units * splits + cus - 1) / cus);
+  const float mean_tiles = 0.5f * (static_cast<float>(prefix_len) / 64.0f + 1.0f + static_cast<float>(tiles));
+  const float load = static_cast<float>(units) * mean_tiles / (8.0f * static_cast<float>(cus));
+  float rows = 0.0f;
+  if (head_dim == 128) {
+    rows = 5.7f + 3.6f * (rounds - 1.0f) + 4.5f * load;
+    if (splits > 1) rows += 3.9f + 0.3f * static_cast<float>(splits);
+  } else {
+    const float depth = rounds > 1.0f ? std::max(1.0f, mean_tiles / 8.0f) : static_cast<float>((tiles + 8 * splits - 1) / (8 * splits));
+    rows = 4.1f + 0.56f * rounds * depth + 2.6f * (rounds - 1.0f) + 1.8f * load;
+    if (splits > 1) rows += 2.2f + 0.15f * static_cast<float>(splits);
+  }
+  float tiled = static_cast<float>(plan.steps_per_slot);
+  if (plan.partial_pieces > 0) tiled += 10.0f + 16.0f * static_cast<float>(plan.partial_pieces) / static_cast<float>(cus);
+  return 1.1f * rows < tiled ? static_cast<int>(splits) : 0;
+}
+
 }  // namespace
 
 int launch_chunk_attn(const void* q, const void* k_cache, const void* v_cache,
@@ -1312,10 +1308,20 @@ int launch_chunk_attn(const void* q, const void* k_cache, const void* v_cache,
   int64_t slots_owned = kStaticSlots;
   float* scratch_ptr = static_scratch_only ? static_scratch(&cus) : device_scratch(stream, &cus, &slots_owned);
   if (static_scratch_only && scratch_ptr == nullptr) return KVRA_ENODEVICE;
+  int* const counters = scratch_ptr != nullptr
+      ? reinterpret_cast<int*>(scratch_ptr + static_cast<size_t>(slots_owned) * kPartialFloats(128)) : nullptr;
   AttnPlan plan;
   const int rc0 = cached_plan(prefix_len, chunk_len, n_q_heads, n_kv_heads, head_dim, cus, scratch_ptr != nullptr, &plan);
   if (rc0 != KVRA_OK) return rc0;
   if (plan.scratch_slots > slots_owned) return KVRA_ESCRATCH;   // only the fixed array can be too small
+  int splits = rows_splits(plan, prefix_len, chunk_len, n_q_heads, n_kv_heads, head_dim, cus,
+                           scratch_ptr != nullptr ? slots_owned * attn_partial_bytes(128) : 0);
+#ifdef KVRA_TRACE
+  if (g_trace_buf != nullptr) splits = 0;   // only the tiled kernel leaves stamps
+#endif
+  if (splits > 0)
+    return launch_attn_rows(q, k_cache, v_cache, prefix_len, chunk_len, n_q_heads, n_kv_heads, head_dim, scale, out, splits,
+                            scratch_ptr, counters, stream);
   AttnArgs a;
   schedule_args(plan, prefix_len, chunk_len, n_q_heads, n_kv_heads, &a);
   a.q = static_cast<const __bf16*>(q);
@@ -1324,8 +1330,7 @@ int launch_chunk_attn(const void* q, const void* k_cache, const void* v_cache,
   a.out = static_cast<__bf16*>(out);
   a.c_log2 = scale * 1.4426950408889634f;
   a.scratch = plan.partial_pieces > 0 ? scratch_ptr : nullptr;
-  a.counters = scratch_ptr != nullptr
-      ? reinterpret_cast<int*>(scratch_ptr + static_cast<size_t>(slots_owned) * kPartialFloats(128)) : nullptr;
+  a.counters = counters;
   const int workgroups = plan.groups * plan.slots;
 #ifdef KVRA_TRACE
   a.trace = workgroups <= g_trace_groups ? g_trace_buf : nullptr;

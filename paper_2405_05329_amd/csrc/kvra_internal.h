@@ -18,6 +18,12 @@ int launch_append_kv(const void* k_in, const void* v_in, void* q_inout, void* k_
 int launch_chunk_attn(const void* q, const void* k_cache, const void* v_cache,
                       int64_t prefix_len, int64_t chunk_len, int n_q_heads, int n_kv_heads, int head_dim,
                       float scale, void* out, hipStream_t stream, bool static_scratch_only);
+// The kernel for few rows (kvra_attn_rows.hip), `splits` workgroups per slice of 32 virtual rows.  splits > 1 needs scratch:
+// attn_rows_slot_bytes(head_dim) and, zero between launches, one counter per slice (times splits for the slots).
+int launch_attn_rows(const void* q, const void* k_cache, const void* v_cache, int64_t prefix_len, int64_t chunk_len,
+                     int n_q_heads, int n_kv_heads, int head_dim, float scale, void* out, int splits, float* scratch,
+                     int* counters, hipStream_t stream);
+int64_t attn_rows_slot_bytes(int head_dim);
 int64_t attn_static_scratch_bytes();   // size of the fixed scratch array kvra_chunk_attn_noalloc uses
 
 // Launch shape of kvra_chunk_attn for a device with `cus` compute units (pure host arithmetic).
