@@ -34,104 +34,142 @@ __device__ __forceinline__ unsigned short f32_to_bf16_rne(float x) {
   return static_cast<unsigned short>(u >> 16);
 }
 
-// One workgroup serves TOK consecutive tokens (TOK * D/2 <= 256).  Phase 1: TOK * D/2 threads form
-// cos/sin of (prefix + row) * inv_freq[i] in fp64 and park them in LDS as fp32.  Phase 2: all
-// threads stream "pair units" (a 16-byte piece of the low half of a head row and its partner in
-// the high half) for K and Q, and plain 16-byte pieces for V.  Long chunks use the largest TOK
-// (every thread busy in phase 1); short chunks use fewer tokens per workgroup so that the launch
-// still puts several workgroups on every CU.
+// cos and sin of phi, |phi| < 2^26, to about one unit in the last place of a double: phi - n pi/2 with pi/2 as a sum of two
+// doubles (n has at most 26 bits, each fused multiply-add rounds once), then the Taylor series on [-pi/4, pi/4], whose
+// first terms left out are below 2^-54.
+__device__ __forceinline__ void sincos_reduced(double phi, double* s, double* c) {
+  const double n = rint(phi * 0.63661977236758134308);
+  double r = fma(-n, 1.57079632679489655800e+00, phi);
+  r = fma(-n, 6.12323399573676603587e-17, r);
+  const double z = r * r;
+  double ps = 1.0 / 355687428096000.0, pc = -1.0 / 6402373705728000.0;   // 1/17!, -1/18!
+  ps = fma(ps, z, -1.0 / 1307674368000.0);
+  pc = fma(pc, z, 1.0 / 20922789888000.0);
+  ps = fma(ps, z, 1.0 / 6227020800.0);
+  pc = fma(pc, z, -1.0 / 87178291200.0);
+  ps = fma(ps, z, -1.0 / 39916800.0);
+  pc = fma(pc, z, 1.0 / 479001600.0);
+  ps = fma(ps, z, 1.0 / 362880.0);
+  pc = fma(pc, z, -1.0 / 3628800.0);
+  ps = fma(ps, z, -1.0 / 5040.0);
+  pc = fma(pc, z, 1.0 / 40320.0);
+  ps = fma(ps, z, 1.0 / 120.0);
+  pc = fma(pc, z, -1.0 / 720.0);
+  ps = fma(ps, z, -1.0 / 6.0);
+  pc = fma(pc, z, 1.0 / 24.0);
+  pc = fma(pc, z, -0.5);
+  ps = fma(ps * z, r, r);
+  pc = fma(pc, z, 1.0);
+  const int quadrant = static_cast<int>(n) & 3;
+  const double s0 = quadrant & 1 ? pc : ps, c0 = quadrant & 1 ? ps : pc;
+  *s = quadrant & 2 ? -s0 : s0;
+  *c = quadrant == 1 || quadrant == 2 ? -c0 : c0;
+}
+
+// One workgroup serves TOK consecutive tokens (TOK * D/2 <= 256): TOK * D/2 threads form cos/sin of
+// (prefix + row) * inv_freq[i] in fp64 and park them in LDS as fp32; all threads move "pair units" (a 16-byte piece of the
+// low half of a head row and its partner in the high half) of K and Q, and plain 16-byte pieces of V.
+// A short chunk is a chain of latencies, not of traffic, so everything a thread needs first - its frequency (from the
+// kernel arguments), its first pieces of V and its first units of K and Q - is on its way before the angles are worked out.
+// Long chunks use the largest TOK (every thread has an angle); short ones use fewer tokens per workgroup so that the launch
+// still puts several workgroups on every CU.  Before (V, then the library's sincos, then K, then Q) -> after, back to back
+// launches: 160 tokens, 2 heads x 64: 4.3 -> 3.1 us; 1003 tokens, 71 heads on 1: 7.6 -> 5.6; 1024 tokens, 32 heads x 128: 9.7
+// -> 8.9; 5824 tokens: 43.7 -> 42.4 (6.8 TB/s, much of it from the last-level cache).
 template <int D, int TOK>
 __global__ __launch_bounds__(256) void append_kv_kernel(AppendArgs a) {
   constexpr int HALF = D / 2;
-  static_assert(TOK * HALF <= 256, "one thread per (token, frequency) in phase 1");
+  static_assert(TOK * HALF <= 256, "one thread per (token, frequency)");
   constexpr int PAIRS = D / 16;            // pair units per head row
   constexpr int CHUNKS = D / 8;            // 16-byte pieces per head row
+  constexpr int AHEAD = 2;                 // pieces and units of a thread on their way together
   __shared__ float cs[TOK][HALF];
   __shared__ float sn[TOK][HALF];
 
   const int tid = threadIdx.x;
   const int tok0 = blockIdx.x * TOK;
   const int ntok = min(TOK, a.chunk_len - tok0);
-
   const int Hkv = a.n_kv_heads, H = a.n_q_heads;
 
-  // ---- V: bit-exact copy, issued first: it needs no angles, and its traffic overlaps the
-  // fp64 sincos below -------------------------------------------------------------------
-  {
-    const int per_tok = Hkv * CHUNKS;
-    const int total = ntok * per_tok;
-    const u16x8* src = reinterpret_cast<const u16x8*>(a.v_in) + static_cast<long long>(tok0) * per_tok;
-    u16x8* dst = reinterpret_cast<u16x8*>(a.v_cache) + (a.prefix_len + tok0) * per_tok;
-#pragma unroll 4
-    for (int u = tid; u < total; u += 256) dst[u] = src[u];
-  }
+  const int t_mine = tid / HALF;
+  const bool has_angle = a.use_rope && t_mine < ntok;
+  double freq = 0.0;
+  if (has_angle) freq = a.inv_freq[tid % HALF];
+
+  // V: bit-exact copy
+  const int v_total = ntok * Hkv * CHUNKS;
+  const u16x8* v_src = reinterpret_cast<const u16x8*>(a.v_in) + static_cast<long long>(tok0) * Hkv * CHUNKS;
+  u16x8* v_dst = reinterpret_cast<u16x8*>(a.v_cache) + (a.prefix_len + tok0) * Hkv * CHUNKS;
+  u16x8 v[AHEAD];
+#pragma unroll
+  for (int i = 0; i < AHEAD; ++i)
+    if (tid + 256 * i < v_total) v[i] = v_src[tid + 256 * i];
+
+  // units of a token: those of its K heads, which go to the cache, then (rotation only) those of its Q heads, in place
+  const int heads = Hkv + (a.q != nullptr && a.use_rope ? H : 0);
+  const int per_tok = heads * PAIRS, total = ntok * per_tok;
+  u16x8 lo[AHEAD], hi[AHEAD];
+  unsigned short* dst[AHEAD];
+  int where[AHEAD];                        // offset of the unit's cos/sin, in floats
+  auto load_units = [&](int u0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < AHEAD; ++i) {
+      const int u = u0 + 256 * i;
+      if (u >= total) break;
+      const int t = TOK == 1 ? 0 : u / per_tok;
+      const int rem = u - t * per_tok;
+      const int head = rem / PAIRS, j = rem % PAIRS;
+      const unsigned short* src;
+      if (head < Hkv) {
+        src = a.k_in + (static_cast<long long>(tok0 + t) * Hkv + head) * D + 8 * j;
+        dst[i] = a.k_cache + ((a.prefix_len + tok0 + t) * Hkv + head) * D + 8 * j;
+      } else {
+        dst[i] = a.q + (static_cast<long long>(tok0 + t) * H + (head - Hkv)) * D + 8 * j;
+        src = dst[i];
+      }
+      where[i] = t * HALF + 8 * j;
+      lo[i] = *reinterpret_cast<const u16x8*>(src);
+      hi[i] = *reinterpret_cast<const u16x8*>(src + HALF);
+    }
+  };
+  load_units(tid);
 
   if (a.use_rope) {
-    const int t = tid / HALF, i = tid % HALF;
-    if (t < ntok) {
-      const double phi = static_cast<double>(a.prefix_len + tok0 + t) * a.inv_freq[i];
+    if (has_angle) {
+      const double phi = static_cast<double>(a.prefix_len + tok0 + t_mine) * freq;
       double s, c;
-      sincos(phi, &s, &c);
-      cs[t][i] = static_cast<float>(c);
-      sn[t][i] = static_cast<float>(s);
+      if (phi < 67108864.0) sincos_reduced(phi, &s, &c);
+      else sincos(phi, &s, &c);            // a rope base below 1
+      cs[t_mine][tid % HALF] = static_cast<float>(c);
+      sn[t_mine][tid % HALF] = static_cast<float>(s);
     }
     __syncthreads();
   }
 
-  // ---- K: rotate (or copy) into the cache --------------------------------------------
-  {
-    const int per_tok = Hkv * PAIRS;
-    const int total = ntok * per_tok;
-#pragma unroll 2
-    for (int u = tid; u < total; u += 256) {
-      const int t = u / per_tok;
-      const int rem = u - t * per_tok;
-      const int head = rem / PAIRS;
-      const int j = rem - head * PAIRS;
-      const long long src_row = (static_cast<long long>(tok0 + t) * Hkv + head) * D;
-      const long long dst_row = ((a.prefix_len + tok0 + t) * Hkv + head) * D;
-      const u16x8 lo = *reinterpret_cast<const u16x8*>(a.k_in + src_row + 8 * j);
-      const u16x8 hi = *reinterpret_cast<const u16x8*>(a.k_in + src_row + HALF + 8 * j);
-      u16x8 olo = lo, ohi = hi;
+#pragma unroll
+  for (int i = 0; i < AHEAD; ++i)
+    if (tid + 256 * i < v_total) v_dst[tid + 256 * i] = v[i];
+  for (int u0 = tid; u0 < total; u0 += 256 * AHEAD) {
+    if (u0 != tid) load_units(u0);
+#pragma unroll
+    for (int i = 0; i < AHEAD; ++i) {
+      if (u0 + 256 * i >= total) break;
+      u16x8 olo = lo[i], ohi = hi[i];
       if (a.use_rope) {
+        const float* c = &cs[0][0] + where[i];
+        const float* s = &sn[0][0] + where[i];
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-          const float c = cs[t][8 * j + e], s = sn[t][8 * j + e];
-          const float x0 = bf16_to_f32(lo[e]), x1 = bf16_to_f32(hi[e]);
-          olo[e] = f32_to_bf16_rne(fmaf(x0, c, -(x1 * s)));
-          ohi[e] = f32_to_bf16_rne(fmaf(x1, c, x0 * s));
+          const float x0 = bf16_to_f32(lo[i][e]), x1 = bf16_to_f32(hi[i][e]);
+          olo[e] = f32_to_bf16_rne(fmaf(x0, c[e], -(x1 * s[e])));
+          ohi[e] = f32_to_bf16_rne(fmaf(x1, c[e], x0 * s[e]));
         }
       }
-      *reinterpret_cast<u16x8*>(a.k_cache + dst_row + 8 * j) = olo;
-      *reinterpret_cast<u16x8*>(a.k_cache + dst_row + HALF + 8 * j) = ohi;
+      *reinterpret_cast<u16x8*>(dst[i]) = olo;
+      *reinterpret_cast<u16x8*>(dst[i] + HALF) = ohi;
     }
   }
-
-  // ---- Q: rotate in place -------------------------------------------------------------
-  if (a.q != nullptr && a.use_rope) {
-    const int per_tok = H * PAIRS;
-    const int total = ntok * per_tok;
-#pragma unroll 2
-    for (int u = tid; u < total; u += 256) {
-      const int t = u / per_tok;
-      const int rem = u - t * per_tok;
-      const int head = rem / PAIRS;
-      const int j = rem - head * PAIRS;
-      unsigned short* row = a.q + (static_cast<long long>(tok0 + t) * H + head) * D;
-      const u16x8 lo = *reinterpret_cast<const u16x8*>(row + 8 * j);
-      const u16x8 hi = *reinterpret_cast<const u16x8*>(row + HALF + 8 * j);
-      u16x8 olo, ohi;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const float c = cs[t][8 * j + e], s = sn[t][8 * j + e];
-        const float x0 = bf16_to_f32(lo[e]), x1 = bf16_to_f32(hi[e]);
-        olo[e] = f32_to_bf16_rne(fmaf(x0, c, -(x1 * s)));
-        ohi[e] = f32_to_bf16_rne(fmaf(x1, c, x0 * s));
-      }
-      *reinterpret_cast<u16x8*>(row + 8 * j) = olo;
-      *reinterpret_cast<u16x8*>(row + HALF + 8 * j) = ohi;
-    }
-  }
+#pragma unroll 4
+  for (int u = tid + 256 * AHEAD; u < v_total; u += 256) v_dst[u] = v_src[u];
 }
 
 int launch_append_kv(const void* k_in, const void* v_in, void* q_inout, void* k_cache, void* v_cache,
