@@ -623,7 +623,8 @@ int launch_linear(const void* x, const void* w, const void* w2, const void* resi
 
 // ---- RMSNorm ------------------------------------------------------------------------------------
 // y[t, :] = x[t, :] / sqrt(mean(x[t, :]^2) + eps) * gain, fp32 arithmetic, one workgroup per token.
-// HBM-bound: every element is read once and written once with 16-byte accesses.
+// HBM-bound: every element is read once and written once with 16-byte accesses.  The gain is on its way with the row (with
+// few rows the kernel is a chain of latencies: 1 x 4096 2.5 -> 2.3 us; 5824 x 4096: 15.7 -> 15.0, 6.4 TB/s).
 struct NormArgs {
   const __bf16* x;
   const __bf16* gain;
@@ -641,13 +642,20 @@ __global__ __launch_bounds__(kNormThreads) void rms_norm_kernel(NormArgs a) {
   const int tid = threadIdx.x;
   const int pieces = a.hidden / 8;
   const bf16x8* xr = reinterpret_cast<const bf16x8*>(a.x + static_cast<long long>(blockIdx.x) * a.hidden);
-  bf16x8 v[kNormMaxPieces];
+  const bf16x8* gr = reinterpret_cast<const bf16x8*>(a.gain);
+  bf16x8 v[kNormMaxPieces], g[kNormMaxPieces];
   float ss = 0.0f;
 #pragma unroll
   for (int i = 0; i < kNormMaxPieces; ++i) {
     const int p = tid + i * kNormThreads;
     if (p < pieces) {
       v[i] = xr[p];
+      g[i] = gr[p];
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < kNormMaxPieces; ++i) {
+    if (tid + i * kNormThreads < pieces) {
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         const float f = static_cast<float>(v[i][e]);
@@ -663,16 +671,14 @@ __global__ __launch_bounds__(kNormThreads) void rms_norm_kernel(NormArgs a) {
 #pragma unroll
   for (int w = 0; w < kNormThreads / 64; ++w) tot += part[w];
   const float rinv = 1.0f / sqrtf(tot / static_cast<float>(a.hidden) + a.eps);
-  const bf16x8* gr = reinterpret_cast<const bf16x8*>(a.gain);
   bf16x8* yr = reinterpret_cast<bf16x8*>(a.y + static_cast<long long>(blockIdx.x) * a.hidden);
 #pragma unroll
   for (int i = 0; i < kNormMaxPieces; ++i) {
     const int p = tid + i * kNormThreads;
     if (p < pieces) {
-      const bf16x8 g = gr[p];
       bf16x8 o;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) o[e] = static_cast<__bf16>(static_cast<float>(v[i][e]) * rinv * static_cast<float>(g[e]));
+      for (int e = 0; e < 8; ++e) o[e] = static_cast<__bf16>(static_cast<float>(v[i][e]) * rinv * static_cast<float>(g[i][e]));
       yr[p] = o;
     }
   }
