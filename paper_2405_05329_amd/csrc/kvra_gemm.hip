@@ -463,20 +463,26 @@ __global__ __launch_bounds__(T::THREADS, T::PER_SIMD) void linear_kernel(GemmArg
   }
 }
 
-// Few tokens: a pass over the weights, bound by how fast they come from memory.  A workgroup owns 16 weight rows and all
-// (up to 16) tokens; its 8 waves share out k in chunks of 64, and both operands go from global memory straight into MFMA
-// fragments, since no wave needs what another one loads: no LDS and no barrier until the sums of the eight shares meet at
-// the end.  The loads of kRowsAhead chunks (of a 4096-deep row: all there are) are in flight together.
+// Few tokens: a pass over the weights, bound by how fast they come from memory.  A workgroup owns 16 weight rows (SwiGLU: 8
+// columns, their gate rows and their up rows) and all (up to 16) tokens; its 8 waves share out k in chunks of 64, and both
+// operands go from global memory straight into MFMA fragments, since no wave needs what another one loads: no LDS and no
+// barrier until the sums of the eight shares meet at the end.  The loads of kRowsAhead chunks (of a 4096-deep row: all there
+// are) are in flight together.  Measured and not taken (1 token): the last chunks of a row in one go instead of one by one
+// (4096 x 11008: no difference); two sets of four chunks, one on its way while the other is multiplied (24.4 us against 22.1);
+// rows as whole 1 KiB loads with fp32 multiply-adds on the vector ALU (29.1, and slower with every further token).
 constexpr int kRowsThreads = 512, kRowsWaves = 8, kRowsAhead = 8;
 
+template <bool DUAL>
 __global__ __launch_bounds__(kRowsThreads, 2) void linear_rows_kernel(GemmArgs a) {
   __shared__ f32x4 part[kRowsWaves][64];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r16 = lane & 15, kg = lane >> 4;
-  const int n0 = blockIdx.x * 16;   // n is a multiple of 32
-  const char* const w = reinterpret_cast<const char*>(a.w) +
-                        2 * (static_cast<long long>(n0 + r16) * a.k + 8 * kg);
+  constexpr int COLS = DUAL ? 8 : 16;
+  const int n0 = blockIdx.x * COLS;   // n is a multiple of 32 (of each weight)
+  const __bf16* const weight = DUAL && r16 >= COLS ? a.w2 : a.w;
+  const char* const w = reinterpret_cast<const char*>(weight) +
+                        2 * (static_cast<long long>(n0 + r16 % COLS) * a.k + 8 * kg);
   const char* const x = reinterpret_cast<const char*>(a.x) +
                         2 * (static_cast<long long>(min(r16, a.m - 1)) * a.k + 8 * kg);
   f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -502,24 +508,36 @@ __global__ __launch_bounds__(kRowsThreads, 2) void linear_rows_kernel(GemmArgs a
   for (; c < chunks; c += kRowsWaves) steps(c, std::integral_constant<int, 1>{});
   part[wave][lane] = acc;
   __syncthreads();
-  if (wave != 0 || r16 >= a.m) return;
-  // 4 columns of a token per lane
+  if (wave != 0) return;
+  // rows 4 kg .. 4 kg + 3 of a token per lane
   f32x4 v = part[0][lane];
 #pragma unroll
   for (int u = 1; u < kRowsWaves; ++u) v += part[u][lane];
-  int s = 0;
-  if (a.n_seg > 1 && n0 >= a.seg[0].end) s = 1;
-  if (a.n_seg > 2 && n0 >= a.seg[1].end) s = 2;
-  const long long at = static_cast<long long>(r16) * a.seg[s].ld + n0 - a.seg[s].first + 4 * kg;
-  if (a.res != nullptr) {
-    const bf16x4 r = *reinterpret_cast<const bf16x4*>(a.res + at);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] += static_cast<float>(r[e]);
-  }
   bf16x4 o;
+  if constexpr (DUAL) {
+    // the up rows of this lane's columns are 32 lanes on
 #pragma unroll
-  for (int e = 0; e < 4; ++e) o[e] = static_cast<__bf16>(v[e]);
-  *reinterpret_cast<bf16x4*>(a.seg[s].ptr + at) = o;
+    for (int e = 0; e < 4; ++e) {
+      const float g = v[e], u = __shfl_xor(v[e], 32);
+      o[e] = static_cast<__bf16>(g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)) * u);
+    }
+    if (kg >= 2 || r16 >= a.m) return;
+    *reinterpret_cast<bf16x4*>(a.seg[0].ptr + static_cast<long long>(r16) * a.seg[0].ld + n0 + 4 * kg) = o;
+  } else {
+    if (r16 >= a.m) return;
+    int s = 0;
+    if (a.n_seg > 1 && n0 >= a.seg[0].end) s = 1;
+    if (a.n_seg > 2 && n0 >= a.seg[1].end) s = 2;
+    const long long at = static_cast<long long>(r16) * a.seg[s].ld + n0 - a.seg[s].first + 4 * kg;
+    if (a.res != nullptr) {
+      const bf16x4 r = *reinterpret_cast<const bf16x4*>(a.res + at);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] += static_cast<float>(r[e]);
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o[e] = static_cast<__bf16>(v[e]);
+    *reinterpret_cast<bf16x4*>(a.seg[s].ptr + at) = o;
+  }
 }
 
 namespace {
@@ -535,7 +553,8 @@ int launch_tile(GemmArgs& a, hipStream_t stream) {
 }
 
 int launch_rows(GemmArgs& a, hipStream_t stream) {
-  return launch_kernel(linear_rows_kernel, dim3(static_cast<unsigned>(a.n / 16)), dim3(kRowsThreads), a, stream);
+  const dim3 grid(static_cast<unsigned>(a.n / 16)), block(kRowsThreads);   // dual: a.n counts the rows of both weights
+  return launch_kernel(a.dual ? linear_rows_kernel<true> : linear_rows_kernel<false>, grid, block, a, stream);
 }
 
 // ---- which kernel a shape gets ----------------------------------------------------------------------
@@ -604,10 +623,13 @@ int launch_linear(const void* x, const void* w, const void* w2, const void* resi
   a.m = static_cast<int>(m);
   a.n = static_cast<int>(a.dual ? 2 * n_out : n_out);
   a.k = static_cast<int>(k);
-  // Up to 8 tokens (16 where there are fewer than 8192 weight rows) the direct kernel is the fastest, except for SwiGLU
-  // where 32 x 32 tiles keep up: at 1 token 8.4 / 19.1 / 22.1 us for n x k = 4096 x 4096 / 12288 x 4096 / 4096 x 11008
-  // (weights at 4.0 / 5.3 / 4.1 TB/s) against 10.4 / 23.3 / 25.6; at 16 tokens 10.2 / 24.8 / 26.8 against 11.4 / 23.6 / 28.5.
-  if (!a.dual && a.m <= (a.n < 8192 ? 16 : 8)) return launch_rows(a, stream);
+  // Up to 8 tokens (16 where there are fewer than 8192 weight rows) the direct kernel is the fastest: at 1 token 8.4 / 19.1 /
+  // 22.1 us for n x k = 4096 x 4096 / 12288 x 4096 / 4096 x 11008 (weights at 4.0 / 5.3 / 4.1 TB/s) against 10.4 / 23.3 / 25.6;
+  // at 16 tokens 10.2 / 24.8 / 26.8 against 11.4 / 23.6 / 28.5.
+  // SwiGLU reads more rows per column and gives way to the tiles at 4 tokens where there are 16384 rows or more: n x k =
+  // 11008 x 4096 at 1 / 4 / 8 tokens 34.7 / 38.3 / 43.3 us (5.2 TB/s at 1) against 41.2 / 41.2 / 41.5; 5632 x 2048 at 1 / 8 / 12
+  // 10.4 / 12.5 / 13.7 against 12.7 / 13.1 / 13.1; 2816 x 1024 at 1 / 16 4.9 / 6.0 against 6.2 / 6.2.
+  if (a.m <= (a.n < 8192 ? 16 : a.dual && a.n >= 16384 ? 4 : 8)) return launch_rows(a, stream);
   const TileChoice* best = nullptr;
   float best_cost = 0.0f;
   for (const TileChoice& c : kTiles) {

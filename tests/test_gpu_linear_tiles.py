@@ -33,6 +33,8 @@ pytestmark = pytest.mark.gpu
     (6001, 4128, 128, "plain"),                                      # several large tiles per workgroup
     (1, 32, 64, "plain"), (16, 544, 320, "residual"), (8, 8224, 128, "plain"), (9, 8224, 128, "residual"),
     (5, 1056, 5632, "residual"), (17, 544, 320, "plain"), (1, 64, 128, "swiglu"),   # few tokens
+    (17, 96, 128, "swiglu"), (16, 2080, 320, "swiglu"), (16, 4064, 64, "swiglu"), (8, 4128, 576, "swiglu"),   # SwiGLU: direct
+    (9, 4128, 64, "swiglu"), (4, 8224, 576, "swiglu"), (5, 8224, 64, "swiglu"), (3, 32, 4608, "swiglu"),      # or tiled
 ])
 def test_linear_tiles(m, n, k, mode):
     x = synth.normal_bf16(5, 23, 0, (m, k))
