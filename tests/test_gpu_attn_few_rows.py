@@ -22,6 +22,7 @@ pytestmark = pytest.mark.gpu
     (8, 2, 128, 1699, 300), (8, 2, 128, 777, 524), (4, 2, 64, 2500, 179),     # two and three workgroups per slice
     (32, 32, 128, 5824, 77), (32, 32, 128, 8000, 1), (16, 16, 64, 4097, 3),   # eight heads or more: pairs by XCD
     (7, 1, 64, 23000, 2), (8, 1, 128, 19999, 4),                              # the most workgroups per slice
+    (16, 16, 128, 12000, 130), (8, 8, 64, 20000, 420), (8, 8, 128, 20000, 290),   # beyond: tiles with waves that have no rows
 ])
 def test_few_rows(H, Hkv, d, prefix, c):
     C, extra = prefix + c, 40
