@@ -44,8 +44,12 @@ __device__ __forceinline__ float other_row(float x) {
 // Written as inline assembly on purpose: the compiler guards every LDS-direct load it knows about
 // with a full vmcnt(0) wait (it cannot tell the ring slots apart), which would serialise the
 // prefetch; here completion is awaited by hand, once per block, with s_waitcnt vmcnt(n).
+// Wait states: a memory instruction may read a scalar register that a vector instruction wrote (the resource comes from
+// v_readfirstlane, or from the lanes it was spilled to) five states later at the earliest, and the compiler, which does not
+// know that a memory instruction stands in here, keeps no such distance.  s_mov (one) and s_nop 3 (four) make it up whatever
+// is scheduled in front of the block.
 __device__ __forceinline__ void lds_dma16(u32x4 resource, unsigned lane_byte_off, unsigned lds_byte_addr) {
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds"
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 3\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds"
                :
                : "v"(lane_byte_off), "s"(resource), "s"(lds_byte_addr)
                : "memory", "m0");
