@@ -517,19 +517,27 @@ __device__ __forceinline__ void attend(const AttnArgs& a, u32x4* smem, int* last
           // opaque to the optimiser: otherwise the compares below become loop-carried
           // counters that are kept up to date (and kept in registers) on every tile
           asm volatile("" : "+v"(rel));
-          // compare and select one element at a time through vcc (written out: left to itself the
-          // compiler keeps all the lane masks alive in scalar registers, which spills others)
+          // compare and select, four elements at a time through three mask registers (written out: left to itself the
+          // compiler keeps all the lane masks alive in scalar registers, which spills others).  Between a comparison and the
+          // select that reads its mask the hardware needs two other instructions, which the order below provides.
 #pragma unroll
-          for (int kb = 0; kb < KB; ++kb)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              float x = s[kb][qb][e];
-              asm volatile("v_cmp_gt_i32 vcc, %1, %2\n\tv_cndmask_b32 %0, %0, %3, vcc"
-                           : "+v"(x)
-                           : "n"(16 * kb + e), "v"(rel), "v"(ninf)
-                           : "vcc");
-              s[kb][qb][e] = x;
-            }
+          for (int kb = 0; kb < KB; ++kb) {
+            unsigned long long m1, m2;
+            float x0 = s[kb][qb][0], x1 = s[kb][qb][1], x2 = s[kb][qb][2], x3 = s[kb][qb][3];
+            asm volatile("v_cmp_gt_i32 vcc, 0, %6\n\t"
+                         "v_cmp_gt_i32 %4, 1, %6\n\t"
+                         "v_cmp_gt_i32 %5, 2, %6\n\t"
+                         "v_cndmask_b32 %0, %0, %7, vcc\n\t"
+                         "v_cmp_gt_i32 vcc, 3, %6\n\t"
+                         "v_cndmask_b32 %1, %1, %7, %4\n\t"
+                         "v_cndmask_b32 %2, %2, %7, %5\n\t"
+                         "v_cndmask_b32 %3, %3, %7, vcc\n\t"
+                         "v_subrev_u32 %6, 16, %6"
+                         : "+v"(x0), "+v"(x1), "+v"(x2), "+v"(x3), "=&s"(m1), "=&s"(m2), "+v"(rel)
+                         : "v"(ninf)
+                         : "vcc");
+            s[kb][qb] = f32x4{x0, x1, x2, x3};
+          }
         }
       }
       // ---- online softmax (base 2) with a lazily moved exponent reference -------------------

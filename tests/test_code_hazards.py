@@ -116,6 +116,8 @@ def violations(code, reads, writes, needed):
 RULES = {
     # a vector instruction writes a scalar register (v_readfirstlane, a spilled one coming back), a memory instruction reads it
     "vector-written scalar -> memory": (lambda i: scalar(i.uses) if i.vmem else (), lambda i: i.valu, 5),
+    # a vector instruction writes a scalar register (a comparison's mask), another vector instruction reads it
+    "vector-written scalar -> vector": (lambda i: scalar(i.uses) if i.valu else (), lambda i: i.valu, 2),
     # the LDS address of a load straight into LDS
     "m0 -> load to LDS": (lambda i: {"m0"} if i.to_lds else (), lambda i: not i.valu, 1),
 }
