@@ -16,7 +16,9 @@ typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 typedef __attribute__((address_space(3))) bf16x8 lds_bf16x8;
 typedef __attribute__((address_space(3))) void lds_void;
 
-constexpr float kNoKeyYet = -1e30f;    // exponent reference of a row before its first visible key
+// Exponent reference of a row before its first visible key: the lowest finite number, so that no finite score lies below
+// it and a merge that takes the larger of two references always takes that of a row that has met a key.
+constexpr float kNoKeyYet = -3.402823466e38f;
 
 // A store that is visible to the whole device once it has been acknowledged, and a load that sees such
 // stores (they go past whatever a non-coherent cache level holds).
