@@ -172,6 +172,15 @@ int kvra_chunk_attn_plan(int64_t prefix_len, int64_t chunk_len, int n_q_heads, i
                          int head_dim, int n_cus, kvra_attn_plan* plan);
 
 /*
+ * Which of its two kernels kvra_chunk_attn takes for a shape on a device with n_cus compute units while it has its scratch
+ * (host arithmetic only): *splits_out = 0 for the tiled kernel, which runs the plan above; otherwise the kernel for few rows,
+ * which does not, with that many workgroups for every slice of 32 virtual rows of a kv head.
+ * Errors: as kvra_chunk_attn_plan.
+ */
+int kvra_chunk_attn_row_splits(int64_t prefix_len, int64_t chunk_len, int n_q_heads, int n_kv_heads,
+                               int head_dim, int n_cus, int* splits_out);
+
+/*
  * The pieces of that plan, one record of 10 ints each, workgroup by workgroup in the order each
  * workgroup runs them (host arithmetic only; the kernel walks the same list with the same code):
  *   [0] workgroup id  [1] kv head  [2] row tile  [3] first key tile  [4] end key tile (exclusive)
@@ -329,6 +338,13 @@ int kvra_rms_norm(const void* x, const void* gain, void* y, int64_t rows, int hi
  */
 int kvra_linear(const void* x, const void* w, const void* w2, const void* residual, void* out,
                 int64_t m, int64_t n, int64_t k, void* stream);
+
+/*
+ * The tile kvra_linear (swiglu != 0: with w2) takes for a shape (host arithmetic only), as 4 ints: [0] weight rows (swiglu:
+ * of both weights together) and [1] tokens of a workgroup's tile, [2] depth of its k stages (0: the kernel for few tokens, which
+ * has none), [3] the largest number of tiles a workgroup walks.
+ */
+int kvra_linear_tile(int64_t m, int64_t n, int64_t k, int swiglu, int* tile_out);
 
 /*
  * The three projections of the App. C listing in one launch.  wqkv: [(n_q_heads + 2 n_kv_heads) *

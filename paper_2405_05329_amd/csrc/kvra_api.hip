@@ -112,6 +112,16 @@ extern "C" int kvra_chunk_attn_plan(int64_t prefix_len, int64_t chunk_len, int n
   return KVRA_OK;
 }
 
+extern "C" int kvra_chunk_attn_row_splits(int64_t prefix_len, int64_t chunk_len, int n_q_heads, int n_kv_heads,
+                                          int head_dim, int n_cus, int* splits_out) {
+  if (splits_out == nullptr || n_cus < 1) return KVRA_EINVAL;
+  if (chunk_len < 1 || prefix_len < 0) return KVRA_EINVAL;
+  int rc = check_heads(n_q_heads, n_kv_heads, head_dim);
+  if (rc != KVRA_OK) return rc;
+  if (chunk_len > kMaxTokens || prefix_len > kMaxTokens) return KVRA_EUNSUPPORTED;
+  return kvra::attn_row_splits(prefix_len, chunk_len, n_q_heads, n_kv_heads, head_dim, n_cus, splits_out);
+}
+
 extern "C" int kvra_chunk_attn_pieces(int64_t prefix_len, int64_t chunk_len, int n_q_heads, int n_kv_heads,
                                       int head_dim, int n_cus, int32_t* records, int64_t capacity,
                                       int64_t* count_out) {
@@ -158,6 +168,20 @@ extern "C" int kvra_linear(const void* x, const void* w, const void* w2, const v
   void* outs[1] = {out};
   const int cols[1] = {static_cast<int>(n)};
   return kvra::launch_linear(x, w, w2, residual, outs, cols, 1, m, n, k, static_cast<hipStream_t>(stream));
+}
+
+extern "C" int kvra_linear_tile(int64_t m, int64_t n, int64_t k, int swiglu, int* tile_out) {
+  if (tile_out == nullptr) return KVRA_EINVAL;
+  int rc = check_linear(m, n, k);
+  if (rc != KVRA_OK) return rc;
+  kvra::LinearPlan p;
+  rc = kvra::linear_plan(m, n, k, swiglu != 0, &p);
+  if (rc != KVRA_OK) return rc;
+  tile_out[0] = p.tile_rows;
+  tile_out[1] = p.tile_tokens;
+  tile_out[2] = p.tile_k;
+  tile_out[3] = p.rounds;
+  return KVRA_OK;
 }
 
 extern "C" int kvra_qkv_proj(const void* x, const void* wqkv, void* q_out, void* k_out, void* v_out,

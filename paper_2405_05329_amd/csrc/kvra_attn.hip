@@ -1305,6 +1305,15 @@ int rows_splits(const AttnPlan& plan, int64_t prefix_len, int64_t chunk_len, int
 
 }  // namespace
 
+int attn_row_splits(int64_t prefix_len, int64_t chunk_len, int n_q_heads, int n_kv_heads, int head_dim, int cus, int* splits) {
+  AttnPlan plan;
+  const int rc = plan_chunk_attn(prefix_len, chunk_len, n_q_heads, n_kv_heads, head_dim, cus, true, &plan);
+  if (rc != KVRA_OK) return rc;
+  *splits = rows_splits(plan, prefix_len, chunk_len, n_q_heads, n_kv_heads, head_dim, cus,
+                        static_cast<int64_t>(kSlotsPerCu) * cus * attn_partial_bytes(128));
+  return KVRA_OK;
+}
+
 int launch_chunk_attn(const void* q, const void* k_cache, const void* v_cache,
                       int64_t prefix_len, int64_t chunk_len, int n_q_heads, int n_kv_heads, int head_dim,
                       float scale, void* out, hipStream_t stream, bool static_scratch_only) {

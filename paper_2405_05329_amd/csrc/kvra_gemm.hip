@@ -588,12 +588,38 @@ const TileChoice kTiles[] = {
     {32, 32, 128, 1, true, 3.28f, 0.78f, 0.112f, 0.001f, launch_tile<GemmTile<32, 32, 128, 8, 1, 2, 4, 2, true>>},
 };
 
+int64_t tiles_per_xcd(const TileChoice& c, const GemmArgs& a) {   // 64 bits: the query takes sizes that no memory holds
+  return (static_cast<int64_t>((a.n + c.tn - 1) / c.tn) * ((a.m + c.tm - 1) / c.tm) + 7) / 8;
+}
+
 float tile_cost(const TileChoice& c, const GemmArgs& a) {
-  const int per_xcd = ((a.n + c.tn - 1) / c.tn * ((a.m + c.tm - 1) / c.tm) + 7) / 8, slots = 32 * c.per_cu;
-  const int rounds = (per_xcd + slots - 1) / slots;
+  const int slots = 32 * c.per_cu;
+  const int64_t per_xcd = tiles_per_xcd(c, a), rounds = (per_xcd + slots - 1) / slots;
   const float last = static_cast<float>(per_xcd - (rounds - 1) * slots) / slots;
   const float full = rounds - 1 + std::max(0.0f, 2.0f * last - 1.0f);
   return c.fixed + a.k / 64 * (rounds * c.step + full * c.step_full) + rounds * c.per_round;
+}
+
+// Up to 8 tokens (16 where there are fewer than 8192 weight rows) the direct kernel is the fastest: at 1 token 8.4 / 19.1 /
+// 22.1 us for n x k = 4096 x 4096 / 12288 x 4096 / 4096 x 11008 (weights at 4.0 / 5.3 / 4.1 TB/s) against 10.4 / 23.3 / 25.6;
+// at 16 tokens 10.2 / 24.8 / 26.8 against 11.4 / 23.6 / 28.5.
+// SwiGLU reads more rows per column and gives way to the tiles at 4 tokens where there are 16384 rows or more: n x k =
+// 11008 x 4096 at 1 / 4 / 8 tokens 34.7 / 38.3 / 43.3 us (5.2 TB/s at 1) against 41.2 / 41.2 / 41.5; 5632 x 2048 at 1 / 8 / 12
+// 10.4 / 12.5 / 13.7 against 12.7 / 13.1 / 13.1; 2816 x 1024 at 1 / 16 4.9 / 6.0 against 6.2 / 6.2.
+bool takes_rows(const GemmArgs& a) { return a.m <= (a.n < 8192 ? 16 : a.dual && a.n >= 16384 ? 4 : 8); }
+
+const TileChoice* choose_tile(const GemmArgs& a) {
+  const TileChoice* best = nullptr;
+  float best_cost = 0.0f;
+  for (const TileChoice& c : kTiles) {
+    if ((a.dual && !c.dual) || a.k % c.tk != 0) continue;
+    const float cost = tile_cost(c, a);
+    if (best == nullptr || cost < best_cost) {
+      best = &c;
+      best_cost = cost;
+    }
+  }
+  return best;
 }
 
 }  // namespace
@@ -623,24 +649,25 @@ int launch_linear(const void* x, const void* w, const void* w2, const void* resi
   a.m = static_cast<int>(m);
   a.n = static_cast<int>(a.dual ? 2 * n_out : n_out);
   a.k = static_cast<int>(k);
-  // Up to 8 tokens (16 where there are fewer than 8192 weight rows) the direct kernel is the fastest: at 1 token 8.4 / 19.1 /
-  // 22.1 us for n x k = 4096 x 4096 / 12288 x 4096 / 4096 x 11008 (weights at 4.0 / 5.3 / 4.1 TB/s) against 10.4 / 23.3 / 25.6;
-  // at 16 tokens 10.2 / 24.8 / 26.8 against 11.4 / 23.6 / 28.5.
-  // SwiGLU reads more rows per column and gives way to the tiles at 4 tokens where there are 16384 rows or more: n x k =
-  // 11008 x 4096 at 1 / 4 / 8 tokens 34.7 / 38.3 / 43.3 us (5.2 TB/s at 1) against 41.2 / 41.2 / 41.5; 5632 x 2048 at 1 / 8 / 12
-  // 10.4 / 12.5 / 13.7 against 12.7 / 13.1 / 13.1; 2816 x 1024 at 1 / 16 4.9 / 6.0 against 6.2 / 6.2.
-  if (a.m <= (a.n < 8192 ? 16 : a.dual && a.n >= 16384 ? 4 : 8)) return launch_rows(a, stream);
-  const TileChoice* best = nullptr;
-  float best_cost = 0.0f;
-  for (const TileChoice& c : kTiles) {
-    if ((a.dual && !c.dual) || a.k % c.tk != 0) continue;
-    const float cost = tile_cost(c, a);
-    if (best == nullptr || cost < best_cost) {
-      best = &c;
-      best_cost = cost;
-    }
+  if (takes_rows(a)) return launch_rows(a, stream);
+  return choose_tile(a)->launch(a, stream);
+}
+
+int linear_plan(int64_t m, int64_t n_out, int64_t k, bool dual, LinearPlan* plan) {
+  GemmArgs a = {};
+  a.dual = dual ? 1 : 0;
+  a.m = static_cast<int>(m);
+  a.n = static_cast<int>(dual ? 2 * n_out : n_out);
+  a.k = static_cast<int>(k);
+  if (takes_rows(a)) {
+    *plan = LinearPlan{16, 16, 0, 1};
+    return KVRA_OK;
   }
-  return best->launch(a, stream);
+  const TileChoice* c = choose_tile(a);
+  const int64_t per_xcd = tiles_per_xcd(*c, a);
+  const int64_t workgroups = std::min<int64_t>(per_xcd, 32 * c->per_cu);   // of an XCD
+  *plan = LinearPlan{c->tn, c->tm, c->tk, static_cast<int>((per_xcd + workgroups - 1) / workgroups)};
+  return KVRA_OK;
 }
 
 // ---- RMSNorm ------------------------------------------------------------------------------------

@@ -65,6 +65,8 @@ int64_t attn_partial_bytes(int head_dim);   // scratch bytes per partial-result 
 int64_t attn_counter_bytes();               // scratch bytes of the merge counters, behind the slots
 int plan_chunk_attn(int64_t prefix_len, int64_t chunk_len, int n_q_heads, int n_kv_heads, int head_dim,
                     int cus, bool scratch_available, AttnPlan* plan);
+// Which kernel the launch gets: 0 = the tiled one with that plan, else the one for few rows with so many workgroups per slice.
+int attn_row_splits(int64_t prefix_len, int64_t chunk_len, int n_q_heads, int n_kv_heads, int head_dim, int cus, int* splits);
 // Every piece of the launch as kPieceRecordInts ints: workgroup, kv head, row tile, first key tile, end key
 // tile, key tiles of the unit, partial-result slot (-1: whole unit), pieces the merge of its unit reads,
 // whether its own slot is among them, merge counter (-1: none).
@@ -77,6 +79,13 @@ int list_chunk_attn_pieces(int64_t prefix_len, int64_t chunk_len, int n_q_heads,
 int launch_linear(const void* x, const void* w, const void* w2, const void* residual,
                   void* const* out, const int* seg_cols, int n_seg,
                   int64_t m, int64_t n_out, int64_t k, hipStream_t stream);
+
+// Which kernel and tile such a launch gets (dual: with w2): weight rows (dual: of both weights) x tokens of a workgroup's tile,
+// depth of a k stage (0: the direct kernel for few tokens, which has none), tiles the busiest workgroup walks.
+struct LinearPlan {
+  int tile_rows, tile_tokens, tile_k, rounds;
+};
+int linear_plan(int64_t m, int64_t n_out, int64_t k, bool dual, LinearPlan* plan);
 
 int launch_rms_norm(const void* x, const void* gain, void* y, int64_t rows, int hidden, float eps,
                     hipStream_t stream);

@@ -66,6 +66,8 @@ def _load() -> ctypes.CDLL:
     lib.kvra_chunk_attn_noalloc_scratch_bytes.argtypes = []
     lib.kvra_chunk_attn_plan.restype = i32
     lib.kvra_chunk_attn_plan.argtypes = [i64, i64, i32, i32, i32, i32, ctypes.POINTER(KvraAttnPlan)]
+    lib.kvra_chunk_attn_row_splits.restype = i32
+    lib.kvra_chunk_attn_row_splits.argtypes = [i64, i64, i32, i32, i32, i32, ctypes.POINTER(i32)]
     lib.kvra_chunk_attn_pieces.restype = i32
     lib.kvra_chunk_attn_pieces.argtypes = [i64, i64, i32, i32, i32, i32, ctypes.POINTER(ctypes.c_int32), i64,
                                            ctypes.POINTER(i64)]
@@ -93,6 +95,8 @@ def _load() -> ctypes.CDLL:
     lib.kvra_rms_norm.argtypes = [vp, vp, vp, i64, i32, f32, vp]
     lib.kvra_linear.restype = i32
     lib.kvra_linear.argtypes = [vp, vp, vp, vp, vp, i64, i64, i64, vp]
+    lib.kvra_linear_tile.restype = i32
+    lib.kvra_linear_tile.argtypes = [i64, i64, i64, i32, ctypes.POINTER(i32)]
     lib.kvra_qkv_proj.restype = i32
     lib.kvra_qkv_proj.argtypes = [vp, vp, vp, vp, vp, i64, i32, i32, i32, i64, vp]
     lib.kvra_layer_workspace_bytes.restype = i64
@@ -193,6 +197,16 @@ def kvra_chunk_attn_plan(prefix_len, chunk_len, n_q_heads, n_kv_heads, head_dim,
     if rc != 0:
         raise KvraError(rc, "kvra_chunk_attn_plan")
     return {name: getattr(plan, name) for name, _ in KvraAttnPlan._fields_}
+
+
+def kvra_chunk_attn_row_splits(prefix_len, chunk_len, n_q_heads, n_kv_heads, head_dim, n_cus) -> int:
+    """0 if the shape gets the tiled attention kernel, else the workgroups per slice of the kernel for few rows."""
+    splits = ctypes.c_int()
+    rc = _lib.kvra_chunk_attn_row_splits(prefix_len, chunk_len, n_q_heads, n_kv_heads, head_dim, n_cus,
+                                         ctypes.byref(splits))
+    if rc != KVRA_OK:
+        raise KvraError(rc, "kvra_chunk_attn_row_splits")
+    return splits.value
 
 
 PIECE_FIELDS = ("workgroup", "kv_head", "row_tile", "jt0", "jt1", "unit_steps", "slot", "merge_pieces",
@@ -356,6 +370,15 @@ def kvra_linear(x, w, w2, residual, out, m, n, k, stream=None):
                           _stream(stream))
     if rc != KVRA_OK:
         raise KvraError(rc, "kvra_linear")
+
+
+def kvra_linear_tile(m, n, k, swiglu) -> tuple:
+    """(weight rows, tokens, k stage depth or 0 for the kernel for few tokens, tiles of the busiest workgroup)."""
+    tile = (ctypes.c_int * 4)()
+    rc = _lib.kvra_linear_tile(int(m), int(n), int(k), int(bool(swiglu)), tile)
+    if rc != KVRA_OK:
+        raise KvraError(rc, "kvra_linear_tile")
+    return tuple(tile)
 
 
 def kvra_qkv_proj(x, wqkv, q_out, k_out, v_out, m, n_q_heads, n_kv_heads, head_dim, k, stream=None):

@@ -547,3 +547,32 @@ def test_header_is_plain_c_and_a_c_program_can_call_the_host_entry_points(tmp_pa
     assert [int(x) for x in bounds.split()] == want_b
     plan = kvra.kvra_chunk_attn_plan(want_b[7], want_b[8] - want_b[7], 32, 32, 128, 256)
     assert [int(x) for x in rest.split()[:3]] == [plan["slots"], plan["head_steps"], plan["segments"]]
+
+
+def test_which_attention_kernel_a_shape_gets():
+    """0 = the tiled kernel, else workgroups per slice of the kernel for few rows; several only where the tiled plan would go
+    through the scratch too, and never more than there are CUs for."""
+    ask = kvra.kvra_chunk_attn_row_splits
+    assert ask(10048, 1536, 32, 32, 128, 256) == 0 and ask(0, 1024, 32, 32, 128, 256) == 0
+    assert ask(0, 160, 2, 2, 64, 256) == 1 and ask(16384, 1, 32, 32, 128, 256) == 8
+    for prefix, c, H, Hkv, d in [(4097, 3, 16, 16, 64), (23000, 2, 7, 1, 64), (5824, 77, 32, 32, 128), (2500, 179, 4, 2, 64)]:
+        for cus in (1, 64, 256, 304):
+            splits, plan = ask(prefix, c, H, Hkv, d, cus), kvra.kvra_chunk_attn_plan(prefix, c, H, Hkv, d, cus)
+            units = Hkv * ((c * (H // Hkv) + 31) // 32)
+            assert splits <= 1 or (plan["partial_pieces"] > 0 and units * splits <= cus and splits <= 32), (prefix, cus)
+    for bad in [(-1, 1, 2, 2, 64, 256), (0, 0, 2, 2, 64, 256), (0, 1, 3, 2, 64, 256), (0, 1, 2, 2, 96, 256), (0, 1, 2, 2, 64, 0)]:
+        with pytest.raises(kvra.KvraError):
+            ask(*bad)
+
+
+def test_which_tile_a_linear_layer_gets():
+    ask = kvra.kvra_linear_tile
+    assert ask(1, 4096, 4096, False)[2] == 0 and ask(16, 4096, 4096, False)[2] == 0 and ask(17, 4096, 4096, False)[2] > 0
+    assert ask(8192, 8192, 8192, False) == (256, 256, 64, 4)
+    for m, n, k, swiglu in [(77, 4096, 11008, False), (1003, 4672, 4544, False), (300, 704, 256, True), (1 << 24, 1 << 24, 64, True)]:
+        rows, tokens, depth, rounds = ask(m, n, k, swiglu)
+        per_xcd = -(-(-(-n * (2 if swiglu else 1) // rows) * -(-m // tokens)) // 8)
+        assert k % depth == 0 and -(-per_xcd // 64) <= rounds <= -(-per_xcd // 32)   # one or two workgroups per CU
+    for bad in [(0, 32, 64, False), (1, 33, 64, False), (1, 32, 96, False), (1 << 25, 32, 64, False)]:
+        with pytest.raises(kvra.KvraError):
+            ask(*bad)
