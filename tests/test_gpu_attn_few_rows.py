@@ -15,6 +15,9 @@ from gpu_pipeline import to_bits, to_dev
 pytestmark = pytest.mark.gpu
 
 
+BEYOND = [(16, 16, 128, 12000, 130), (8, 8, 64, 20000, 420), (8, 8, 128, 20000, 290)]   # tiles with waves that have no rows
+
+
 @pytest.mark.parametrize("H,Hkv,d,prefix,c", [
     (2, 2, 64, 0, 1), (2, 2, 64, 63, 1), (3, 3, 128, 0, 31), (3, 3, 128, 31, 33), (5, 1, 128, 64, 32),   # one tile, two tiles
     (8, 8, 64, 447, 65), (8, 8, 128, 448, 64), (8, 2, 128, 449, 63),          # eight tiles, and one more or less
@@ -22,9 +25,12 @@ pytestmark = pytest.mark.gpu
     (8, 2, 128, 1699, 300), (8, 2, 128, 777, 524), (4, 2, 64, 2500, 179),     # two and three workgroups per slice
     (32, 32, 128, 5824, 77), (32, 32, 128, 8000, 1), (16, 16, 64, 4097, 3),   # eight heads or more: pairs by XCD
     (7, 1, 64, 23000, 2), (8, 1, 128, 19999, 4),                              # the most workgroups per slice
-    (16, 16, 128, 12000, 130), (8, 8, 64, 20000, 420), (8, 8, 128, 20000, 290),   # beyond: tiles with waves that have no rows
+    *BEYOND,                                                                  # the first ones that go to the tiled kernel
 ])
 def test_few_rows(H, Hkv, d, prefix, c):
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    tiled = kvra.kvra_chunk_attn_row_splits(prefix, c, H, Hkv, d, cus) == 0
+    assert tiled == ((H, Hkv, d, prefix, c) in BEYOND), "not the kernel this shape is here for"
     C, extra = prefix + c, 40
     q, k, v = synth.make_qkv(6, 51, C, H, Hkv, d)
     scale = synth.default_scale(d)

@@ -13,14 +13,16 @@ from paper_2405_05329_amd import kvra, synth
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("H,Hkv,d,prefix,c,border", [
-    (2, 2, 64, 0, 1, 1), (2, 2, 128, 0, 1, 1),                                 # a single key
-    (8, 2, 128, 449, 63, 480), (5, 1, 64, 100, 33, 64), (2, 2, 64, 0, 160, 77),   # few rows, one workgroup per slice
-    (16, 16, 64, 4097, 3, 4098), (7, 1, 128, 9000, 4, 5000),                   # several
-    (71, 1, 64, 700, 900, 1000), (32, 32, 128, 0, 2048, 1111),                 # many rows, whole units
-    (16, 16, 128, 3000, 500, 3200), (32, 32, 128, 0, 1024, 640), (8, 8, 64, 9000, 1200, 9500),   # cut units
+@pytest.mark.parametrize("H,Hkv,d,prefix,c,border,tiled", [
+    (2, 2, 64, 0, 1, 1, False), (2, 2, 128, 0, 1, 1, False),                                 # a single key
+    (8, 2, 128, 449, 63, 480, False), (5, 1, 64, 100, 33, 64, False), (2, 2, 64, 0, 160, 77, False),   # few rows, one workgroup per slice
+    (16, 16, 64, 4097, 3, 4098, False), (7, 1, 128, 9000, 4, 5000, False),                   # several
+    (71, 1, 64, 700, 900, 1000, True), (32, 32, 128, 0, 2048, 1111, True),                 # many rows, all or most units whole
+    (16, 16, 128, 3000, 500, 3200, True), (32, 32, 128, 0, 1024, 640, True), (8, 8, 64, 9000, 1200, 9500, True),   # cut units
 ])
-def test_very_low_scores(H, Hkv, d, prefix, c, border):
+def test_very_low_scores(H, Hkv, d, prefix, c, border, tiled):
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    assert (kvra.kvra_chunk_attn_row_splits(prefix, c, H, Hkv, d, cus) == 0) == tiled, "not the kernel this shape is here for"
     total = prefix + c
     q = torch.full((c, H, d), -2.0 ** 60, dtype=torch.bfloat16, device="cuda")
     k = torch.full((total, Hkv, d), 2.0 ** 50, dtype=torch.bfloat16, device="cuda")
