@@ -1,6 +1,7 @@
 """kvra_linear over the range of its launch rule: every tile shape of the ring kernel (sizes at which the rule picks it,
 ragged in tokens and columns), one k stage only, several tiles per workgroup, odd numbers of stages, and the direct
-kernel for few tokens at the edges of its range.
+kernel for few tokens at the edges of its range.  (That the rule picks them is asserted: here, and for the first list in
+tests/test_library_host.py.)
 
 Bar as for every single operator: fp32 arithmetic and one rounding to bf16, |err| <= 2^-8 |want| + 1e-4 against the
 fp64 oracle (half a unit in the last place is at most 2^-8 of the value; the fp32 sums over k <= 5632 unit-variance terms
@@ -29,14 +30,32 @@ pytestmark = pytest.mark.gpu
     (77, 4576, 384, "plain"), (131, 1376, 384, "swiglu"),            # 64 x 64, k shared out over two waves
     (97, 2080, 384, "residual"), (77, 1440, 384, "swiglu"),          # 32 x 64
     (39, 96, 384, "residual"), (39, 32, 384, "swiglu"),              # 32 x 32
-    (5000, 4096, 64, "residual"), (4001, 2080, 64, "swiglu"),        # one stage per tile, several tiles per workgroup
-    (6001, 4128, 128, "plain"),                                      # several large tiles per workgroup
+    (5000, 4096, 64, "residual"), (4001, 2080, 64, "swiglu"),        # 128 x 128, one stage per tile, several tiles per workgroup
+    (6001, 4128, 128, "plain"),                                      # 128 x 128, several tiles of two stages
     (1, 32, 64, "plain"), (16, 544, 320, "residual"), (8, 8224, 128, "plain"), (9, 8224, 128, "residual"),
     (5, 1056, 5632, "residual"), (17, 544, 320, "plain"), (1, 64, 128, "swiglu"),   # few tokens
     (17, 96, 128, "swiglu"), (16, 2080, 320, "swiglu"), (16, 4064, 64, "swiglu"), (8, 4128, 576, "swiglu"),   # SwiGLU: direct
     (9, 4128, 64, "swiglu"), (4, 8224, 576, "swiglu"), (5, 8224, 64, "swiglu"), (3, 32, 4608, "swiglu"),      # or tiled
 ])
 def test_linear_tiles(m, n, k, mode):
+    check_linear(m, n, k, mode)
+
+
+@pytest.mark.parametrize("m,n,k,mode,tile", [
+    (3746, 8768, 64, "plain", (256, 192, 64, 3)), (2564, 6272, 64, "swiglu", (256, 192, 64, 3)),
+    (2761, 8768, 64, "swiglu", (256, 256, 64, 3)), (5716, 5024, 128, "plain", (256, 256, 64, 2)),
+    (3549, 6688, 128, "residual", (192, 256, 64, 2)), (2564, 6272, 320, "plain", (192, 192, 64, 2)),
+    (5519, 2944, 320, "residual", (128, 256, 64, 2)), (4140, 2944, 384, "plain", (128, 192, 64, 2)),
+])
+def test_tiles_in_turn(m, n, k, mode, tile):
+    """The interleaved form of the ring kernel (the six larger tiles) with several tiles per workgroup: the loads run on into
+    the next tile while the last one is finished, with one stage per tile, two, and numbers at which the ring does not come
+    out even."""
+    assert kvra.kvra_linear_tile(m, n, k, mode == "swiglu") == tile
+    check_linear(m, n, k, mode)
+
+
+def check_linear(m, n, k, mode):
     x = synth.normal_bf16(5, 23, 0, (m, k))
     w = synth.normal_bf16(5, 23, 1, (n, k), std=k ** -0.5)
     xf, wf = orc.bf16_bits_to_f64(x), orc.bf16_bits_to_f64(w)

@@ -576,3 +576,23 @@ def test_which_tile_a_linear_layer_gets():
     for bad in [(0, 32, 64, False), (1, 33, 64, False), (1, 32, 96, False), (1 << 25, 32, 64, False)]:
         with pytest.raises(kvra.KvraError):
             ask(*bad)
+
+
+@pytest.mark.parametrize("tile,shapes", [
+    ((256, 256, 64), [(2221, 5408, 192, False), (1435, 4128, 192, True)]),
+    ((256, 192, 64), [(4093, 2144, 192, False), (849, 4960, 192, True)]),
+    ((192, 256, 64), [(2691, 4384, 192, False)]),
+    ((192, 192, 64), [(2317, 3360, 192, False), (649, 5472, 192, True)]),
+    ((128, 256, 64), [(3789, 1568, 320, False), (389, 5472, 384, True)]),
+    ((128, 192, 64), [(813, 4768, 192, False), (527, 3424, 192, True)]),
+    ((128, 128, 64), [(321, 5728, 192, False), (195, 4384, 192, True)]),
+    ((64, 128, 64), [(325, 4896, 192, False), (197, 3680, 192, True)]),
+    ((64, 64, 64), [(77, 96, 192, False), (77, 96, 192, True)]),
+    ((64, 64, 128), [(77, 4576, 384, False), (131, 1376, 384, True)]),
+    ((32, 64, 128), [(97, 2080, 384, False), (77, 1440, 384, True)]),
+    ((32, 32, 128), [(39, 96, 384, False), (39, 32, 384, True)]),
+])
+def test_the_gpu_tests_of_the_linear_kernel_meet_every_tile(tile, shapes):
+    """The shapes with which tests/test_gpu_linear_tiles.py runs each tile of the ring kernel are ones the rule gives it."""
+    for shape in shapes:
+        assert kvra.kvra_linear_tile(*shape)[:3] == tile, shape
