@@ -70,11 +70,14 @@ __device__ __forceinline__ void sincos_reduced(double phi, double* s, double* c)
 // (prefix + row) * inv_freq[i] in fp64 and park them in LDS as fp32; all threads move "pair units" (a 16-byte piece of the
 // low half of a head row and its partner in the high half) of K and Q, and plain 16-byte pieces of V.
 // A short chunk is a chain of latencies, not of traffic, so everything a thread needs first - its frequency (from the
-// kernel arguments), its first pieces of V and its first units of K and Q - is on its way before the angles are worked out.
+// kernel arguments), its first pieces of V and its first units of K and Q - is loaded together, ahead of the angles.
 // Long chunks use the largest TOK (every thread has an angle); short ones use fewer tokens per workgroup so that the launch
 // still puts several workgroups on every CU.  Before (V, then the library's sincos, then K, then Q) -> after, back to back
-// launches: 160 tokens, 2 heads x 64: 4.3 -> 3.1 us; 1003 tokens, 71 heads on 1: 7.6 -> 5.6; 1024 tokens, 32 heads x 128: 9.7
-// -> 8.9; 5824 tokens: 43.7 -> 42.4 (6.8 TB/s, much of it from the last-level cache).
+// launches: 160 tokens, 2 heads x 64: 4.4 -> 3.4 us; 1003 tokens, 71 heads on 1: 7.6 -> 5.3; 1024 tokens, 32 heads x 128: 9.3
+// -> 8.2; 5824 tokens: 43.2 -> 43.0 (6.7 TB/s, much of it from the last-level cache).
+// Without rotation nothing waits for angles, and V and K are two plain copies: loaded together like the rest, 1183 tokens of 32
+// heads took 6.0 us, one after the other 5.3 (two streams of a read and a write each overlap better across waves than one of
+// four).  With rotation but without queries V leaves before the angles: 1132 tokens 6.6 -> 6.45 us (6.2 before either).
 template <int D, int TOK>
 __global__ __launch_bounds__(256) void append_kv_kernel(AppendArgs a) {
   constexpr int HALF = D / 2;
@@ -90,22 +93,42 @@ __global__ __launch_bounds__(256) void append_kv_kernel(AppendArgs a) {
   const int ntok = min(TOK, a.chunk_len - tok0);
   const int Hkv = a.n_kv_heads, H = a.n_q_heads;
 
+  // V: bit-exact copy; without rotation K as well
+  const int v_total = ntok * Hkv * CHUNKS;
+  const long long from = static_cast<long long>(tok0) * Hkv * CHUNKS, to = (a.prefix_len + tok0) * Hkv * CHUNKS;
+  const u16x8* v_src = reinterpret_cast<const u16x8*>(a.v_in) + from;
+  u16x8* v_dst = reinterpret_cast<u16x8*>(a.v_cache) + to;
+  if (!a.use_rope) {
+#pragma unroll 4
+    for (int u = tid; u < v_total; u += 256) v_dst[u] = v_src[u];
+    const u16x8* k_src = reinterpret_cast<const u16x8*>(a.k_in) + from;
+    u16x8* k_dst = reinterpret_cast<u16x8*>(a.k_cache) + to;
+    for (int u = tid; u < v_total; u += 512) {
+      const u16x8 k0 = k_src[u], k1 = k_src[min(u + 256, v_total - 1)];
+      k_dst[u] = k0;
+      if (u + 256 < v_total) k_dst[u + 256] = k1;
+    }
+    return;
+  }
+
   const int t_mine = tid / HALF;
-  const bool has_angle = a.use_rope && t_mine < ntok;
+  const bool has_angle = t_mine < ntok;
   double freq = 0.0;
   if (has_angle) freq = a.inv_freq[tid % HALF];
 
-  // V: bit-exact copy
-  const int v_total = ntok * Hkv * CHUNKS;
-  const u16x8* v_src = reinterpret_cast<const u16x8*>(a.v_in) + static_cast<long long>(tok0) * Hkv * CHUNKS;
-  u16x8* v_dst = reinterpret_cast<u16x8*>(a.v_cache) + (a.prefix_len + tok0) * Hkv * CHUNKS;
   u16x8 v[AHEAD];
 #pragma unroll
   for (int i = 0; i < AHEAD; ++i)
     if (tid + 256 * i < v_total) v[i] = v_src[tid + 256 * i];
 
-  // units of a token: those of its K heads, which go to the cache, then (rotation only) those of its Q heads, in place
-  const int heads = Hkv + (a.q != nullptr && a.use_rope ? H : 0);
+  auto store_v = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < AHEAD; ++i)
+      if (tid + 256 * i < v_total) v_dst[tid + 256 * i] = v[i];
+  };
+
+  // units of a token: those of its K heads, which go to the cache, then those of its Q heads, in place
+  const int heads = Hkv + (a.q != nullptr ? H : 0);
   const int per_tok = heads * PAIRS, total = ntok * per_tok;
   u16x8 lo[AHEAD], hi[AHEAD];
   unsigned short* dst[AHEAD];
@@ -132,37 +155,36 @@ __global__ __launch_bounds__(256) void append_kv_kernel(AppendArgs a) {
     }
   };
   load_units(tid);
+  // One wait for all of it: behind the branches above the compiler does not know how many loads are on their way, and would
+  // wait for everything, the stores before included, ahead of each store (1132 tokens, 32 heads x 128: 9.3 us, so 9.1).
+  __builtin_amdgcn_s_waitcnt(0x0F70);
+  // Without queries V is half of what is moved: it leaves before the angles are worked out.
+  if (a.q == nullptr) store_v();
 
-  if (a.use_rope) {
-    if (has_angle) {
-      const double phi = static_cast<double>(a.prefix_len + tok0 + t_mine) * freq;
-      double s, c;
-      if (phi < 67108864.0) sincos_reduced(phi, &s, &c);
-      else sincos(phi, &s, &c);            // a rope base below 1
-      cs[t_mine][tid % HALF] = static_cast<float>(c);
-      sn[t_mine][tid % HALF] = static_cast<float>(s);
-    }
-    __syncthreads();
+  if (has_angle) {
+    const double phi = static_cast<double>(a.prefix_len + tok0 + t_mine) * freq;
+    double s, c;
+    if (phi < 67108864.0) sincos_reduced(phi, &s, &c);
+    else sincos(phi, &s, &c);              // a rope base below 1
+    cs[t_mine][tid % HALF] = static_cast<float>(c);
+    sn[t_mine][tid % HALF] = static_cast<float>(s);
   }
+  __syncthreads();
 
-#pragma unroll
-  for (int i = 0; i < AHEAD; ++i)
-    if (tid + 256 * i < v_total) v_dst[tid + 256 * i] = v[i];
+  if (a.q != nullptr) store_v();
   for (int u0 = tid; u0 < total; u0 += 256 * AHEAD) {
     if (u0 != tid) load_units(u0);
 #pragma unroll
     for (int i = 0; i < AHEAD; ++i) {
       if (u0 + 256 * i >= total) break;
-      u16x8 olo = lo[i], ohi = hi[i];
-      if (a.use_rope) {
-        const float* c = &cs[0][0] + where[i];
-        const float* s = &sn[0][0] + where[i];
+      const float* c = &cs[0][0] + where[i];
+      const float* s = &sn[0][0] + where[i];
+      u16x8 olo, ohi;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const float x0 = bf16_to_f32(lo[i][e]), x1 = bf16_to_f32(hi[i][e]);
-          olo[e] = f32_to_bf16_rne(fmaf(x0, c[e], -(x1 * s[e])));
-          ohi[e] = f32_to_bf16_rne(fmaf(x1, c[e], x0 * s[e]));
-        }
+      for (int e = 0; e < 8; ++e) {
+        const float x0 = bf16_to_f32(lo[i][e]), x1 = bf16_to_f32(hi[i][e]);
+        olo[e] = f32_to_bf16_rne(fmaf(x0, c[e], -(x1 * s[e])));
+        ohi[e] = f32_to_bf16_rne(fmaf(x1, c[e], x0 * s[e]));
       }
       *reinterpret_cast<u16x8*>(dst[i]) = olo;
       *reinterpret_cast<u16x8*>(dst[i] + HALF) = ohi;

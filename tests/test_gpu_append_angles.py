@@ -43,3 +43,22 @@ def test_angles(d, prefix, c, base, with_q):
         qb = orc.bf16_bits_to_f64(to_bits(q))
         worst = float(np.max(np.abs(qb - want[:, None]) - slack[:, None]))
         assert worst <= 0, worst
+
+
+@pytest.mark.parametrize("d,Hkv,prefix,c", [
+    (64, 1, 0, 1), (64, 3, 5, 2050), (128, 15, 1, 3), (128, 16, 0, 1), (128, 17, 9, 2), (128, 32, 7, 3),   # 8 .. 512 pieces a token
+    (128, 33, 0, 5), (64, 71, 2, 5000), (64, 1, 3, 16500), (128, 49, 0, 4100),
+])
+def test_copy_without_rotation(d, Hkv, prefix, c):
+    """rope_base 0: K and V arrive bit for bit (any pattern, NaNs included), Q and every other row stay as they are."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(3)
+    bits = lambda *shape: torch.randint(-32768, 32768, shape, dtype=torch.int16, device="cuda", generator=gen)
+    k, v, q = bits(c, Hkv, d), bits(c, Hkv, d), bits(c, 2 * Hkv, d)
+    kc, vc = bits(prefix + c + 3, Hkv, d), bits(prefix + c + 3, Hkv, d)
+    want_k, want_v, want_q = kc.clone(), vc.clone(), q.clone()
+    want_k[prefix:prefix + c], want_v[prefix:prefix + c] = k, v
+    bf16 = lambda t: t.view(torch.bfloat16)
+    kvra.kvra_append_kv(bf16(k), bf16(v), bf16(q), bf16(kc), bf16(vc), prefix, c, prefix + c + 3, 2 * Hkv, Hkv, d, 0.0)
+    torch.cuda.synchronize()
+    assert torch.equal(kc, want_k) and torch.equal(vc, want_v) and torch.equal(q, want_q)
