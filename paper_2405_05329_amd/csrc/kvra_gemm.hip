@@ -673,7 +673,10 @@ int linear_plan(int64_t m, int64_t n_out, int64_t k, bool dual, LinearPlan* plan
 // ---- RMSNorm ------------------------------------------------------------------------------------
 // y[t, :] = x[t, :] / sqrt(mean(x[t, :]^2) + eps) * gain, fp32 arithmetic, one workgroup per token.
 // HBM-bound: every element is read once and written once with 16-byte accesses.  The gain is on its way with the row (with
-// few rows the kernel is a chain of latencies: 1 x 4096 2.5 -> 2.3 us; 5824 x 4096: 15.7 -> 15.0, 6.4 TB/s).
+// few rows the kernel is a chain of latencies), and there is a variant for one, two and four pieces per thread: with four in all
+// of them a narrow row spends its time on branches around pieces that it does not have (and the early gain doubles
+// those).  Gain late, four -> gain early, four -> as it is: 5208 x 256 4.9 -> 5.5 -> 4.0 us; 4000 x 1024 5.2 -> 5.5 -> 4.5;
+// 1898 x 2048 4.15 -> 4.3 -> 3.9; 5824 x 4096 15.3 -> 14.7 -> 14.7 (6.5 TB/s).
 struct NormArgs {
   const __bf16* x;
   const __bf16* gain;
@@ -686,16 +689,17 @@ struct NormArgs {
 constexpr int kNormThreads = 256;
 constexpr int kNormMaxPieces = 4;   // 16-byte pieces a thread keeps in registers: hidden <= 8192
 
+template <int PIECES>   // at most so many per thread
 __global__ __launch_bounds__(kNormThreads) void rms_norm_kernel(NormArgs a) {
   __shared__ float part[kNormThreads / 64];
   const int tid = threadIdx.x;
   const int pieces = a.hidden / 8;
   const bf16x8* xr = reinterpret_cast<const bf16x8*>(a.x + static_cast<long long>(blockIdx.x) * a.hidden);
   const bf16x8* gr = reinterpret_cast<const bf16x8*>(a.gain);
-  bf16x8 v[kNormMaxPieces], g[kNormMaxPieces];
+  bf16x8 v[PIECES], g[PIECES];
   float ss = 0.0f;
 #pragma unroll
-  for (int i = 0; i < kNormMaxPieces; ++i) {
+  for (int i = 0; i < PIECES; ++i) {
     const int p = tid + i * kNormThreads;
     if (p < pieces) {
       v[i] = xr[p];
@@ -703,7 +707,7 @@ __global__ __launch_bounds__(kNormThreads) void rms_norm_kernel(NormArgs a) {
     }
   }
 #pragma unroll
-  for (int i = 0; i < kNormMaxPieces; ++i) {
+  for (int i = 0; i < PIECES; ++i) {
     if (tid + i * kNormThreads < pieces) {
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
@@ -722,7 +726,7 @@ __global__ __launch_bounds__(kNormThreads) void rms_norm_kernel(NormArgs a) {
   const float rinv = 1.0f / sqrtf(tot / static_cast<float>(a.hidden) + a.eps);
   bf16x8* yr = reinterpret_cast<bf16x8*>(a.y + static_cast<long long>(blockIdx.x) * a.hidden);
 #pragma unroll
-  for (int i = 0; i < kNormMaxPieces; ++i) {
+  for (int i = 0; i < PIECES; ++i) {
     const int p = tid + i * kNormThreads;
     if (p < pieces) {
       bf16x8 o;
@@ -741,7 +745,11 @@ int launch_rms_norm(const void* x, const void* gain, void* y, int64_t rows, int 
   a.rows = static_cast<int>(rows);
   a.hidden = hidden;
   a.eps = eps;
-  return launch_kernel(rms_norm_kernel, dim3(static_cast<unsigned>(rows)), dim3(kNormThreads), a, stream);
+  const dim3 grid(static_cast<unsigned>(rows)), block(kNormThreads);
+  const int per_thread = (hidden / 8 + kNormThreads - 1) / kNormThreads;
+  if (per_thread == 1) return launch_kernel(rms_norm_kernel<1>, grid, block, a, stream);
+  if (per_thread == 2) return launch_kernel(rms_norm_kernel<2>, grid, block, a, stream);
+  return launch_kernel(rms_norm_kernel<kNormMaxPieces>, grid, block, a, stream);
 }
 
 int rms_norm_max_hidden() { return kNormThreads * kNormMaxPieces * 8; }

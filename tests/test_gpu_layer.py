@@ -55,6 +55,18 @@ def test_rms_norm(rows, hidden):
     _one_rounding(to_bits(y), orc.rms_norm(_f64(x), _f64(g), 1e-6), f"rms_norm {rows}x{hidden}")
 
 
+@pytest.mark.parametrize("rows,hidden", [(3, 8), (40, 2040), (41, 2048), (2, 2056), (9, 4088), (7, 4104), (11, 6152)])
+def test_rms_norm_at_the_edges_of_its_variants(rows, hidden):
+    """One, two and up to four 16-byte pieces per thread; rows around the output stay untouched."""
+    x = synth.normal_bf16(0, 20, 0, (rows, hidden), std=1.7)
+    g = synth.normal_bf16(0, 20, 1, (hidden,), std=1.0)
+    y = torch.full((rows + 2, hidden), 7.0, dtype=torch.bfloat16, device="cuda")
+    kvra.kvra_rms_norm(to_dev(x), to_dev(g), y[1:rows + 1], rows, hidden, 1e-6)
+    torch.cuda.synchronize()
+    assert bool((y[0] == 7.0).all()) and bool((y[-1] == 7.0).all())
+    _one_rounding(to_bits(y[1:rows + 1]), orc.rms_norm(_f64(x), _f64(g), 1e-6), f"rms_norm {rows}x{hidden}")
+
+
 @pytest.mark.parametrize("m,n,k", [(1, 32, 64), (300, 512, 256), (257, 1056, 320), (513, 96, 4096), (64, 4352, 128),
                                    (1000, 768, 1024)])
 @pytest.mark.parametrize("mode", ["plain", "residual", "swiglu"])
