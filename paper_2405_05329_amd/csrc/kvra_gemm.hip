@@ -13,7 +13,7 @@
 // Pipeline of a workgroup.  Both operand tiles come by LDS-direct loads into a ring of k stages, a stage 64 deep (a whole
 // 128-byte line of every row: with 32-deep stages each line came in two halves, -10 %); the ring is refilled as the waves
 // walk through it, across tiles when a workgroup has more than one.  Everything that is not an MFMA is placed between
-// MFMAs: operand reads one step ahead, the loads of the stage that replaces the one just read (4 or 8 per wave and stage;
+// MFMAs: operand reads one step ahead, the loads of the stage that replaces the one just read (2 to 8 per wave and stage;
 // in a burst they block the wave that issues them for hundreds of cycles), and the one barrier per stage sits inside the
 // MFMA stream, where every wave already holds the operands of the next few MFMAs.
 // 8192^3: 974 -> 777 us (1416 TFLOP/s), 11584 x 12288 x 4096: 1010 -> 912 us; what remains is power: with the loads and
@@ -76,11 +76,13 @@ struct GemmTile {
 
 // 64 lanes x 16 bytes -> 1 KiB of consecutive LDS (lane l lands at +16 l); inline assembly so that completion can be
 // awaited by hand with s_waitcnt vmcnt(n) instead of a full drain per load.  With on_mask = 0 no lane is enabled and
-// nothing moves: no branch around it, so that it can sit between MFMAs.
+// nothing moves: no branch around it, so that it can sit between MFMAs.  Between a vector instruction that writes a scalar
+// register (a spilled address coming back) and a memory instruction that reads it five wait states have to lie, and the compiler
+// does not see that one stands in here: two scalar moves and s_nop 2 make them up (no slower: 8192^3 777 and 767 us).
 __device__ __forceinline__ void gemm_lds_dma16_if(unsigned long long on_mask, const void* uniform_base,
                                                   unsigned lane_byte_off, unsigned lds_byte_addr) {
   unsigned long long saved;
-  asm volatile("s_mov_b32 m0, %3\n\ts_and_saveexec_b64 %0, %4\n\tglobal_load_lds_dwordx4 %1, %2\n\ts_mov_b64 exec, %0"
+  asm volatile("s_mov_b32 m0, %3\n\ts_and_saveexec_b64 %0, %4\n\ts_nop 2\n\tglobal_load_lds_dwordx4 %1, %2\n\ts_mov_b64 exec, %0"
                : "=&s"(saved)
                : "v"(lane_byte_off), "s"(uniform_base), "s"(lds_byte_addr), "s"(on_mask)
                : "memory", "m0", "scc");
