@@ -458,7 +458,7 @@ def main():
         from paper_2405_05329_amd import probe
         alone = probe.matrix_pipes_alone(torch)
         alone["achieved_over_it"] = achieved / alone["tflops"]
-        alone["what"] = ("v_mfma_f32_32x32x16_bf16 back to back on register operands, no memory or LDS access in the "
+        alone["what"] = ("v_mfma_f32_16x16x32_bf16 (the kernel's instruction) back to back on register operands, no memory or LDS access in the "
                          "loop, measured in this process after the timed steps; context for frac, which stays "
                          "against the published peak")
         result["roofline"]["matrix_pipes_alone"] = alone
@@ -498,8 +498,10 @@ def main():
         # Times of append + attention on a grid of (prefix, chunk) pairs; between grid points the cost follows
         # the launch plan, which knows what the grid cannot show: the row-tile count jumps with the chunk
         # length (a 1088-token chunk needs five row tiles per head, a 1024-token one four), and the schedule
-        # gives every compute unit plan.steps_per_slot tile steps.  Model, fitted by least squares:
-        #   t = a0 + steps_per_slot * (a1 + a2 * rows_per_tile / 256) + a3 * chunk
+        # gives every compute unit plan.steps_per_slot tile steps.  Launches of few rows go to another kernel, whose work is
+        # what its 32-row slices read.  Model, fitted by least squares:
+        #   t = a0 + steps_per_slot * (a1 + a2 * rows_per_tile / 256) + a3 * chunk     (the plan's kernel)
+        #   t = b0 + b1 * slices * key tiles                                           (the one for few rows)
         qw = q_work[0]
 
         def measure(prefix, c):
@@ -522,8 +524,10 @@ def main():
             return float(np.mean([evs[j][1].elapsed_time(evs[j + 1][1]) for j in range(n_rep)]))
 
         def features(prefix, c):
+            if kvra.kvra_chunk_attn_row_splits(prefix, c, H, Hkv, d, cus) > 0:
+                return [0.0, 0.0, 0.0, 0.0, 1.0, c * (H // Hkv) / 32.0 * Hkv * (prefix + c) / 64.0]
             pl = kvra.kvra_chunk_attn_plan(prefix, c, H, Hkv, d, cus)
-            return [1.0, pl["steps_per_slot"], pl["steps_per_slot"] * pl["rows_per_tile"] / 256.0, float(c)]
+            return [1.0, pl["steps_per_slot"], pl["steps_per_slot"] * pl["rows_per_tile"] / 256.0, float(c), 0.0, 0.0]
 
         step_c = max(64, C // 256 * 8)
         cs = sorted({step_c * k for k in (1, 2, 3, 4, 6, 8, 12, 16, 24)} | {C // 16 + 64, C // 8 - 192, C // 4 + 256, C // 3})
@@ -585,9 +589,10 @@ def main():
         _, ref_total = measured_chunks(bounds)
         mk = max(cost(bal[i], bal[i + 1] - bal[i]) for i in range(p))
         result["makespan"]["kvra_balance"] = {
-            "cost_model": "t = a0 + steps_per_slot * (a1 + a2 * rows_per_tile / 256) + a3 * chunk, fitted to "
+            "cost_model": "t = a0 + steps_per_slot * (a1 + a2 * rows_per_tile / 256) + a3 * chunk, for launches of few rows "
+                          "b0 + b1 * slices * key tiles, fitted to "
                           f"{len(table)} measured (prefix, chunk) points (steps_per_slot and rows_per_tile from "
-                          "kvra_chunk_attn_plan), times the measured / model ratio of the candidates the search has "
+                          "kvra_chunk_attn_plan, the kernel from kvra_chunk_attn_row_splits), times the measured / model ratio of the candidates the search has "
                           "already run (Gaussian weights around each measured chunk)",
             "coefficients_ms": [float(x) for x in coef],
             "fit_error_mean": float(resid.mean()), "fit_error_max": float(resid.max()),
