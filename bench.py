@@ -29,16 +29,14 @@ WORKLOAD = "llama7b_16k_balanced"
 
 # HBM bytes per kvra_chunk_attn call (mean over the calls of a step) from rocprofv3 --pmc FETCH_SIZE /
 # WRITE_SIZE runs of this file, scaled by what the same counters read for a plain copy of known size.
-# A measured constant, not a live reading: `source` names the tracked summary it was copied from and the
-# commit whose kernel that run profiled.
+# A measured constant, not a live reading: `source` names the tracked summary it was copied from.
 ATTN_TRAFFIC = {
-    "llama7b_16k_balanced": {"bytes": 3.18e8,
-                             "source": "profiles/chunk_attn_append_llama7b_16k_balanced.md: FETCH_SIZE 265.8 MiB + WRITE_SIZE "
-                                       "37.4 MiB per call (persistent kernel, merge inside, tails of chunks 3-7 run in gangs, "
-                                       "the merging piece of a cut unit stores no partial result of its own); above the "
-                                       "algorithmic bytes because the pieces of the leftover units of chunks 0 and 1, and a "
-                                       "fourth of the tails of chunks 3 and 4, read the K/V of their head at other times than "
-                                       "its other row tiles (L2 hit rate 76 %); 1.3 TB/s at this launch time, a sixth of the "
+    "llama7b_16k_balanced": {"bytes": 3.24e8,
+                             "source": "profiles/chunk_attn_append_llama7b_16k_balanced.md: FETCH_SIZE 274.4 MiB + WRITE_SIZE "
+                                       "34.8 MiB per call (16x16x32 MFMAs, no loads for tiles past a piece's end); above the "
+                                       "algorithmic bytes because the pieces of the leftover units and tails of chunks 0 to 2, and "
+                                       "a part of the tails of chunks 3 and 4, read the K/V of their head at other times than "
+                                       "its other row tiles (L2 hit rate 74 %); 1.5 TB/s at this launch time, a fifth of the "
                                        "HBM peak, so not what bounds the kernel"},
 }
 
