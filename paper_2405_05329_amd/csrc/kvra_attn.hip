@@ -10,15 +10,17 @@
 // so P never visits LDS.
 //
 // Why 16x16x32 and not 32x32x16 (same bytes read, same registers).  The chip is power-managed, and the 16x16x32 form,
-// which reads and writes its sums half as often, does the same work at 12 % less energy: MFMAs alone on N(0,1) operands, all
-// CUs, 2026 against 1786 TFLOP/s; the tile loop clocks 1.97 instead of 1.65 GHz.  The price is issue: an MFMA keeps its
-// SIMD from issuing vector instructions for 8 cycles whatever its size (80 vector instructions of a softmax: 529 cycles
-// alone, 704 beside 32x32x16 MFMAs, 997 beside 16x16x32 ones), and there are twice as many.  So the form only pays
+// which reads and writes its sums half as often, does the same work at less energy: MFMAs alone on N(0,1) operands, all
+// CUs, 2028 against 1821 TFLOP/s; the tile loop of 16k launches clocks 1.9-2.1 instead of 1.6-1.8 GHz.  The price is issue: an MFMA
+// keeps its SIMD from issuing vector instructions for as long whatever its size, and there are twice as many (a multiply-add
+// costs its wave 4.4 cycles alone, 5.7 beside 32x32x16 MFMAs and 7.9 beside 16x16x32 ones, an exponential 8.6, 11.1 and 15.2).
+// So the form only pays
 // with a lean VALU block: staging without any bookkeeping (buffer loads whose hardware bounds check stands for "past the end
 // of the cache" and "past the piece"), no branch for waves that are done (they leave the loop), one copy of the softmax
-// code.  Both together: 12928 + 1280 tokens, 32 heads x 128: 240 -> 224 us; 16384 causal: 1735 -> 1592 us; 71 heads x 64 on
-// one KV head, 8192 causal: 599 -> 565 us.  The softmax laid between the wave's own P.V MFMAs instead (every wave always
-// has both kinds to issue) is 11 % slower: the SIMD serves its older wave first, and a wave whose next
+// code.  Both together: 12928 + 1280 tokens, 32 heads x 128: 233 -> 219 us; 5824 causal: 242 -> 223; 71 heads x 64 on
+// one KV head, 4096 causal: 169 -> 158.  On short launches that leave part of the chip idle the clock is at its top with either
+// form: 3529 tokens, 16 heads x 64 on one KV head 43.3 -> 44.4 us.  The softmax laid between the wave's own P.V MFMAs instead (every
+// wave always has both kinds to issue) is 11 % slower: the SIMD serves its older wave first, and a wave whose next
 // instruction is an MFMA that has to wait holds back its exponentials too.
 //
 // Rows.  With grouped queries (G = n_q_heads / n_kv_heads > 1) the G heads that share a KV head

@@ -7,8 +7,8 @@
 // operands of v_mfma_f32_16x16x32_bf16 want (lane (r, kg) holds 8 consecutive k of row r).  The
 // weight rows go to the A side and the token rows to the B side, i.e. the kernel forms the
 // TRANSPOSED tile out^T[n, m]: in the 16x16 accumulator layout a lane then owns one token and
-// 4 consecutive n.  (The 32x32x16 form of the same work holds a 12 % lower rate on this power-managed chip: a loop of nothing
-// but MFMAs on N(0,1) operands, all CUs, 1786 against 2026 TFLOP/s - half as deep, it writes its sums twice as often.)
+// 4 consecutive n.  (The 32x32x16 form of the same work holds a 10 % lower rate on this power-managed chip: a loop of nothing
+// but MFMAs on N(0,1) operands, all CUs, 1821 against 2028 TFLOP/s - half as deep, it writes its sums twice as often.)
 //
 // Pipeline of a workgroup.  Both operand tiles come by LDS-direct loads into a ring of k stages, a stage 64 deep (a whole
 // 128-byte line of every row: with 32-deep stages each line came in two halves, -10 %); the ring is refilled as the waves
