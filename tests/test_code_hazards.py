@@ -118,6 +118,10 @@ RULES = {
     "vector-written scalar -> memory": (lambda i: scalar(i.uses) if i.vmem else (), lambda i: i.valu, 5),
     # a vector instruction writes a scalar register (a comparison's mask), another vector instruction reads it
     "vector-written scalar -> vector": (lambda i: scalar(i.uses) if i.valu else (), lambda i: i.valu, 2),
+    # a matrix product's result, read by anything but another one (eight is what the compiler keeps behind the 16x16x32 form)
+    "matrix product -> vector or memory": (lambda i: {r for r in i.uses if r[0] in "va" and r != "vcc"}
+                                           if "mfma" not in i.op and (i.valu or i.vmem or i.op.startswith("ds_")) else (),
+                                           lambda i: "mfma" in i.op, 8),
     # the LDS address of a load straight into LDS
     "m0 -> load to LDS": (lambda i: {"m0"} if i.to_lds else (), lambda i: not i.valu, 1),
 }
