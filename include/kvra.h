@@ -372,9 +372,9 @@ typedef struct {
 int64_t kvra_layer_workspace_bytes(const kvra_layer* layer, int64_t chunk_len);
 
 /*
- * One layer over one chunk: RMSNorm, q/k/v projections, kvra_append_kv (rotary embedding + cache
- * rows [prefix_len, prefix_len + chunk_len)), kvra_chunk_attn, output projection + residual,
- * RMSNorm, SwiGLU MLP + residual; eight launches on `stream`.
+ * One layer over one chunk: RMSNorm, q/k/v projections with what kvra_append_kv does on their way out (rotary
+ * embedding, cache rows [prefix_len, prefix_len + chunk_len)), kvra_chunk_attn, output projection + residual,
+ * RMSNorm, SwiGLU MLP + residual; seven launches on `stream`.
  *   x, y        [chunk_len, hidden]; y may not alias x
  *   workspace   caller-owned device memory, 256-byte aligned, at least
  *               kvra_layer_workspace_bytes(layer, chunk_len); contents are scratch

@@ -261,11 +261,21 @@ extern "C" int kvra_layer_chunk(const kvra_layer* L, const void* x, void* y, voi
   if ((rc = check_linear(c, 2 * static_cast<int64_t>(L->ffn), L->hidden)) != KVRA_OK) return rc;
   if ((rc = check_linear(c, L->hidden, L->ffn)) != KVRA_OK) return rc;
   char* ws = static_cast<char*>(workspace);
-  void *h = ws + w.h, *q = ws + w.q, *k = ws + w.k, *v = ws + w.v, *attn = ws + w.attn, *x2 = ws + w.x2, *act = ws + w.act;
-  if ((rc = kvra_rms_norm(x, L->norm1, h, c, L->hidden, L->rms_eps, stream)) != KVRA_OK) return rc;
-  if ((rc = kvra_qkv_proj(h, L->wqkv, q, k, v, c, L->n_q_heads, L->n_kv_heads, L->head_dim, L->hidden, stream)) != KVRA_OK) return rc;
-  if ((rc = kvra_append_kv(k, v, q, k_cache, v_cache, prefix_len, c, capacity, L->n_q_heads, L->n_kv_heads,
-                           L->head_dim, L->rope_base, stream)) != KVRA_OK) return rc;
+  void *h = ws + w.h, *q = ws + w.q, *k = ws + w.k, *attn = ws + w.attn, *x2 = ws + w.x2, *act = ws + w.act;
+  const hipStream_t st = static_cast<hipStream_t>(stream);
+  const int64_t kvd = static_cast<int64_t>(L->n_kv_heads) * L->head_dim;
+  // The projection rotates Q and K and puts K and V into their cache rows; the angles stand where an unrotated K and V would
+  // have been: chunk_len * head_dim floats, at most the room of one KV head's K and V.
+  float* const angles = L->rope_base > 0.0f ? static_cast<float*>(k) : nullptr;
+  if (angles != nullptr)
+    rc = kvra::launch_rms_norm_angles(x, L->norm1, h, c, L->hidden, L->rms_eps, prefix_len, L->head_dim, L->rope_base, angles, st);
+  else
+    rc = kvra::launch_rms_norm(x, L->norm1, h, c, L->hidden, L->rms_eps, st);
+  if (rc != KVRA_OK) return rc;
+  void* outs[3] = {q, static_cast<char*>(k_cache) + prefix_len * kvd * 2, static_cast<char*>(v_cache) + prefix_len * kvd * 2};
+  const int cols[3] = {static_cast<int>(hd), static_cast<int>(kvd), static_cast<int>(kvd)};
+  if ((rc = kvra::launch_linear(h, L->wqkv, nullptr, nullptr, outs, cols, 3, c, qkv_rows, L->hidden, st, L->head_dim, angles)) != KVRA_OK)
+    return rc;
   if ((rc = kvra_chunk_attn(q, k_cache, v_cache, prefix_len, c, L->n_q_heads, L->n_kv_heads, L->head_dim,
                             L->scale, attn, stream)) != KVRA_OK) return rc;
   if ((rc = kvra_linear(attn, L->wo, nullptr, x, x2, c, L->hidden, hd, stream)) != KVRA_OK) return rc;

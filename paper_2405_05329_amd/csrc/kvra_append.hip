@@ -1,7 +1,7 @@
 // kvra_append_kv: rotary embedding + KV-cache population of one chunk (App. C listing, cache
 // concatenation step; Sec. 4.3 contiguity).  HBM-bound streaming kernel: every byte of K, V
 // (and Q) is read once and written once with 128-bit accesses.
-#include "kvra_internal.h"
+#include "kvra_rope_device.h"
 
 namespace kvra {
 
@@ -32,38 +32,6 @@ __device__ __forceinline__ unsigned short f32_to_bf16_rne(float x) {
   if ((u & 0x7FFFFFFFu) > 0x7F800000u) return static_cast<unsigned short>((u >> 16) | 0x0040u);
   u += 0x7FFFu + ((u >> 16) & 1u);
   return static_cast<unsigned short>(u >> 16);
-}
-
-// cos and sin of phi, |phi| < 2^26, to about one unit in the last place of a double: phi - n pi/2 with pi/2 as a sum of two
-// doubles (n has at most 26 bits, each fused multiply-add rounds once), then the Taylor series on [-pi/4, pi/4], whose
-// first terms left out are below 2^-54.
-__device__ __forceinline__ void sincos_reduced(double phi, double* s, double* c) {
-  const double n = rint(phi * 0.63661977236758134308);
-  double r = fma(-n, 1.57079632679489655800e+00, phi);
-  r = fma(-n, 6.12323399573676603587e-17, r);
-  const double z = r * r;
-  double ps = 1.0 / 355687428096000.0, pc = -1.0 / 6402373705728000.0;   // 1/17!, -1/18!
-  ps = fma(ps, z, -1.0 / 1307674368000.0);
-  pc = fma(pc, z, 1.0 / 20922789888000.0);
-  ps = fma(ps, z, 1.0 / 6227020800.0);
-  pc = fma(pc, z, -1.0 / 87178291200.0);
-  ps = fma(ps, z, -1.0 / 39916800.0);
-  pc = fma(pc, z, 1.0 / 479001600.0);
-  ps = fma(ps, z, 1.0 / 362880.0);
-  pc = fma(pc, z, -1.0 / 3628800.0);
-  ps = fma(ps, z, -1.0 / 5040.0);
-  pc = fma(pc, z, 1.0 / 40320.0);
-  ps = fma(ps, z, 1.0 / 120.0);
-  pc = fma(pc, z, -1.0 / 720.0);
-  ps = fma(ps, z, -1.0 / 6.0);
-  pc = fma(pc, z, 1.0 / 24.0);
-  pc = fma(pc, z, -0.5);
-  ps = fma(ps * z, r, r);
-  pc = fma(pc, z, 1.0);
-  const int quadrant = static_cast<int>(n) & 3;
-  const double s0 = quadrant & 1 ? pc : ps, c0 = quadrant & 1 ? ps : pc;
-  *s = quadrant & 2 ? -s0 : s0;
-  *c = quadrant == 1 || quadrant == 2 ? -c0 : c0;
 }
 
 // One workgroup serves TOK consecutive tokens (TOK * D/2 <= 256): TOK * D/2 threads form cos/sin of
@@ -163,11 +131,7 @@ __global__ __launch_bounds__(256) void append_kv_kernel(AppendArgs a) {
 
   if (has_angle) {
     const double phi = static_cast<double>(a.prefix_len + tok0 + t_mine) * freq;
-    double s, c;
-    if (phi < 67108864.0) sincos_reduced(phi, &s, &c);
-    else sincos(phi, &s, &c);              // a rope base below 1
-    cs[t_mine][tid % HALF] = static_cast<float>(c);
-    sn[t_mine][tid % HALF] = static_cast<float>(s);
+    rope_angle(phi, &cs[t_mine][tid % HALF], &sn[t_mine][tid % HALF]);
   }
   __syncthreads();
 
@@ -194,6 +158,22 @@ __global__ __launch_bounds__(256) void append_kv_kernel(AppendArgs a) {
   for (int u = tid + 256 * AHEAD; u < v_total; u += 256) v_dst[u] = v_src[u];
 }
 
+const double* rope_frequencies(float rope_base, int head_dim) {
+  // a program calls with one base and head size: the powers (0.9 us of a 4 us call) are formed when either changes
+  struct Frequencies {
+    float base = 0.0f;
+    int head_dim = 0;
+    double inv[64] = {};
+  };
+  static thread_local Frequencies f;
+  if (rope_base > 0.0f && (f.base != rope_base || f.head_dim != head_dim)) {
+    for (int i = 0; i < head_dim / 2; ++i) f.inv[i] = std::pow(static_cast<double>(rope_base), -2.0 * i / head_dim);
+    f.base = rope_base;
+    f.head_dim = head_dim;
+  }
+  return f.inv;
+}
+
 int launch_append_kv(const void* k_in, const void* v_in, void* q_inout, void* k_cache, void* v_cache,
                      int64_t prefix_len, int64_t chunk_len, int n_q_heads, int n_kv_heads, int head_dim,
                      float rope_base, hipStream_t stream) {
@@ -208,19 +188,8 @@ int launch_append_kv(const void* k_in, const void* v_in, void* q_inout, void* k_
   a.n_q_heads = n_q_heads;
   a.n_kv_heads = n_kv_heads;
   a.use_rope = rope_base > 0.0f ? 1 : 0;
-  // a program calls with one base and head size: the powers (0.9 us of a 4 us call) are formed when either changes
-  struct Frequencies {
-    float base = 0.0f;
-    int head_dim = 0;
-    double inv[64] = {};
-  };
-  static thread_local Frequencies f;
-  if (a.use_rope && (f.base != rope_base || f.head_dim != head_dim)) {
-    for (int i = 0; i < head_dim / 2; ++i) f.inv[i] = std::pow(static_cast<double>(rope_base), -2.0 * i / head_dim);
-    f.base = rope_base;
-    f.head_dim = head_dim;
-  }
-  for (int i = 0; i < 64; ++i) a.inv_freq[i] = f.inv[i];   // (without rotation nothing reads them)
+  const double* const inv = rope_frequencies(rope_base, head_dim);   // (without rotation nothing reads them)
+  for (int i = 0; i < 64; ++i) a.inv_freq[i] = inv[i];
   // tokens per workgroup: the most that phase 1 can serve, halved until the grid holds about
   // eight workgroups per CU (256 CUs) or one token per workgroup is reached
   int tok = 256 / (head_dim / 2);

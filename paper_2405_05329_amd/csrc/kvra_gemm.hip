@@ -18,7 +18,7 @@
 // MFMA stream, where every wave already holds the operands of the next few MFMAs.
 // 8192^3: 974 -> 777 us (1416 TFLOP/s), 11584 x 12288 x 4096: 1010 -> 912 us; what remains is power: with the loads and
 // operand reads taken out the same loop is 20 % faster at the same MFMA count.
-#include "kvra_internal.h"
+#include "kvra_rope_device.h"
 
 #include <algorithm>
 #include <type_traits>
@@ -50,6 +50,11 @@ struct GemmArgs {
   int k;
   int tiles_n, tiles_m;
   int dual;
+  // Q/K/V projection that also rotates and appends (segments: Q, cache rows of K, cache rows of V): head size, else 0.  The
+  // weight rows are walked in blocks of GemmTile::ROPE_ROWS alternating between the lower and the upper half of a head.
+  int rope;
+  int rotated;             // output columns [0, rotated) are rotated (those of Q and K; 0: none)
+  const float* angles;     // [m][rope]: cos of a token's rope / 2 angles, then their sin
 };
 
 // Tile of a workgroup: TN weight rows x TM tokens, k in stages of TK through a ring of ST LDS slots;
@@ -59,6 +64,7 @@ struct GemmTile {
   static constexpr int TN = TN_, TM = TM_, TK = TK_, ST = ST_, WN = WN_, WM = WM_, WK = WK_;
   static constexpr bool WHOLE = WHOLE_;                    // operands of a whole stage are read ahead (see the kernel)
   static constexpr int DUAL_ROWS = TN / WN >= 64 ? 32 : 16;   // dual mode: rows of a weight that sit side by side in the tile
+  static constexpr int ROPE_ROWS = TN / WN % 64 == 0 ? 32 : 16;   // rope mode: rows of a half that sit side by side
   static constexpr int NW = WN * WM * WK, THREADS = 64 * NW;
   static constexpr int PER_SIMD = PER_SIMD_;               // waves per SIMD the register budget is cut for
   static constexpr int NB = TN / WN / 16, MB = TM / WM / 16;   // 16 x 16 blocks of a wave
@@ -105,7 +111,7 @@ __device__ __forceinline__ void gather_columns(const f32x4& lo, const f32x4& hi,
   }
 }
 
-template <class T>
+template <class T, bool ROPE>
 __global__ __launch_bounds__(T::THREADS, T::PER_SIMD) void linear_kernel(GemmArgs a) {
   constexpr int NB = T::NB, MB = T::MB, L = T::L, ST = T::ST, TK = T::TK, KPW = T::KPW, PR = T::PR;
   extern __shared__ u32x4 smem[];
@@ -146,6 +152,9 @@ __global__ __launch_bounds__(T::THREADS, T::PER_SIMD) void linear_kernel(GemmArg
                 "f(row) must not depend on which of a wave's loads it is");
   unsigned off[L];
   const __bf16* src[L];
+  // Rope mode with three units of 32 rows (16 of a lower half, 16 of an upper) to a wave: the second wave takes its last two
+  // units first, so that either has two that are neighbours in a head, and then one.
+  auto rope_unit = [](int u) -> int { return u < 3 ? u : u == 5 ? 3 : u + 1; };
   auto aim = [&](int t) {
     int n0, m0;
     place(t, &n0, &m0);
@@ -157,7 +166,12 @@ __global__ __launch_bounds__(T::THREADS, T::PER_SIMD) void linear_kernel(GemmArg
         const int first = min(n0 + idx * T::RPL, a.n - 1);   // uniform
         row = min(n0 + idx * T::RPL + ld_row, a.n - 1);
         src[i] = a.w;
-        if (a.dual) {                                        // blocks of rows alternate between the two weights
+        if (ROPE) {                                          // blocks of rows alternate between the halves of a head
+          constexpr int RR = T::ROPE_ROWS;
+          if constexpr (NB == 6) row = min(n0 + rope_unit(idx * T::RPL / 32) * 32 + idx * T::RPL % 32 + ld_row, a.n - 1);
+          const int in_head = row & (a.rope - 1);
+          row += (in_head / (2 * RR) * RR + (in_head / RR % 2) * (a.rope / 2) + in_head % RR) - in_head;
+        } else if (a.dual) {                                 // or between the two weights
           constexpr int DR = T::DUAL_ROWS;
           if ((first / DR) & 1) src[i] = a.w2;
           row = row / (2 * DR) * DR + row % DR;
@@ -388,7 +402,76 @@ __global__ __launch_bounds__(T::THREADS, T::PER_SIMD) void linear_kernel(GemmArg
       for (int e = 0; e < 8; ++e) b[e] = static_cast<__bf16>(v[e]);
       *reinterpret_cast<bf16x8*>(o) = b;
     };
-    if (a.dual) {
+    if constexpr (ROPE) {
+      // RB blocks of the lower half of a head, then the RB blocks of its upper half that they are rotated with.  First all
+      // blocks are rotated where they are, then all are stored: loads and stores of a wave are counted in one order, and
+      // angles asked for behind a store would be waited for as long as that store takes.  Stores cover whole 64-byte segments
+      // wherever a wave has them: in pieces of 32 the same tile costs 4.5 us more for 12288 columns of 1024 tokens (whole: 98
+      // us in place of 92 for the plain projection and 11 for the append launch that this saves).
+      constexpr int RB = T::ROPE_ROWS / 16;
+      constexpr int AH = T::PER_SIMD > 2 ? 1 : MB >= 8 ? 2 : MB % 4 == 0 ? 4 : MB % 3 == 0 ? 3 : MB;   // as registers allow
+      auto walk_of = [&](int nb) __attribute__((always_inline)) -> int {
+        if constexpr (NB == 6) return n0 + 32 * (nb < 4 ? 4 * wn + nb / 2 : 2 + wn);
+        return nw + 16 * nb;
+      };
+#pragma unroll
+      for (int nb = 0; nb < NB; nb += 2 * RB) {
+        const int walk = walk_of(nb), in_head = walk & (a.rope - 1);
+        if (walk - in_head >= a.rotated) continue;
+        const float* const angle = a.angles + (in_head >> 1) + 4 * kg;
+#pragma unroll
+        for (int m1 = 0; m1 < MB; m1 += AH) {
+          f32x4 c[AH][RB], sn[AH][RB];   // on their way together
+#pragma unroll
+          for (int u = 0; u < AH; ++u)
+#pragma unroll
+            for (int h = 0; h < RB; ++h) {
+              const float* const at = angle + static_cast<long long>(min(mw + 16 * (m1 + u), a.m - 1)) * a.rope + 16 * h;
+              c[u][h] = *reinterpret_cast<const f32x4*>(at);
+              sn[u][h] = *reinterpret_cast<const f32x4*>(at + a.rope / 2);
+            }
+#pragma unroll
+          for (int u = 0; u < AH; ++u)
+#pragma unroll
+            for (int h = 0; h < RB; ++h)
+#pragma unroll
+              for (int e = 0; e < 4; ++e) {
+                const float x0 = acc[nb + h][m1 + u][e], x1 = acc[nb + RB + h][m1 + u][e];
+                acc[nb + h][m1 + u][e] = fmaf(x0, c[u][h][e], -(x1 * sn[u][h][e]));
+                acc[nb + RB + h][m1 + u][e] = fmaf(x1, c[u][h][e], x0 * sn[u][h][e]);
+              }
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int nb = 0; nb < NB; nb += 4) {
+        const int walk = walk_of(nb), in_head = walk & (a.rope - 1), head = walk - in_head;
+        if (walk >= a.n) continue;
+        const int s = head < a.seg[0].end ? 0 : head < a.seg[1].end ? 1 : 2;
+        const int ld = a.seg[s].ld;
+        const bool two = nb + 4 <= NB;   // units; a single one leaves a lane 8 columns of the lower half or 8 of the upper
+        __bf16* const obase = a.seg[s].ptr + head - a.seg[s].first + (in_head >> 1) +
+                              (two ? lane_col : (kg & 1) * (a.rope / 2) + 8 * (kg >> 1));
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) {
+          const int tok = mw + 16 * mb;
+          __bf16* const o = obase + static_cast<long long>(tok) * ld;
+          float v[8], u[8];
+          if (two) {
+            constexpr int L1 = RB == 2 ? 1 : 2;          // where the second half of the lower columns sits
+            gather_columns(acc[nb][mb], acc[min(nb + L1, NB - 1)][mb], v);
+            gather_columns(acc[min(nb + 3 - L1, NB - 1)][mb], acc[min(nb + 3, NB - 1)][mb], u);
+            if (tok < a.m) {
+              store8(v, o);
+              store8(u, o + a.rope / 2);
+            }
+          } else {
+            gather_columns(acc[nb][mb], acc[nb + 1][mb], v);
+            if (tok < a.m) store8(v, o);
+          }
+        }
+      }
+    } else if (a.dual) {
       // blocks nb = 4 i, 4 i + 1 / 4 i + 2, 4 i + 3 are the gate / up rows of the same 32 output columns
       if constexpr (NB % 4 == 0) {
 #pragma unroll
@@ -474,8 +557,11 @@ __global__ __launch_bounds__(T::THREADS, T::PER_SIMD) void linear_kernel(GemmArg
 // rows as whole 1 KiB loads with fp32 multiply-adds on the vector ALU (29.1, and slower with every further token).
 constexpr int kRowsThreads = 512, kRowsWaves = 8, kRowsAhead = 8;
 
-template <bool DUAL>
+enum RowsKind { kRowsPlain, kRowsDual, kRowsRope };
+
+template <RowsKind KIND>
 __global__ __launch_bounds__(kRowsThreads, 2) void linear_rows_kernel(GemmArgs a) {
+  constexpr bool DUAL = KIND == kRowsDual, ROPE = KIND == kRowsRope;
   __shared__ f32x4 part[kRowsWaves][64];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -483,8 +569,10 @@ __global__ __launch_bounds__(kRowsThreads, 2) void linear_rows_kernel(GemmArgs a
   constexpr int COLS = DUAL ? 8 : 16;
   const int n0 = blockIdx.x * COLS;   // n is a multiple of 32 (of each weight)
   const __bf16* const weight = DUAL && r16 >= COLS ? a.w2 : a.w;
-  const char* const w = reinterpret_cast<const char*>(weight) +
-                        2 * (static_cast<long long>(n0 + r16 % COLS) * a.k + 8 * kg);
+  // rope: 8 rows of the lower half of a head, then the 8 of its upper half that they are rotated with
+  const int head = n0 & -a.rope, rope_col = (n0 - head) >> 1;   // (rope only)
+  const int row = ROPE ? head + rope_col + r16 % 8 + (r16 >= 8 ? a.rope / 2 : 0) : n0 + r16 % COLS;
+  const char* const w = reinterpret_cast<const char*>(weight) + 2 * (static_cast<long long>(row) * a.k + 8 * kg);
   const char* const x = reinterpret_cast<const char*>(a.x) +
                         2 * (static_cast<long long>(min(r16, a.m - 1)) * a.k + 8 * kg);
   f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -525,6 +613,23 @@ __global__ __launch_bounds__(kRowsThreads, 2) void linear_rows_kernel(GemmArgs a
     }
     if (kg >= 2 || r16 >= a.m) return;
     *reinterpret_cast<bf16x4*>(a.seg[0].ptr + static_cast<long long>(r16) * a.seg[0].ld + n0 + 4 * kg) = o;
+  } else if constexpr (ROPE) {
+    const int s = head < a.seg[0].end ? 0 : head < a.seg[1].end ? 1 : 2;
+    const int i = rope_col + 4 * (kg & 1);   // of the angles of this lane's columns
+    f32x4 other;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) other[e] = __shfl_xor(v[e], 32);   // the other half of the pairs
+    if (r16 >= a.m) return;
+    if (head < a.rotated) {
+      const float* const angle = a.angles + static_cast<long long>(r16) * a.rope + i;
+      const f32x4 c = *reinterpret_cast<const f32x4*>(angle), sn = *reinterpret_cast<const f32x4*>(angle + a.rope / 2);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = fmaf(v[e], c[e], (kg >= 2 ? other[e] : -other[e]) * sn[e]);
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o[e] = static_cast<__bf16>(v[e]);
+    *reinterpret_cast<bf16x4*>(a.seg[s].ptr + static_cast<long long>(r16) * a.seg[s].ld + head - a.seg[s].first + i +
+                               (kg >= 2 ? a.rope / 2 : 0)) = o;
   } else {
     if (r16 >= a.m) return;
     int s = 0;
@@ -551,12 +656,14 @@ int launch_tile(GemmArgs& a, hipStream_t stream) {
   const int per = (a.tiles_n * a.tiles_m + 7) / 8;
   constexpr int PER_CU = T::PER_SIMD * 4 / T::NW;
   const unsigned grid = 8u * static_cast<unsigned>(std::min(per, 32 * PER_CU));
-  return launch_kernel(linear_kernel<T>, dim3(grid), dim3(T::THREADS), a, stream, T::LDS);
+  if (a.rope != 0) return launch_kernel(linear_kernel<T, true>, dim3(grid), dim3(T::THREADS), a, stream, T::LDS);
+  return launch_kernel(linear_kernel<T, false>, dim3(grid), dim3(T::THREADS), a, stream, T::LDS);
 }
 
 int launch_rows(GemmArgs& a, hipStream_t stream) {
   const dim3 grid(static_cast<unsigned>(a.n / 16)), block(kRowsThreads);   // dual: a.n counts the rows of both weights
-  return launch_kernel(a.dual ? linear_rows_kernel<true> : linear_rows_kernel<false>, grid, block, a, stream);
+  return launch_kernel(a.dual ? linear_rows_kernel<kRowsDual> : a.rope != 0 ? linear_rows_kernel<kRowsRope> : linear_rows_kernel<kRowsPlain>,
+                       grid, block, a, stream);
 }
 
 // ---- which kernel a shape gets ----------------------------------------------------------------------
@@ -628,7 +735,7 @@ const TileChoice* choose_tile(const GemmArgs& a) {
 
 int launch_linear(const void* x, const void* w, const void* w2, const void* residual,
                   void* const* out, const int* seg_cols, int n_seg,
-                  int64_t m, int64_t n_out, int64_t k, hipStream_t stream) {
+                  int64_t m, int64_t n_out, int64_t k, hipStream_t stream, int rope, const float* angles) {
   GemmArgs a;
   a.x = static_cast<const __bf16*>(x);
   a.w = static_cast<const __bf16*>(w);
@@ -648,6 +755,9 @@ int launch_linear(const void* x, const void* w, const void* w2, const void* resi
     }
   }
   a.dual = w2 != nullptr ? 1 : 0;
+  a.rope = rope;
+  a.rotated = angles != nullptr ? seg_cols[0] + seg_cols[1] : 0;
+  a.angles = angles;
   a.m = static_cast<int>(m);
   a.n = static_cast<int>(a.dual ? 2 * n_out : n_out);
   a.k = static_cast<int>(k);
@@ -687,12 +797,27 @@ struct NormArgs {
   int hidden;
   float eps;
 };
+struct NormAngleArgs : NormArgs {
+  float* angles;           // [rows][head_dim]: cos of a token's head_dim / 2 angles, then their sin
+  int head_dim;
+  long long position;      // of the first row
+  double inv_freq[64];
+};
 
 constexpr int kNormThreads = 256;
 constexpr int kNormMaxPieces = 4;   // 16-byte pieces a thread keeps in registers: hidden <= 8192
 
-template <int PIECES>   // at most so many per thread
-__global__ __launch_bounds__(kNormThreads) void rms_norm_kernel(NormArgs a) {
+// The last wave of a row also forms the angles of its token for the projection that follows, while the row is on its way.
+__device__ __forceinline__ void norm_angles(const NormArgs&, int) {}
+__device__ __forceinline__ void norm_angles(const NormAngleArgs& a, int tid) {
+  const int i = tid - (kNormThreads - 64);
+  if (i < 0 || i >= a.head_dim / 2) return;
+  float* const row = a.angles + static_cast<long long>(blockIdx.x) * a.head_dim;
+  rope_angle(static_cast<double>(a.position + blockIdx.x) * a.inv_freq[i], row + i, row + a.head_dim / 2 + i);
+}
+
+template <int PIECES, class Args>   // at most so many per thread
+__global__ __launch_bounds__(kNormThreads) void rms_norm_kernel(Args a) {
   __shared__ float part[kNormThreads / 64];
   const int tid = threadIdx.x;
   const int pieces = a.hidden / 8;
@@ -708,6 +833,7 @@ __global__ __launch_bounds__(kNormThreads) void rms_norm_kernel(NormArgs a) {
       g[i] = gr[p];
     }
   }
+  norm_angles(a, tid);
 #pragma unroll
   for (int i = 0; i < PIECES; ++i) {
     if (tid + i * kNormThreads < pieces) {
@@ -739,8 +865,10 @@ __global__ __launch_bounds__(kNormThreads) void rms_norm_kernel(NormArgs a) {
   }
 }
 
-int launch_rms_norm(const void* x, const void* gain, void* y, int64_t rows, int hidden, float eps, hipStream_t stream) {
-  NormArgs a;
+namespace {
+
+template <class Args>
+int launch_norm(Args& a, const void* x, const void* gain, void* y, int64_t rows, int hidden, float eps, hipStream_t stream) {
   a.x = static_cast<const __bf16*>(x);
   a.gain = static_cast<const __bf16*>(gain);
   a.y = static_cast<__bf16*>(y);
@@ -749,9 +877,27 @@ int launch_rms_norm(const void* x, const void* gain, void* y, int64_t rows, int 
   a.eps = eps;
   const dim3 grid(static_cast<unsigned>(rows)), block(kNormThreads);
   const int per_thread = (hidden / 8 + kNormThreads - 1) / kNormThreads;
-  if (per_thread == 1) return launch_kernel(rms_norm_kernel<1>, grid, block, a, stream);
-  if (per_thread == 2) return launch_kernel(rms_norm_kernel<2>, grid, block, a, stream);
-  return launch_kernel(rms_norm_kernel<kNormMaxPieces>, grid, block, a, stream);
+  if (per_thread == 1) return launch_kernel(rms_norm_kernel<1, Args>, grid, block, a, stream);
+  if (per_thread == 2) return launch_kernel(rms_norm_kernel<2, Args>, grid, block, a, stream);
+  return launch_kernel(rms_norm_kernel<kNormMaxPieces, Args>, grid, block, a, stream);
+}
+
+}  // namespace
+
+int launch_rms_norm(const void* x, const void* gain, void* y, int64_t rows, int hidden, float eps, hipStream_t stream) {
+  NormArgs a;
+  return launch_norm(a, x, gain, y, rows, hidden, eps, stream);
+}
+
+int launch_rms_norm_angles(const void* x, const void* gain, void* y, int64_t rows, int hidden, float eps, int64_t position,
+                           int head_dim, float rope_base, float* angles, hipStream_t stream) {
+  NormAngleArgs a;
+  a.angles = angles;
+  a.head_dim = head_dim;
+  a.position = position;
+  const double* const inv = rope_frequencies(rope_base, head_dim);
+  for (int i = 0; i < 64; ++i) a.inv_freq[i] = inv[i];
+  return launch_norm(a, x, gain, y, rows, hidden, eps, stream);
 }
 
 int rms_norm_max_hidden() { return kNormThreads * kNormMaxPieces * 8; }

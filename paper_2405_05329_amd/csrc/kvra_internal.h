@@ -15,6 +15,9 @@ int launch_append_kv(const void* k_in, const void* v_in, void* q_inout, void* k_
                      int64_t prefix_len, int64_t chunk_len, int n_q_heads, int n_kv_heads, int head_dim,
                      float rope_base, hipStream_t stream);
 
+// base^(-2i/d), i < d/2, in fp64 (64 entries; zeros before the first base > 0): the calling thread's, until its next call.
+const double* rope_frequencies(float rope_base, int head_dim);
+
 int launch_chunk_attn(const void* q, const void* k_cache, const void* v_cache,
                       int64_t prefix_len, int64_t chunk_len, int n_q_heads, int n_kv_heads, int head_dim,
                       float scale, void* out, hipStream_t stream, bool static_scratch_only);
@@ -76,9 +79,11 @@ int list_chunk_attn_pieces(int64_t prefix_len, int64_t chunk_len, int n_q_heads,
 
 // out[m, n_out] = x[m, k] . w[n_out, k]^T (+ residual), or silu(x . w^T) * (x . w2^T) when w2 is given.
 // The n_out output columns are split over n_seg (1..3) dense matrices of seg_cols[s] columns each.
+// rope != 0 (three segments: Q, K, V): the head size; where angles are given, the columns of Q and K are rotated by them
+// on the way out ([m][rope]: cos of a token's rope / 2 angles, then their sin).
 int launch_linear(const void* x, const void* w, const void* w2, const void* residual,
                   void* const* out, const int* seg_cols, int n_seg,
-                  int64_t m, int64_t n_out, int64_t k, hipStream_t stream);
+                  int64_t m, int64_t n_out, int64_t k, hipStream_t stream, int rope = 0, const float* angles = nullptr);
 
 // Which kernel and tile such a launch gets (dual: with w2): weight rows (dual: of both weights) x tokens of a workgroup's tile,
 // depth of a k stage (0: the direct kernel for few tokens, which has none), tiles the busiest workgroup walks.
@@ -89,6 +94,9 @@ int linear_plan(int64_t m, int64_t n_out, int64_t k, bool dual, LinearPlan* plan
 
 int launch_rms_norm(const void* x, const void* gain, void* y, int64_t rows, int hidden, float eps,
                     hipStream_t stream);
+// The same, and the rotary angles of the rows' tokens (positions from `position` on) for launch_linear's `angles`.
+int launch_rms_norm_angles(const void* x, const void* gain, void* y, int64_t rows, int hidden, float eps, int64_t position,
+                           int head_dim, float rope_base, float* angles, hipStream_t stream);
 int rms_norm_max_hidden();
 
 // More than 64 KiB of dynamic LDS has to be granted per kernel and device.  A thread remembers what it has asked for (the
