@@ -266,20 +266,15 @@ extern "C" int kvra_layer_chunk(const kvra_layer* L, const void* x, void* y, voi
   const int64_t kvd = static_cast<int64_t>(L->n_kv_heads) * L->head_dim;
   // The projection rotates Q and K and puts K and V into their cache rows; the angles stand where an unrotated K and V would
   // have been: chunk_len * head_dim floats, at most the room of one KV head's K and V.
-  float* const angles = L->rope_base > 0.0f ? static_cast<float*>(k) : nullptr;
-  if (angles != nullptr)
-    rc = kvra::launch_rms_norm_angles(x, L->norm1, h, c, L->hidden, L->rms_eps, prefix_len, L->head_dim, L->rope_base, angles, st);
-  else
-    rc = kvra::launch_rms_norm(x, L->norm1, h, c, L->hidden, L->rms_eps, st);
-  if (rc != KVRA_OK) return rc;
   void* outs[3] = {q, static_cast<char*>(k_cache) + prefix_len * kvd * 2, static_cast<char*>(v_cache) + prefix_len * kvd * 2};
   const int cols[3] = {static_cast<int>(hd), static_cast<int>(kvd), static_cast<int>(kvd)};
-  if ((rc = kvra::launch_linear(h, L->wqkv, nullptr, nullptr, outs, cols, 3, c, qkv_rows, L->hidden, st, L->head_dim, angles)) != KVRA_OK)
+  if ((rc = kvra::launch_norm_qkv_append(x, L->norm1, L->rms_eps, h, static_cast<float*>(k), L->wqkv, outs, cols, prefix_len,
+                                         L->rope_base, L->head_dim, c, L->hidden, st)) != KVRA_OK)
     return rc;
   if ((rc = kvra_chunk_attn(q, k_cache, v_cache, prefix_len, c, L->n_q_heads, L->n_kv_heads, L->head_dim,
                             L->scale, attn, stream)) != KVRA_OK) return rc;
   if ((rc = kvra_linear(attn, L->wo, nullptr, x, x2, c, L->hidden, hd, stream)) != KVRA_OK) return rc;
-  if ((rc = kvra_rms_norm(x2, L->norm2, h, c, L->hidden, L->rms_eps, stream)) != KVRA_OK) return rc;
-  if ((rc = kvra_linear(h, L->w_gate, L->w_up, nullptr, act, c, L->ffn, L->hidden, stream)) != KVRA_OK) return rc;
+  if ((rc = kvra::launch_norm_swiglu(x2, L->norm2, L->rms_eps, h, L->w_gate, L->w_up, act, c, L->ffn, L->hidden, st)) != KVRA_OK)
+    return rc;
   return kvra_linear(act, L->w_down, nullptr, x2, y, c, L->hidden, L->ffn, stream);
 }

@@ -549,60 +549,105 @@ __global__ __launch_bounds__(T::THREADS, T::PER_SIMD) void linear_kernel(GemmArg
 }
 
 // Few tokens: a pass over the weights, bound by how fast they come from memory.  A workgroup owns 16 weight rows (SwiGLU: 8
-// columns, their gate rows and their up rows) and all (up to 16) tokens; its 8 waves share out k in chunks of 64, and both
+// columns, their gate rows and their up rows; with rotation: 8 rows of the lower half of a head and the 8 of its upper half that
+// they are rotated with) and all (up to 16) tokens; its waves share out k in chunks of 64, and both
 // operands go from global memory straight into MFMA fragments, since no wave needs what another one loads: no LDS and no
-// barrier until the sums of the eight shares meet at the end.  The loads of kRowsAhead chunks (of a 4096-deep row: all there
-// are) are in flight together.  Measured and not taken (1 token): the last chunks of a row in one go instead of one by one
-// (4096 x 11008: no difference); two sets of four chunks, one on its way while the other is multiplied (24.4 us against 22.1);
-// rows as whole 1 KiB loads with fp32 multiply-adds on the vector ALU (29.1, and slower with every further token).
-constexpr int kRowsThreads = 512, kRowsWaves = 8, kRowsAhead = 8;
-
+// barrier until the sums of the shares meet at the end.  Measured and not taken (1 token): the last chunks of a
+// row in one go instead of one by one (4096 x 11008: no difference); the loads of eight chunks held in flight by hand (22.2 us ->
+// 22.9), two sets of four or of two chunks in turn (24.8, 22.1; 12288 x 4096 19.5 -> 26, 23); lanes without a token asking for
+// nothing (no difference); rows as whole 1 KiB loads with fp32 multiply-adds on the vector ALU (29.1, and slower with every
+// further token).
+// Waves: 16 where a row holds at least four chunks for each of them, else 8 (one token, 8 -> 16 waves: 12288 x 4096 19.5 ->
+// 18.2 us, 5.5 TB/s; 11008 x 4096 SwiGLU 34.4 -> 32.1, 5.6; 4096 x 11008 22.2 -> 21.6; 2048 x 5632 10.0 -> 9.5; but 1024 x 2816
+// 5.1 -> 5.3, 2816 x 1024 SwiGLU 4.6 -> 4.8).
+// NORM: the tokens come before their RMSNorm, x * gain is what is multiplied, and since its factor 1 / rms belongs to a
+// token it is applied to the sums: the waves add up the squares of what they load anyway, and the norm launch and the
+// wait behind it go.  As many roundings as with a norm of its own (x * gain instead of x * gain / rms).  Few registers, so that
+// two workgroups of 16 waves share a CU: with four chunks in one go (128 registers) 1 token of the 4096-wide layer takes 158 us
+// instead of 141.  Not taken either: two blocks of rows per workgroup, which halves that work (+12 us), and persistent workgroups
+// that keep x * gain in registers (+25): one workgroup per CU in step with itself does not keep the memory busy.
 enum RowsKind { kRowsPlain, kRowsDual, kRowsRope };
 
-template <RowsKind KIND>
-__global__ __launch_bounds__(kRowsThreads, 2) void linear_rows_kernel(GemmArgs a) {
+struct NormedRowsArgs : GemmArgs {
+  const __bf16* gain;
+  float eps;
+  long long position;      // of the first token (rope)
+  double inv_freq[64];     // (rope)
+};
+
+template <RowsKind KIND, bool NORM, int WAVES>
+__global__ __launch_bounds__(64 * WAVES, 8) void linear_rows_kernel(std::conditional_t<NORM, NormedRowsArgs, GemmArgs> a) {
   constexpr bool DUAL = KIND == kRowsDual, ROPE = KIND == kRowsRope;
-  __shared__ f32x4 part[kRowsWaves][64];
+  constexpr int AHEAD = NORM ? 1 : 64 / WAVES;   // chunks of a wave in one go (64 / WAVES: all of a 4096-deep row)
+  static_assert(NORM || !ROPE, "the rotation is only wanted behind a norm");
+  __shared__ f32x4 part[WAVES][64];
+  __shared__ float squares[NORM ? WAVES : 1][64];
+  __shared__ float cs[ROPE ? 16 : 1][8], sn[ROPE ? 16 : 1][8];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r16 = lane & 15, kg = lane >> 4;
   constexpr int COLS = DUAL ? 8 : 16;
   const int n0 = blockIdx.x * COLS;   // n is a multiple of 32 (of each weight)
   const __bf16* const weight = DUAL && r16 >= COLS ? a.w2 : a.w;
-  // rope: 8 rows of the lower half of a head, then the 8 of its upper half that they are rotated with
   const int head = n0 & -a.rope, rope_col = (n0 - head) >> 1;   // (rope only)
   const int row = ROPE ? head + rope_col + r16 % 8 + (r16 >= 8 ? a.rope / 2 : 0) : n0 + r16 % COLS;
   const char* const w = reinterpret_cast<const char*>(weight) + 2 * (static_cast<long long>(row) * a.k + 8 * kg);
   const char* const x = reinterpret_cast<const char*>(a.x) +
                         2 * (static_cast<long long>(min(r16, a.m - 1)) * a.k + 8 * kg);
+  if constexpr (ROPE) {
+    // the angles of 8 frequencies for 16 tokens, by the last two waves
+    const int i = tid - 64 * (WAVES - 2), t = i >> 3;
+    if (i >= 0 && t < a.m && head < a.rotated)
+      rope_angle(static_cast<double>(a.position + t) * a.inv_freq[rope_col + (i & 7)], &cs[t][i & 7], &sn[t][i & 7]);
+  }
   f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+  float ss = 0.0f;
   const int chunks = a.k / 64;
   auto steps = [&](int c, auto count_tag) __attribute__((always_inline)) {
     constexpr int COUNT = decltype(count_tag)::value;
-    bf16x8 fw[COUNT][2], fx[COUNT][2];
+    bf16x8 fw[COUNT][2], fx[COUNT][2], fg[NORM ? COUNT : 1][2];
 #pragma unroll
     for (int u = 0; u < COUNT; ++u)
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
-        const long long at = (static_cast<long long>(c) + u * kRowsWaves) * 128 + h * 64;
+        const long long at = (static_cast<long long>(c) + u * WAVES) * 128 + h * 64;
         fw[u][h] = *reinterpret_cast<const bf16x8*>(w + at);
         fx[u][h] = *reinterpret_cast<const bf16x8*>(x + at);
+        if constexpr (NORM) fg[u][h] = *reinterpret_cast<const bf16x8*>(reinterpret_cast<const char*>(a.gain) + at + 16 * kg);
       }
 #pragma unroll
     for (int u = 0; u < COUNT; ++u)
 #pragma unroll
-      for (int h = 0; h < 2; ++h) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[u][h], fx[u][h], acc, 0, 0, 0);
+      for (int h = 0; h < 2; ++h) {
+        if constexpr (NORM) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const float f = static_cast<float>(fx[u][h][e]);
+            ss = fmaf(f, f, ss);
+            fx[u][h][e] = static_cast<__bf16>(f * static_cast<float>(fg[u][h][e]));
+          }
+        }
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[u][h], fx[u][h], acc, 0, 0, 0);
+      }
   };
   int c = wave;
-  for (; c + (kRowsAhead - 1) * kRowsWaves < chunks; c += kRowsAhead * kRowsWaves) steps(c, std::integral_constant<int, kRowsAhead>{});
-  for (; c < chunks; c += kRowsWaves) steps(c, std::integral_constant<int, 1>{});
+  for (; c + (AHEAD - 1) * WAVES < chunks; c += AHEAD * WAVES) steps(c, std::integral_constant<int, AHEAD>{});
+  for (; c < chunks; c += WAVES) steps(c, std::integral_constant<int, 1>{});
   part[wave][lane] = acc;
+  if constexpr (NORM) squares[wave][lane] = ss;
   __syncthreads();
   if (wave != 0) return;
   // rows 4 kg .. 4 kg + 3 of a token per lane
   f32x4 v = part[0][lane];
 #pragma unroll
-  for (int u = 1; u < kRowsWaves; ++u) v += part[u][lane];
+  for (int u = 1; u < WAVES; ++u) v += part[u][lane];
+  if constexpr (NORM) {
+#pragma unroll
+    for (int u = 1; u < WAVES; ++u) ss += squares[u][lane];
+    ss += __shfl_xor(ss, 16);
+    ss += __shfl_xor(ss, 32);
+    v *= 1.0f / sqrtf(ss / static_cast<float>(a.k) + a.eps);
+  }
   bf16x4 o;
   if constexpr (DUAL) {
     // the up rows of this lane's columns are 32 lanes on
@@ -615,20 +660,18 @@ __global__ __launch_bounds__(kRowsThreads, 2) void linear_rows_kernel(GemmArgs a
     *reinterpret_cast<bf16x4*>(a.seg[0].ptr + static_cast<long long>(r16) * a.seg[0].ld + n0 + 4 * kg) = o;
   } else if constexpr (ROPE) {
     const int s = head < a.seg[0].end ? 0 : head < a.seg[1].end ? 1 : 2;
-    const int i = rope_col + 4 * (kg & 1);   // of the angles of this lane's columns
+    const int i = 4 * (kg & 1);              // of the angles of this lane's columns
     f32x4 other;
 #pragma unroll
     for (int e = 0; e < 4; ++e) other[e] = __shfl_xor(v[e], 32);   // the other half of the pairs
     if (r16 >= a.m) return;
     if (head < a.rotated) {
-      const float* const angle = a.angles + static_cast<long long>(r16) * a.rope + i;
-      const f32x4 c = *reinterpret_cast<const f32x4*>(angle), sn = *reinterpret_cast<const f32x4*>(angle + a.rope / 2);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = fmaf(v[e], c[e], (kg >= 2 ? other[e] : -other[e]) * sn[e]);
+      for (int e = 0; e < 4; ++e) v[e] = fmaf(v[e], cs[r16][i + e], (kg >= 2 ? other[e] : -other[e]) * sn[r16][i + e]);
     }
 #pragma unroll
     for (int e = 0; e < 4; ++e) o[e] = static_cast<__bf16>(v[e]);
-    *reinterpret_cast<bf16x4*>(a.seg[s].ptr + static_cast<long long>(r16) * a.seg[s].ld + head - a.seg[s].first + i +
+    *reinterpret_cast<bf16x4*>(a.seg[s].ptr + static_cast<long long>(r16) * a.seg[s].ld + head - a.seg[s].first + rope_col + i +
                                (kg >= 2 ? a.rope / 2 : 0)) = o;
   } else {
     if (r16 >= a.m) return;
@@ -660,10 +703,11 @@ int launch_tile(GemmArgs& a, hipStream_t stream) {
   return launch_kernel(linear_kernel<T, false>, dim3(grid), dim3(T::THREADS), a, stream, T::LDS);
 }
 
-int launch_rows(GemmArgs& a, hipStream_t stream) {
-  const dim3 grid(static_cast<unsigned>(a.n / 16)), block(kRowsThreads);   // dual: a.n counts the rows of both weights
-  return launch_kernel(a.dual ? linear_rows_kernel<kRowsDual> : a.rope != 0 ? linear_rows_kernel<kRowsRope> : linear_rows_kernel<kRowsPlain>,
-                       grid, block, a, stream);
+template <RowsKind KIND, bool NORM, class Args>
+int launch_rows(Args& a, hipStream_t stream) {
+  const int blocks = a.n / 16;   // dual: a.n counts the rows of both weights
+  if (a.k >= 4096) return launch_kernel(linear_rows_kernel<KIND, NORM, 16>, dim3(blocks), dim3(1024), a, stream);
+  return launch_kernel(linear_rows_kernel<KIND, NORM, 8>, dim3(blocks), dim3(512), a, stream);
 }
 
 // ---- which kernel a shape gets ----------------------------------------------------------------------
@@ -717,6 +761,13 @@ float tile_cost(const TileChoice& c, const GemmArgs& a) {
 // 10.4 / 12.5 / 13.7 against 12.7 / 13.1 / 13.1; 2816 x 1024 at 1 / 16 4.9 / 6.0 against 6.2 / 6.2.
 bool takes_rows(const GemmArgs& a) { return a.m <= (a.n < 8192 ? 16 : a.dual && a.n >= 16384 ? 4 : 8); }
 
+// With the norm inside, the direct kernel also saves the norm's launch, and pays for it with a load, a conversion and the squares
+// for every weight fragment: whole layers behind 512 tokens, norm apart -> inside, 1 / 16 tokens: hidden 256 28.0 -> 21.1 / 28.1 ->
+// 22.3 us; 1024 29.5 -> 23.8 / 35.6 -> 29.3; 2048 47.4 -> 42.2 / 56.9 -> 53.3 (the append launch that is saved
+// included).  Wide SwiGLU layers are better off with the norm apart: 11008 x 4096 at 1 token 4.8 + 32.5 us against 39.6; and wide
+// projections beyond 8 tokens with the tiles (12288 x 4096 at 1 token inside: 23.4 us; apart 4.8 + 18.5, and 4.8 for the append).
+bool takes_normed_rows(const GemmArgs& a) { return a.dual ? a.n < 16384 && a.m <= 16 : a.m <= (a.n < 8192 ? 16 : 8); }
+
 const TileChoice* choose_tile(const GemmArgs& a) {
   const TileChoice* best = nullptr;
   float best_cost = 0.0f;
@@ -733,10 +784,11 @@ const TileChoice* choose_tile(const GemmArgs& a) {
 
 }  // namespace
 
-int launch_linear(const void* x, const void* w, const void* w2, const void* residual,
-                  void* const* out, const int* seg_cols, int n_seg,
-                  int64_t m, int64_t n_out, int64_t k, hipStream_t stream, int rope, const float* angles) {
-  GemmArgs a;
+namespace {
+
+void linear_args(const void* x, const void* w, const void* w2, const void* residual, void* const* out, const int* seg_cols,
+                 int n_seg, int64_t m, int64_t n_out, int64_t k, GemmArgs* args) {
+  GemmArgs& a = *args;
   a.x = static_cast<const __bf16*>(x);
   a.w = static_cast<const __bf16*>(w);
   a.w2 = static_cast<const __bf16*>(w2);
@@ -755,14 +807,62 @@ int launch_linear(const void* x, const void* w, const void* w2, const void* resi
     }
   }
   a.dual = w2 != nullptr ? 1 : 0;
-  a.rope = rope;
-  a.rotated = angles != nullptr ? seg_cols[0] + seg_cols[1] : 0;
-  a.angles = angles;
+  a.rope = 0;
+  a.rotated = 0;
+  a.angles = nullptr;
   a.m = static_cast<int>(m);
   a.n = static_cast<int>(a.dual ? 2 * n_out : n_out);
   a.k = static_cast<int>(k);
-  if (takes_rows(a)) return launch_rows(a, stream);
+}
+
+}  // namespace
+
+int launch_linear(const void* x, const void* w, const void* w2, const void* residual,
+                  void* const* out, const int* seg_cols, int n_seg,
+                  int64_t m, int64_t n_out, int64_t k, hipStream_t stream) {
+  GemmArgs a;
+  linear_args(x, w, w2, residual, out, seg_cols, n_seg, m, n_out, k, &a);
+  if (takes_rows(a)) return a.dual ? launch_rows<kRowsDual, false>(a, stream) : launch_rows<kRowsPlain, false>(a, stream);
   return choose_tile(a)->launch(a, stream);
+}
+
+int launch_norm_qkv_append(const void* x, const void* gain, float eps, void* h, float* angles, const void* wqkv, void* const* out,
+                           const int* seg_cols, int64_t position, float rope_base, int head_dim, int64_t m, int64_t k,
+                           hipStream_t stream) {
+  NormedRowsArgs a;
+  linear_args(x, wqkv, nullptr, nullptr, out, seg_cols, 3, m, static_cast<int64_t>(seg_cols[0]) + seg_cols[1] + seg_cols[2], k, &a);
+  const bool rotate = rope_base > 0.0f;
+  a.rope = head_dim;
+  a.rotated = rotate ? seg_cols[0] + seg_cols[1] : 0;
+  if (takes_normed_rows(a)) {
+    a.gain = static_cast<const __bf16*>(gain);
+    a.eps = eps;
+    a.position = position;
+    const double* const inv = rope_frequencies(rope_base, head_dim);
+    for (int i = 0; i < 64; ++i) a.inv_freq[i] = inv[i];
+    return launch_rows<kRowsRope, true>(a, stream);
+  }
+  const int rc = rotate ? launch_rms_norm_angles(x, gain, h, m, static_cast<int>(k), eps, position, head_dim, rope_base, angles, stream)
+                        : launch_rms_norm(x, gain, h, m, static_cast<int>(k), eps, stream);
+  if (rc != KVRA_OK) return rc;
+  a.x = static_cast<const __bf16*>(h);
+  a.angles = angles;
+  return choose_tile(a)->launch(a, stream);
+}
+
+int launch_norm_swiglu(const void* x, const void* gain, float eps, void* h, const void* w_gate, const void* w_up, void* out,
+                       int64_t m, int64_t n_out, int64_t k, hipStream_t stream) {
+  NormedRowsArgs a;
+  const int cols = static_cast<int>(n_out);
+  linear_args(x, w_gate, w_up, nullptr, &out, &cols, 1, m, n_out, k, &a);
+  if (takes_normed_rows(a)) {
+    a.gain = static_cast<const __bf16*>(gain);
+    a.eps = eps;
+    return launch_rows<kRowsDual, true>(a, stream);
+  }
+  const int rc = launch_rms_norm(x, gain, h, m, static_cast<int>(k), eps, stream);
+  if (rc != KVRA_OK) return rc;
+  return launch_linear(h, w_gate, w_up, nullptr, &out, &cols, 1, m, n_out, k, stream);
 }
 
 int linear_plan(int64_t m, int64_t n_out, int64_t k, bool dual, LinearPlan* plan) {

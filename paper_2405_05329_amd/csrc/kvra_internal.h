@@ -79,11 +79,18 @@ int list_chunk_attn_pieces(int64_t prefix_len, int64_t chunk_len, int n_q_heads,
 
 // out[m, n_out] = x[m, k] . w[n_out, k]^T (+ residual), or silu(x . w^T) * (x . w2^T) when w2 is given.
 // The n_out output columns are split over n_seg (1..3) dense matrices of seg_cols[s] columns each.
-// rope != 0 (three segments: Q, K, V): the head size; where angles are given, the columns of Q and K are rotated by them
-// on the way out ([m][rope]: cos of a token's rope / 2 angles, then their sin).
 int launch_linear(const void* x, const void* w, const void* w2, const void* residual,
                   void* const* out, const int* seg_cols, int n_seg,
-                  int64_t m, int64_t n_out, int64_t k, hipStream_t stream, int rope = 0, const float* angles = nullptr);
+                  int64_t m, int64_t n_out, int64_t k, hipStream_t stream);
+// The first half of a layer's attention block: norm, projection onto `out` (Q, rows of the K cache, rows of the V cache), Q and
+// K rotated (rope_base > 0) for positions from `position` on.  h [m, k] and angles [m][head_dim] (cos of a token's head_dim / 2
+// angles, then their sin) are workspace that may or may not be used.
+int launch_norm_qkv_append(const void* x, const void* gain, float eps, void* h, float* angles, const void* wqkv, void* const* out,
+                           const int* seg_cols, int64_t position, float rope_base, int head_dim, int64_t m, int64_t k,
+                           hipStream_t stream);
+// Norm, then silu(. w_gate^T) * (. w_up^T); h [m, k] as above.
+int launch_norm_swiglu(const void* x, const void* gain, float eps, void* h, const void* w_gate, const void* w_up, void* out,
+                       int64_t m, int64_t n_out, int64_t k, hipStream_t stream);
 
 // Which kernel and tile such a launch gets (dual: with w2): weight rows (dual: of both weights) x tokens of a workgroup's tile,
 // depth of a k stage (0: the direct kernel for few tokens, which has none), tiles the busiest workgroup walks.
@@ -94,7 +101,7 @@ int linear_plan(int64_t m, int64_t n_out, int64_t k, bool dual, LinearPlan* plan
 
 int launch_rms_norm(const void* x, const void* gain, void* y, int64_t rows, int hidden, float eps,
                     hipStream_t stream);
-// The same, and the rotary angles of the rows' tokens (positions from `position` on) for launch_linear's `angles`.
+// The same, and the rotary angles of the rows' tokens (positions from `position` on) as launch_norm_qkv_append has them.
 int launch_rms_norm_angles(const void* x, const void* gain, void* y, int64_t rows, int hidden, float eps, int64_t position,
                            int head_dim, float rope_base, float* angles, hipStream_t stream);
 int rms_norm_max_hidden();

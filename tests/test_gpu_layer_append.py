@@ -1,5 +1,5 @@
 """The projection that rotates and appends on its way out (inside kvra_layer_chunk): every tile shape of the linear kernel and
-the kernel for few tokens, both head sizes, with and without rotation, against the public operators called one by one.
+the kernel for few tokens (which takes in the norm as well; with 8 and 16 waves), both head sizes, with and without rotation, against the public operators called one by one.
 
 Bars.  Both sides see the same inputs; they differ where a tensor is rounded to bf16 on one side and not on the other, or
 before and after another factor.  rho = 1.66e-3 is the root mean square relative rounding error of bf16.  V: two roundings of
@@ -22,6 +22,7 @@ def _rel(got, want):
 
 @pytest.mark.parametrize("m,H,Hkv,d,hidden,tile", [
     (1, 1, 1, 64, 384, (16, 16, 0)), (7, 6, 2, 128, 128, (16, 16, 0)), (16, 71, 1, 64, 192, (16, 16, 0)),
+    (1, 3, 1, 64, 4160, (16, 16, 0)), (16, 1, 1, 128, 4096, (16, 16, 0)), (8, 40, 40, 128, 64, (16, 16, 0)),
     (17, 1, 1, 64, 384, (32, 32, 128)), (17, 1, 1, 128, 128, (32, 32, 128)),
     (65, 35, 5, 64, 128, (32, 64, 128)), (33, 25, 5, 128, 128, (32, 64, 128)),
     (17, 1, 1, 64, 192, (64, 64, 64)), (17, 1, 1, 128, 320, (64, 64, 64)),
