@@ -560,12 +560,14 @@ __global__ __launch_bounds__(T::THREADS, T::PER_SIMD) void linear_kernel(GemmArg
 // Waves: 16 where a row holds at least four chunks for each of them, else 8 (one token, 8 -> 16 waves: 12288 x 4096 19.5 ->
 // 18.2 us, 5.5 TB/s; 11008 x 4096 SwiGLU 34.4 -> 32.1, 5.6; 4096 x 11008 22.2 -> 21.6; 2048 x 5632 10.0 -> 9.5; but 1024 x 2816
 // 5.1 -> 5.3, 2816 x 1024 SwiGLU 4.6 -> 4.8).
-// NORM: the tokens come before their RMSNorm, x * gain is what is multiplied, and since its factor 1 / rms belongs to a
-// token it is applied to the sums: the waves add up the squares of what they load anyway, and the norm launch and the
-// wait behind it go.  As many roundings as with a norm of its own (x * gain instead of x * gain / rms).  Few registers, so that
+// NORM: the tokens come before their RMSNorm; the waves add up the squares of the chunks they multiply anyway, and the norm launch
+// and the wait behind it go.  Up to 16 tokens x * gain is what is multiplied, and the factor 1 / rms, which belongs to a token, is
+// applied to the sums: as many roundings as with a norm of its own (x * gain instead of x * gain / rms).  Few registers, so that
 // two workgroups of 16 waves share a CU: with four chunks in one go (128 registers) 1 token of the 4096-wide layer takes 158 us
 // instead of 141.  Not taken either: two blocks of rows per workgroup, which halves that work (+12 us), and persistent workgroups
-// that keep x * gain in registers (+25): one workgroup per CU in step with itself does not keep the memory busy.
+// that keep the tokens in registers (+25): one workgroup per CU in step with itself does not keep the memory busy.
+// Beyond 16 tokens (TB = 2) the waves meet for the sums first and multiply what the norm launch would have stored, so that a row
+// is rounded where it has always been (the meeting costs 1.2 us of a 25 us layer).
 enum RowsKind { kRowsPlain, kRowsDual, kRowsRope };
 
 struct NormedRowsArgs : GemmArgs {
@@ -575,78 +577,178 @@ struct NormedRowsArgs : GemmArgs {
   double inv_freq[64];     // (rope)
 };
 
-template <RowsKind KIND, bool NORM, int WAVES>
-__global__ __launch_bounds__(64 * WAVES, 8) void linear_rows_kernel(std::conditional_t<NORM, NormedRowsArgs, GemmArgs> a) {
+template <RowsKind KIND, bool NORM, int WAVES, int RB, int TB>
+__global__ __launch_bounds__(64 * WAVES, NORM ? (TB > 1 ? 4 : 8) : WAVES / 4) void linear_rows_kernel(std::conditional_t<NORM, NormedRowsArgs, GemmArgs> a) {
   constexpr bool DUAL = KIND == kRowsDual, ROPE = KIND == kRowsRope;
-  constexpr int AHEAD = NORM ? 1 : 64 / WAVES;   // chunks of a wave in one go (64 / WAVES: all of a 4096-deep row)
   static_assert(NORM || !ROPE, "the rotation is only wanted behind a norm");
-  __shared__ f32x4 part[WAVES][64];
-  __shared__ float squares[NORM ? WAVES : 1][64];
-  __shared__ float cs[ROPE ? 16 : 1][8], sn[ROPE ? 16 : 1][8];
+  static_assert(RB * TB <= WAVES && (!ROPE || 2 * RB * TB <= WAVES), "a wave per block at the end, and per half of its angles");
+  __shared__ f32x4 part[RB * TB][WAVES][64];
+  __shared__ float squares[NORM ? TB : 1][NORM ? WAVES : 1][64];
+  __shared__ float cs[ROPE ? 16 * TB : 1][8 * RB], sn[ROPE ? 16 * TB : 1][8 * RB];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r16 = lane & 15, kg = lane >> 4;
   constexpr int COLS = DUAL ? 8 : 16;
-  const int n0 = blockIdx.x * COLS;   // n is a multiple of 32 (of each weight)
+  const int first = blockIdx.x * (COLS * RB), m0 = blockIdx.y * (16 * TB);   // n is a multiple of 32 (of each weight)
   const __bf16* const weight = DUAL && r16 >= COLS ? a.w2 : a.w;
-  const int head = n0 & -a.rope, rope_col = (n0 - head) >> 1;   // (rope only)
-  const int row = ROPE ? head + rope_col + r16 % 8 + (r16 >= 8 ? a.rope / 2 : 0) : n0 + r16 % COLS;
+  const int head = first & -a.rope, rope_col = (first - head) >> 1;   // (rope only)
+  const int row = ROPE ? head + rope_col + r16 % 8 + (r16 >= 8 ? a.rope / 2 : 0) : first + r16 % COLS;
   const char* const w = reinterpret_cast<const char*>(weight) + 2 * (static_cast<long long>(row) * a.k + 8 * kg);
-  const char* const x = reinterpret_cast<const char*>(a.x) +
-                        2 * (static_cast<long long>(min(r16, a.m - 1)) * a.k + 8 * kg);
+  const long long w_step = 2ll * (ROPE || DUAL ? 8 : 16) * a.k;   // from a block of rows to the next
+  const char* x[TB];
+#pragma unroll
+  for (int t = 0; t < TB; ++t)
+    x[t] = reinterpret_cast<const char*>(a.x) + 2 * (static_cast<long long>(min(m0 + 16 * t + r16, a.m - 1)) * a.k + 8 * kg);
   if constexpr (ROPE) {
-    // the angles of 8 frequencies for 16 tokens, by the last two waves
-    const int i = tid - 64 * (WAVES - 2), t = i >> 3;
-    if (i >= 0 && t < a.m && head < a.rotated)
-      rope_angle(static_cast<double>(a.position + t) * a.inv_freq[rope_col + (i & 7)], &cs[t][i & 7], &sn[t][i & 7]);
+    // the angles of 8 RB frequencies for 16 TB tokens, by the last waves
+    const int i = tid - 64 * (WAVES - 2 * RB * TB), t = i / (8 * RB), f = i % (8 * RB);
+    if (i >= 0 && m0 + t < a.m && head < a.rotated)
+      rope_angle(static_cast<double>(a.position + m0 + t) * a.inv_freq[rope_col + f], &cs[t][f], &sn[t][f]);
   }
-  f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-  float ss = 0.0f;
+  f32x4 acc[RB][TB];
+#pragma unroll
+  for (int b = 0; b < RB; ++b)
+#pragma unroll
+    for (int t = 0; t < TB; ++t) acc[b][t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
   const int chunks = a.k / 64;
-  auto steps = [&](int c, auto count_tag) __attribute__((always_inline)) {
-    constexpr int COUNT = decltype(count_tag)::value;
-    bf16x8 fw[COUNT][2], fx[COUNT][2], fg[NORM ? COUNT : 1][2];
+  auto load_w = [&](bf16x8 (&f)[2][RB], int c) __attribute__((always_inline)) {
 #pragma unroll
-    for (int u = 0; u < COUNT; ++u)
+    for (int h = 0; h < 2; ++h)
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const long long at = (static_cast<long long>(c) + u * WAVES) * 128 + h * 64;
-        fw[u][h] = *reinterpret_cast<const bf16x8*>(w + at);
-        fx[u][h] = *reinterpret_cast<const bf16x8*>(x + at);
-        if constexpr (NORM) fg[u][h] = *reinterpret_cast<const bf16x8*>(reinterpret_cast<const char*>(a.gain) + at + 16 * kg);
-      }
-#pragma unroll
-    for (int u = 0; u < COUNT; ++u)
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        if constexpr (NORM) {
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            const float f = static_cast<float>(fx[u][h][e]);
-            ss = fmaf(f, f, ss);
-            fx[u][h][e] = static_cast<__bf16>(f * static_cast<float>(fg[u][h][e]));
-          }
-        }
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[u][h], fx[u][h], acc, 0, 0, 0);
-      }
+      for (int b = 0; b < RB; ++b) f[h][b] = *reinterpret_cast<const bf16x8*>(w + b * w_step + 128ll * c + 64 * h);
   };
-  int c = wave;
-  for (; c + (AHEAD - 1) * WAVES < chunks; c += AHEAD * WAVES) steps(c, std::integral_constant<int, AHEAD>{});
-  for (; c < chunks; c += WAVES) steps(c, std::integral_constant<int, 1>{});
-  part[wave][lane] = acc;
-  if constexpr (NORM) squares[wave][lane] = ss;
+  auto load_x = [&](bf16x8 (&f)[2][TB], int c) __attribute__((always_inline)) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int t = 0; t < TB; ++t) f[h][t] = *reinterpret_cast<const bf16x8*>(x[t] + 128ll * c + 64 * h);
+  };
+  auto multiply = [&](const bf16x8 (&fw)[2][RB], const bf16x8 (&fx)[2][TB]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int t = 0; t < TB; ++t)
+#pragma unroll
+        for (int b = 0; b < RB; ++b) acc[b][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[h][b], fx[h][t], acc[b][t], 0, 0, 0);
+  };
+  const char* gain_at = nullptr;
+  if constexpr (NORM) gain_at = reinterpret_cast<const char*>(a.gain) + 16 * kg;
+  auto load_gain = [&](bf16x8 (&f)[2], int c) __attribute__((always_inline)) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) f[h] = *reinterpret_cast<const bf16x8*>(gain_at + 128ll * c + 64 * h);
+  };
+  float ss[TB];
+#pragma unroll
+  for (int t = 0; t < TB; ++t) ss[t] = 0.0f;
+  auto squared = [&](const bf16x8 (&f)[2][TB]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int t = 0; t < TB; ++t)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) ss[t] = fmaf(static_cast<float>(f[h][t][e]), static_cast<float>(f[h][t][e]), ss[t]);
+  };
+  auto scaled = [&](bf16x8 (&f)[2][TB], const float (&rinv)[TB], const bf16x8 (&gain)[2]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int t = 0; t < TB; ++t)
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          f[h][t][e] = static_cast<__bf16>(static_cast<float>(f[h][t][e]) * rinv[t] * static_cast<float>(gain[h][e]));
+  };
+  if constexpr (NORM && TB == 1) {
+    for (int c = wave; c < chunks; c += WAVES) {
+      bf16x8 fw[2][RB], fx[2][TB], fg[2];
+      load_w(fw, c);
+      load_x(fx, c);
+      load_gain(fg, c);
+      squared(fx);
+      scaled(fx, {1.0f}, fg);
+      multiply(fw, fx);
+    }
+    squares[0][wave][lane] = ss[0];
+  } else if constexpr (NORM) {
+    // first the squares of all chunks, of which the first KEEP stay in registers, then the products
+    constexpr int KEEP = 2;
+    bf16x8 kw[KEEP][2][RB], kx[KEEP][2][TB], kgain[KEEP][2];
+#pragma unroll
+    for (int u = 0; u < KEEP; ++u)
+      if (wave + u * WAVES < chunks) {
+        load_x(kx[u], wave + u * WAVES);
+        load_w(kw[u], wave + u * WAVES);
+        load_gain(kgain[u], wave + u * WAVES);
+      }
+#pragma unroll
+    for (int u = 0; u < KEEP; ++u)
+      if (wave + u * WAVES < chunks) squared(kx[u]);
+    for (int c = wave + KEEP * WAVES; c < chunks; c += WAVES) {
+      bf16x8 fx[2][TB];
+      load_x(fx, c);
+      squared(fx);
+    }
+#pragma unroll
+    for (int t = 0; t < TB; ++t) squares[t][wave][lane] = ss[t];
+    __syncthreads();
+    float rinv[TB];
+#pragma unroll
+    for (int t = 0; t < TB; ++t) {
+      float sum = 0.0f;
+#pragma unroll
+      for (int u = 0; u < WAVES; ++u) sum += squares[t][u][lane];
+      sum += __shfl_xor(sum, 16);
+      sum += __shfl_xor(sum, 32);
+      rinv[t] = 1.0f / sqrtf(sum / static_cast<float>(a.k) + a.eps);
+    }
+#pragma unroll
+    for (int u = 0; u < KEEP; ++u)
+      if (wave + u * WAVES < chunks) {
+        scaled(kx[u], rinv, kgain[u]);
+        multiply(kw[u], kx[u]);
+      }
+    for (int c = wave + KEEP * WAVES; c < chunks; c += WAVES) {
+      bf16x8 fw[2][RB], fx[2][TB], fg[2];
+      load_w(fw, c);
+      load_x(fx, c);
+      load_gain(fg, c);
+      scaled(fx, rinv, fg);
+      multiply(fw, fx);
+    }
+  } else {
+    auto steps = [&](int c, auto count_tag) __attribute__((always_inline)) {
+      constexpr int COUNT = decltype(count_tag)::value;
+      bf16x8 fw[COUNT][2][RB], fx[COUNT][2][TB];
+#pragma unroll
+      for (int u = 0; u < COUNT; ++u) {
+        load_w(fw[u], c + u * WAVES);
+        load_x(fx[u], c + u * WAVES);
+      }
+#pragma unroll
+      for (int u = 0; u < COUNT; ++u) multiply(fw[u], fx[u]);
+    };
+    constexpr int AHEAD = 64 / WAVES;   // chunks of a wave in one go: all of a 4096-deep row
+    int c = wave;
+    for (; c + (AHEAD - 1) * WAVES < chunks; c += AHEAD * WAVES) steps(c, std::integral_constant<int, AHEAD>{});
+    for (; c < chunks; c += WAVES) steps(c, std::integral_constant<int, 1>{});
+  }
+#pragma unroll
+  for (int b = 0; b < RB; ++b)
+#pragma unroll
+    for (int t = 0; t < TB; ++t) part[b * TB + t][wave][lane] = acc[b][t];
   __syncthreads();
-  if (wave != 0) return;
-  // rows 4 kg .. 4 kg + 3 of a token per lane
-  f32x4 v = part[0][lane];
+  if (wave >= RB * TB) return;
+  // a block per wave, of it rows 4 kg .. 4 kg + 3 of a token per lane
+  const int b = wave / TB, t = wave % TB, n0 = first + b * COLS, tok = m0 + 16 * t + r16;
+  f32x4 v = part[wave][0][lane];
 #pragma unroll
-  for (int u = 1; u < WAVES; ++u) v += part[u][lane];
-  if constexpr (NORM) {
+  for (int u = 1; u < WAVES; ++u) v += part[wave][u][lane];
+  if constexpr (NORM && TB == 1) {
+    float sum = 0.0f;
 #pragma unroll
-    for (int u = 1; u < WAVES; ++u) ss += squares[u][lane];
-    ss += __shfl_xor(ss, 16);
-    ss += __shfl_xor(ss, 32);
-    v *= 1.0f / sqrtf(ss / static_cast<float>(a.k) + a.eps);
+    for (int u = 0; u < WAVES; ++u) sum += squares[0][u][lane];
+    sum += __shfl_xor(sum, 16);
+    sum += __shfl_xor(sum, 32);
+    v *= 1.0f / sqrtf(sum / static_cast<float>(a.k) + a.eps);
   }
   bf16x4 o;
   if constexpr (DUAL) {
@@ -656,29 +758,29 @@ __global__ __launch_bounds__(64 * WAVES, 8) void linear_rows_kernel(std::conditi
       const float g = v[e], u = __shfl_xor(v[e], 32);
       o[e] = static_cast<__bf16>(g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)) * u);
     }
-    if (kg >= 2 || r16 >= a.m) return;
-    *reinterpret_cast<bf16x4*>(a.seg[0].ptr + static_cast<long long>(r16) * a.seg[0].ld + n0 + 4 * kg) = o;
+    if (kg >= 2 || tok >= a.m) return;
+    *reinterpret_cast<bf16x4*>(a.seg[0].ptr + static_cast<long long>(tok) * a.seg[0].ld + n0 + 4 * kg) = o;
   } else if constexpr (ROPE) {
     const int s = head < a.seg[0].end ? 0 : head < a.seg[1].end ? 1 : 2;
-    const int i = 4 * (kg & 1);              // of the angles of this lane's columns
+    const int i = 8 * b + 4 * (kg & 1);      // of the angles of this lane's columns
     f32x4 other;
 #pragma unroll
     for (int e = 0; e < 4; ++e) other[e] = __shfl_xor(v[e], 32);   // the other half of the pairs
-    if (r16 >= a.m) return;
+    if (tok >= a.m) return;
     if (head < a.rotated) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = fmaf(v[e], cs[r16][i + e], (kg >= 2 ? other[e] : -other[e]) * sn[r16][i + e]);
+      for (int e = 0; e < 4; ++e) v[e] = fmaf(v[e], cs[16 * t + r16][i + e], (kg >= 2 ? other[e] : -other[e]) * sn[16 * t + r16][i + e]);
     }
 #pragma unroll
     for (int e = 0; e < 4; ++e) o[e] = static_cast<__bf16>(v[e]);
-    *reinterpret_cast<bf16x4*>(a.seg[s].ptr + static_cast<long long>(r16) * a.seg[s].ld + head - a.seg[s].first + rope_col + i +
+    *reinterpret_cast<bf16x4*>(a.seg[s].ptr + static_cast<long long>(tok) * a.seg[s].ld + head - a.seg[s].first + rope_col + i +
                                (kg >= 2 ? a.rope / 2 : 0)) = o;
   } else {
-    if (r16 >= a.m) return;
+    if (tok >= a.m) return;
     int s = 0;
     if (a.n_seg > 1 && n0 >= a.seg[0].end) s = 1;
     if (a.n_seg > 2 && n0 >= a.seg[1].end) s = 2;
-    const long long at = static_cast<long long>(r16) * a.seg[s].ld + n0 - a.seg[s].first + 4 * kg;
+    const long long at = static_cast<long long>(tok) * a.seg[s].ld + n0 - a.seg[s].first + 4 * kg;
     if (a.res != nullptr) {
       const bf16x4 r = *reinterpret_cast<const bf16x4*>(a.res + at);
 #pragma unroll
@@ -705,9 +807,16 @@ int launch_tile(GemmArgs& a, hipStream_t stream) {
 
 template <RowsKind KIND, bool NORM, class Args>
 int launch_rows(Args& a, hipStream_t stream) {
-  const int blocks = a.n / 16;   // dual: a.n counts the rows of both weights
-  if (a.k >= 4096) return launch_kernel(linear_rows_kernel<KIND, NORM, 16>, dim3(blocks), dim3(1024), a, stream);
-  return launch_kernel(linear_rows_kernel<KIND, NORM, 8>, dim3(blocks), dim3(512), a, stream);
+  const unsigned blocks = static_cast<unsigned>(a.n / 16);   // dual: a.n counts the rows of both weights
+  if constexpr (NORM || KIND == kRowsPlain) {
+    if (a.m > 16) {
+      const dim3 grid(blocks / 2, static_cast<unsigned>((a.m + 31) / 32));
+      if (a.k <= (NORM ? 1024 : 512)) return launch_kernel(linear_rows_kernel<KIND, NORM, 8, 2, 2>, grid, dim3(512), a, stream);
+      return launch_kernel(linear_rows_kernel<KIND, NORM, 16, 2, 2>, grid, dim3(1024), a, stream);
+    }
+  }
+  if (a.k >= 4096) return launch_kernel(linear_rows_kernel<KIND, NORM, 16, 1, 1>, dim3(blocks), dim3(1024), a, stream);
+  return launch_kernel(linear_rows_kernel<KIND, NORM, 8, 1, 1>, dim3(blocks), dim3(512), a, stream);
 }
 
 // ---- which kernel a shape gets ----------------------------------------------------------------------
@@ -759,14 +868,31 @@ float tile_cost(const TileChoice& c, const GemmArgs& a) {
 // SwiGLU reads more rows per column and gives way to the tiles at 4 tokens where there are 16384 rows or more: n x k =
 // 11008 x 4096 at 1 / 4 / 8 tokens 34.7 / 38.3 / 43.3 us (5.2 TB/s at 1) against 41.2 / 41.2 / 41.5; 5632 x 2048 at 1 / 8 / 12
 // 10.4 / 12.5 / 13.7 against 12.7 / 13.1 / 13.1; 2816 x 1024 at 1 / 16 4.9 / 6.0 against 6.2 / 6.2.
-bool takes_rows(const GemmArgs& a) { return a.m <= (a.n < 8192 ? 16 : a.dual && a.n >= 16384 ? 4 : 8); }
+// Beyond that, one round of workgroups of 32 rows x 32 tokens where k has an odd number of 64-column chunks, which only the tiles
+// with 64-deep stages can walk, and few of them: 256 columns of 17 / 400 tokens, k = 704: 6.0 / 6.3 -> 4.4 / 4.8 us.  (k = 256: 4.6
+// -> 4.3, 1024: the same, 2816: 8.2 -> 12.0.)
+bool one_round_of_blocks(const GemmArgs& a) { return static_cast<int64_t>(a.n / 32) * ((a.m + 31) / 32) <= 256; }
+bool takes_rows(const GemmArgs& a) {
+  if (a.m > 16) return !a.dual && a.k % 128 != 0 && a.k > 384 && a.k < 1024 && one_round_of_blocks(a);
+  return a.m <= (a.n < 8192 ? 16 : a.dual && a.n >= 16384 ? 4 : 8);
+}
 
 // With the norm inside, the direct kernel also saves the norm's launch, and pays for it with a load, a conversion and the squares
 // for every weight fragment: whole layers behind 512 tokens, norm apart -> inside, 1 / 16 tokens: hidden 256 28.0 -> 21.1 / 28.1 ->
 // 22.3 us; 1024 29.5 -> 23.8 / 35.6 -> 29.3; 2048 47.4 -> 42.2 / 56.9 -> 53.3 (the append launch that is saved
 // included).  Wide SwiGLU layers are better off with the norm apart: 11008 x 4096 at 1 token 4.8 + 32.5 us against 39.6; and wide
 // projections beyond 8 tokens with the tiles (12288 x 4096 at 1 token inside: 23.4 us; apart 4.8 + 18.5, and 4.8 for the append).
-bool takes_normed_rows(const GemmArgs& a) { return a.dual ? a.n < 16384 && a.m <= 16 : a.m <= (a.n < 8192 ? 16 : 8); }
+// Beyond 16 tokens, with blocks of 32 rows x 32 tokens, as long as that is one round of short rows, or where reading
+// both operands again for every block costs less than the launch.  Whole layers, norms apart -> inside: hidden 256, 17 / 256
+// tokens 30.4 -> 23.4 / 32.3 -> 26.2 us (the down projection's share of it as above); 1024, 17 / 160 tokens 38.0 -> 35.6 / 44.1 -> 42.5, 256
+// tokens of either projection alone +1.8 and +20; 2048, 32 tokens 56.7 -> 57.3.
+bool takes_normed_rows(const GemmArgs& a) {
+  if (a.m > 16) {
+    const int64_t workgroups = static_cast<int64_t>(a.n / 32) * ((a.m + 31) / 32);
+    return (one_round_of_blocks(a) && a.k <= 1024) || workgroups * (a.k + 256) <= 330000;
+  }
+  return a.dual ? a.n < 16384 : a.m <= (a.n < 8192 ? 16 : 8);
+}
 
 const TileChoice* choose_tile(const GemmArgs& a) {
   const TileChoice* best = nullptr;
@@ -872,7 +998,7 @@ int linear_plan(int64_t m, int64_t n_out, int64_t k, bool dual, LinearPlan* plan
   a.n = static_cast<int>(dual ? 2 * n_out : n_out);
   a.k = static_cast<int>(k);
   if (takes_rows(a)) {
-    *plan = LinearPlan{16, 16, 0, 1};
+    *plan = a.m > 16 ? LinearPlan{32, 32, 0, 1} : LinearPlan{16, 16, 0, 1};
     return KVRA_OK;
   }
   const TileChoice* c = choose_tile(a);

@@ -23,10 +23,15 @@ def _rel(got, want):
 @pytest.mark.parametrize("m,H,Hkv,d,hidden,tile", [
     (1, 1, 1, 64, 384, (16, 16, 0)), (7, 6, 2, 128, 128, (16, 16, 0)), (16, 71, 1, 64, 192, (16, 16, 0)),
     (1, 3, 1, 64, 4160, (16, 16, 0)), (16, 1, 1, 128, 4096, (16, 16, 0)), (8, 40, 40, 128, 64, (16, 16, 0)),
-    (17, 1, 1, 64, 384, (32, 32, 128)), (17, 1, 1, 128, 128, (32, 32, 128)),
-    (65, 35, 5, 64, 128, (32, 64, 128)), (33, 25, 5, 128, 128, (32, 64, 128)),
-    (17, 1, 1, 64, 192, (64, 64, 64)), (17, 1, 1, 128, 320, (64, 64, 64)),
-    (132, 35, 5, 64, 384, (64, 64, 128)), (84, 25, 5, 128, 384, (64, 64, 128)),
+    # the norm inside, in blocks of 32 rows and 32 tokens (8 and 16 waves); the tile is what the projection alone would get
+    (17, 1, 1, 64, 384, (32, 32, 128)), (17, 1, 1, 128, 128, (32, 32, 128)), (65, 35, 5, 64, 128, (32, 64, 128)),
+    (132, 35, 5, 64, 384, (64, 64, 128)), (17, 1, 1, 128, 320, (64, 64, 64)), (31, 4, 2, 64, 2048, (32, 32, 128)),
+    (65, 2, 1, 128, 704, (32, 32, 0)), (32, 5, 5, 128, 960, (32, 32, 0)), (20, 1, 1, 64, 4160, (64, 64, 64)),
+    # the tiles
+    (33, 25, 5, 64, 2176, (32, 32, 128)), (36, 14, 2, 128, 2176, (32, 32, 128)),
+    (98, 40, 8, 64, 512, (32, 64, 128)), (33, 40, 8, 128, 512, (32, 64, 128)),
+    (388, 15, 5, 64, 256, (64, 64, 64)), (69, 40, 8, 128, 256, (64, 64, 64)),
+    (161, 40, 8, 64, 256, (64, 64, 128)), (161, 21, 3, 128, 256, (64, 64, 128)),
     (514, 16, 16, 64, 320, (64, 128, 64)), (193, 40, 8, 128, 320, (64, 128, 64)),
     (782, 24, 8, 64, 384, (128, 128, 64)), (321, 35, 5, 128, 320, (128, 128, 64)),
     (2437, 15, 5, 64, 384, (128, 192, 64)), (642, 35, 5, 128, 384, (128, 192, 64)),

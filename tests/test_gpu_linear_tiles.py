@@ -55,6 +55,14 @@ def test_tiles_in_turn(m, n, k, mode, tile):
     check_linear(m, n, k, mode)
 
 
+@pytest.mark.parametrize("m,n,k", [(17, 32, 448), (63, 96, 576), (400, 256, 704), (1000, 256, 704), (33, 4096, 960), (300, 800, 832)])
+@pytest.mark.parametrize("mode", ["plain", "residual"])
+def test_blocks_of_32_tokens(m, n, k, mode):
+    """The direct kernel beyond 16 tokens, where k is an odd number of 64-column chunks (8 and 16 waves, up to one round)."""
+    assert kvra.kvra_linear_tile(m, n, k, False) == (32, 32, 0, 1)
+    check_linear(m, n, k, mode)
+
+
 def check_linear(m, n, k, mode):
     x = synth.normal_bf16(5, 23, 0, (m, k))
     w = synth.normal_bf16(5, 23, 1, (n, k), std=k ** -0.5)
