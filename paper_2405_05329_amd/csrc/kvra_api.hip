@@ -273,8 +273,13 @@ extern "C" int kvra_layer_chunk(const kvra_layer* L, const void* x, void* y, voi
     return rc;
   if ((rc = kvra_chunk_attn(q, k_cache, v_cache, prefix_len, c, L->n_q_heads, L->n_kv_heads, L->head_dim,
                             L->scale, attn, stream)) != KVRA_OK) return rc;
-  if ((rc = kvra_linear(attn, L->wo, nullptr, x, x2, c, L->hidden, hd, stream)) != KVRA_OK) return rc;
+  // Calls whose attention is in no need of the scratch may overlap with others on other streams: their projections keep off it too.
+  kvra::SharedScratch scratch;
+  const kvra::SharedScratch* const shared =
+      kvra::attn_scratch_in_use(prefix_len, c, L->n_q_heads, L->n_kv_heads, L->head_dim, st, &scratch) ? &scratch : nullptr;
+  const int hidden_cols[1] = {L->hidden};
+  if ((rc = kvra::launch_linear(attn, L->wo, nullptr, x, &x2, hidden_cols, 1, c, L->hidden, hd, st, shared)) != KVRA_OK) return rc;
   if ((rc = kvra::launch_norm_swiglu(x2, L->norm2, L->rms_eps, h, L->w_gate, L->w_up, act, c, L->ffn, L->hidden, st)) != KVRA_OK)
     return rc;
-  return kvra_linear(act, L->w_down, nullptr, x2, y, c, L->hidden, L->ffn, stream);
+  return kvra::launch_linear(act, L->w_down, nullptr, x2, &y, hidden_cols, 1, c, L->hidden, L->ffn, st, shared);
 }

@@ -1328,6 +1328,20 @@ int attn_row_splits(int64_t prefix_len, int64_t chunk_len, int n_q_heads, int n_
   return KVRA_OK;
 }
 
+bool attn_scratch_in_use(int64_t prefix_len, int64_t chunk_len, int n_q_heads, int n_kv_heads, int head_dim, hipStream_t stream,
+                         SharedScratch* shared) {
+  int cus = 0;
+  int64_t slots = 0;
+  float* const p = device_scratch(stream, &cus, &slots);
+  AttnPlan plan;
+  if (p == nullptr || cached_plan(prefix_len, chunk_len, n_q_heads, n_kv_heads, head_dim, cus, true, &plan) != KVRA_OK ||
+      plan.partial_pieces == 0)
+    return false;
+  *shared = SharedScratch{p, slots * attn_partial_bytes(128), reinterpret_cast<int*>(p + static_cast<size_t>(slots) * kPartialFloats(128)),
+                          kCounterInts};
+  return true;
+}
+
 int launch_chunk_attn(const void* q, const void* k_cache, const void* v_cache,
                       int64_t prefix_len, int64_t chunk_len, int n_q_heads, int n_kv_heads, int head_dim,
                       float scale, void* out, hipStream_t stream, bool static_scratch_only) {

@@ -55,6 +55,10 @@ struct GemmArgs {
   int rope;
   int rotated;             // output columns [0, rotated) are rotated (those of Q and K; 0: none)
   const float* angles;     // [m][rope]: cos of a token's rope / 2 angles, then their sin
+  // Launches whose tiles leave CUs idle: `splits` workgroups share the k of a tile and meet through the scratch.
+  int splits;
+  float* scratch;          // a tile's sums per workgroup
+  int* counters;           // pieces counted so far, one per tile; all zero between launches
 };
 
 // Tile of a workgroup: TN weight rows x TM tokens, k in stages of TK through a ring of ST LDS slots;
@@ -111,8 +115,9 @@ __device__ __forceinline__ void gather_columns(const f32x4& lo, const f32x4& hi,
   }
 }
 
-template <class T, bool ROPE>
+template <class T, bool ROPE, bool SPLIT>
 __global__ __launch_bounds__(T::THREADS, T::PER_SIMD) void linear_kernel(GemmArgs a) {
+  static_assert(!SPLIT || T::WK == 1, "either the waves of a workgroup share k or workgroups do");
   constexpr int NB = T::NB, MB = T::MB, L = T::L, ST = T::ST, TK = T::TK, KPW = T::KPW, PR = T::PR;
   extern __shared__ u32x4 smem[];
   char* const lds = reinterpret_cast<char*>(smem);
@@ -124,12 +129,16 @@ __global__ __launch_bounds__(T::THREADS, T::PER_SIMD) void linear_kernel(GemmArg
   // Workgroup -> tiles.  Workgroup ids go round-robin over the 8 XCDs; each XCD takes a contiguous
   // run of the tile order "bands of 4 weight tiles, token tiles inside a band, weight tile
   // fastest", so that the workgroups an XCD runs together share few weight and token tiles in its L2.
-  const int total = a.tiles_n * a.tiles_m;
+  // (Split: the run goes over all tiles of the first share of k, then of the second, ..., and a workgroup has one piece.)
+  const int tiles = a.tiles_n * a.tiles_m;
+  const int total = SPLIT ? tiles * a.splits : tiles;
   const int per = (total + 7) >> 3;
   const int t_step = gridDim.x >> 3;
-  const int t_first = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
-  const int t_end = min(((blockIdx.x & 7) + 1) * per, total);
-  if (t_first >= t_end) return;   // whole workgroup leaves before any barrier
+  const int t_mine = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+  const int t_last = min(((blockIdx.x & 7) + 1) * per, total);
+  if (t_mine >= t_last) return;   // whole workgroup leaves before any barrier
+  const int share = SPLIT ? t_mine / tiles : 0;
+  const int t_first = SPLIT ? t_mine - share * tiles : t_mine, t_end = SPLIT ? t_first + 1 : t_last;
   auto place = [&](int t, int* n0, int* m0) {
     const int band = t / (4 * a.tiles_m);
     const int width = min(4, a.tiles_n - 4 * band);
@@ -137,7 +146,9 @@ __global__ __launch_bounds__(T::THREADS, T::PER_SIMD) void linear_kernel(GemmArg
     *m0 = (within / width) * T::TM;
     *n0 = (4 * band + within % width) * T::TN;
   };
-  const int KT = a.k / TK;
+  const int KT_all = a.k / TK;
+  const int kt_first = SPLIT ? static_cast<int>(static_cast<long long>(KT_all) * share / a.splits) : 0;
+  const int KT = SPLIT ? static_cast<int>(static_cast<long long>(KT_all) * (share + 1) / a.splits) - kt_first : KT_all;
   int stages_left = ((t_end - t_first + t_step - 1) / t_step) * KT;   // not yet computed
   int loads_left = stages_left;                                       // not yet sent for
 
@@ -187,7 +198,7 @@ __global__ __launch_bounds__(T::THREADS, T::PER_SIMD) void linear_kernel(GemmArg
   int load_t = t_first, load_kt = 0;
   auto send = [&](int i, unsigned slot_base, unsigned long long on) __attribute__((always_inline)) {
     const int idx = T::LOADS % T::NW == 0 ? i * T::NW + wave : min(i * T::NW + wave, T::LOADS - 1);
-    gemm_lds_dma16_if(on, src[i] + static_cast<long long>(load_kt) * TK, off[i], slot_base + idx * 1024);
+    gemm_lds_dma16_if(on, src[i] + static_cast<long long>(SPLIT ? kt_first + load_kt : load_kt) * TK, off[i], slot_base + idx * 1024);
   };
   auto sent = [&]() {   // the stage under load_t / load_kt is on its way: on to the next one
     --loads_left;
@@ -393,6 +404,59 @@ __global__ __launch_bounds__(T::THREADS, T::PER_SIMD) void linear_kernel(GemmArg
           for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
             for (int e = 0; e < 4; ++e) acc[nb][mb][e] += red[s * SHARE + ((nb * MB + mb) * 4 + e) * 64];
+    }
+    if constexpr (SPLIT) {
+      // The pieces of a tile meet as those of the attention kernel do: device-coherent stores, acknowledged before the piece
+      // is counted; the piece that completes the count adds all of them in the order of their shares (its own as well, as it was
+      // stored) and goes on to the epilogue.  16 bytes per lane, as many in flight as registers allow.
+      constexpr int SHARE_BYTES = T::TN * T::TM * 4, COHERENT = 16;   // (the sc1 bit: past the cache of this XCD)
+      const __amdgpu_buffer_rsrc_t res = __builtin_amdgcn_make_buffer_rsrc(
+          reinterpret_cast<char*>(a.scratch) + static_cast<long long>(t) * a.splits * SHARE_BYTES, 0, a.splits * SHARE_BYTES, 0x00020000);
+      auto slot_of = [&](int s, int nb, int mb) __attribute__((always_inline)) -> int {
+        return s * SHARE_BYTES + ((nb * MB + mb) * T::THREADS + tid) * 16;
+      };
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[nb][mb]), res, slot_of(share, nb, mb), 0, COHERENT);
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      __syncthreads();
+      int* const flag = reinterpret_cast<int*>(lds);   // (nothing is staged any more)
+      if (tid == 0) *flag = atomicAdd(a.counters + t, 1) == a.splits - 1 ? 1 : 0;
+      __syncthreads();
+      if (*flag == 0) return;
+      if (tid == 0) a.counters[t] = 0;                 // ready for the next launch
+      constexpr int AT_ONCE = MB == 1 ? 4 : MB == 2 ? 2 : 1, SHARES = MB >= 8 ? 2 : 4;
+#pragma unroll
+      for (int n1 = 0; n1 < NB; n1 += AT_ONCE) {
+#pragma unroll
+        for (int nb = n1; nb < n1 + AT_ONCE && nb < NB; ++nb)
+#pragma unroll
+          for (int mb = 0; mb < MB; ++mb) acc[nb][mb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        for (int s0 = 0; s0 < a.splits; s0 += SHARES) {
+          f32x4 v[SHARES][AT_ONCE][MB];
+#pragma unroll
+          for (int u = 0; u < SHARES; ++u)
+#pragma unroll
+            for (int q = 0; q < AT_ONCE; ++q)
+#pragma unroll
+              for (int mb = 0; mb < MB; ++mb)
+                v[u][q][mb] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                    res, slot_of(min(s0 + u, a.splits - 1), min(n1 + q, NB - 1), mb), 0, COHERENT));
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int u = 0; u < SHARES; ++u)
+            if (s0 + u < a.splits) {
+#pragma unroll
+              for (int q = 0; q < AT_ONCE; ++q)
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb)
+                  if (n1 + q < NB) acc[n1 + q < NB ? n1 + q : 0][mb] += v[u][q][mb];
+            }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
     }
     const int nw = n0 + wn * (T::TN / T::WN), mw = m0 + wm * (T::TM / T::WM) + r16;
     const int lane_col = 16 * (kg & 1) + 8 * (kg >> 1);   // see gather_columns
@@ -801,8 +865,17 @@ int launch_tile(GemmArgs& a, hipStream_t stream) {
   const int per = (a.tiles_n * a.tiles_m + 7) / 8;
   constexpr int PER_CU = T::PER_SIMD * 4 / T::NW;
   const unsigned grid = 8u * static_cast<unsigned>(std::min(per, 32 * PER_CU));
-  if (a.rope != 0) return launch_kernel(linear_kernel<T, true>, dim3(grid), dim3(T::THREADS), a, stream, T::LDS);
-  return launch_kernel(linear_kernel<T, false>, dim3(grid), dim3(T::THREADS), a, stream, T::LDS);
+  if (a.rope != 0) return launch_kernel(linear_kernel<T, true, false>, dim3(grid), dim3(T::THREADS), a, stream, T::LDS);
+  return launch_kernel(linear_kernel<T, false, false>, dim3(grid), dim3(T::THREADS), a, stream, T::LDS);
+}
+
+// a.splits workgroups per tile, all of them in one round
+template <class T>
+int launch_split(GemmArgs& a, hipStream_t stream) {
+  a.tiles_n = (a.n + T::TN - 1) / T::TN;
+  a.tiles_m = (a.m + T::TM - 1) / T::TM;
+  const unsigned pieces = 8u * static_cast<unsigned>((a.tiles_n * a.tiles_m * a.splits + 7) / 8);
+  return launch_kernel(linear_kernel<T, false, true>, dim3(pieces), dim3(T::THREADS), a, stream, T::LDS);
 }
 
 template <RowsKind KIND, bool NORM, class Args>
@@ -833,6 +906,7 @@ struct TileChoice {
   bool dual;
   float fixed, per_round, step, step_full;
   int (*launch)(GemmArgs&, hipStream_t);
+  int (*split)(GemmArgs&, hipStream_t) = nullptr;
 };
 
 const TileChoice kTiles[] = {
@@ -840,10 +914,13 @@ const TileChoice kTiles[] = {
     {256, 192, 64, 1, true, 5.44f, 0.00f, 1.084f, 0.137f, launch_tile<GemmTile<256, 192, 64, 2, 4, 2, 1, 2>>},
     {192, 256, 64, 1, false, 5.84f, 0.00f, 1.012f, 0.202f, launch_tile<GemmTile<192, 256, 64, 2, 2, 4, 1, 2>>},
     {192, 192, 64, 1, true, 3.76f, 1.97f, 0.714f, 0.173f, launch_tile<GemmTile<192, 192, 64, 3, 3, 4, 1, 3>>},
-    {128, 256, 64, 1, true, 4.29f, 1.28f, 0.679f, 0.155f, launch_tile<GemmTile<128, 256, 64, 3, 2, 4, 1, 2>>},
+    {128, 256, 64, 1, true, 4.29f, 1.28f, 0.679f, 0.155f, launch_tile<GemmTile<128, 256, 64, 3, 2, 4, 1, 2>>,
+     launch_split<GemmTile<128, 256, 64, 3, 2, 4, 1, 2>>},
     {128, 192, 64, 1, true, 4.04f, 0.83f, 0.536f, 0.155f, launch_tile<GemmTile<128, 192, 64, 4, 2, 4, 1, 2>>},
-    {128, 128, 64, 1, true, 4.73f, 0.00f, 0.420f, 0.106f, launch_tile<GemmTile<128, 128, 64, 5, 2, 4, 1, 2, true>>},
-    {64, 128, 64, 1, true, 3.51f, 0.85f, 0.303f, 0.042f, launch_tile<GemmTile<64, 128, 64, 6, 1, 8, 1, 2, true>>},
+    {128, 128, 64, 1, true, 4.73f, 0.00f, 0.420f, 0.106f, launch_tile<GemmTile<128, 128, 64, 5, 2, 4, 1, 2, true>>,
+     launch_split<GemmTile<128, 128, 64, 5, 2, 4, 1, 2, true>>},
+    {64, 128, 64, 1, true, 3.51f, 0.85f, 0.303f, 0.042f, launch_tile<GemmTile<64, 128, 64, 6, 1, 8, 1, 2, true>>,
+     launch_split<GemmTile<64, 128, 64, 6, 1, 8, 1, 2, true>>},
     {64, 64, 64, 2, true, 4.16f, 0.00f, 0.241f, 0.205f, launch_tile<GemmTile<64, 64, 64, 5, 1, 4, 1, 2, true>>},
     {64, 64, 128, 1, true, 3.48f, 0.89f, 0.179f, 0.029f, launch_tile<GemmTile<64, 64, 128, 4, 2, 2, 2, 2, true>>},
     {32, 64, 128, 1, true, 3.32f, 0.79f, 0.137f, 0.023f, launch_tile<GemmTile<32, 64, 128, 5, 1, 4, 2, 2, true>>},
@@ -860,6 +937,39 @@ float tile_cost(const TileChoice& c, const GemmArgs& a) {
   const float last = static_cast<float>(per_xcd - (rounds - 1) * slots) / slots;
   const float full = rounds - 1 + std::max(0.0f, 2.0f * last - 1.0f);
   return c.fixed + a.k / 64 * (rounds * c.step + full * c.step_full) + rounds * c.per_round;
+}
+
+// With k shared out over `splits` workgroups per tile, all in one round: the loop is that much shorter, and the merge costs 3.5 us and
+// 0.024 us per KB that the last piece reads back (a tile's sums, once per share).  Pays where k is deep and the tiles are few.  The down
+// projection of a 4096-wide layer (4096 x 11008, weights from memory), tokens: time before -> after: 77: 31.8 -> 28.2 us
+// (64 x 128, four shares); 250: 51.2 -> 41.5 (128 x 128, four); 500: 71.8 -> 63.6 (128 x 128, two); 1000: 103.1 -> 94.5 (128 x 256,
+// two).  4096 x 4096 and 2048 x 5632 would gain nothing to 5 %, so a split has to promise more than that.
+float split_cost(const TileChoice& c, const GemmArgs& a, int splits) {
+  const int64_t pieces = static_cast<int64_t>((a.n + c.tn - 1) / c.tn) * ((a.m + c.tm - 1) / c.tm) * splits;
+  const int stages = a.k / c.tk;
+  const float full = std::max(0.0f, static_cast<float>(pieces) / 128.0f - 1.0f);
+  return c.fixed + c.per_round + (stages + splits - 1) / splits * (c.step + full * c.step_full) + 3.5f +
+         0.024f * splits * static_cast<float>(c.tn * c.tm / 256);
+}
+
+// The tile and number of shares to split a launch that would get `whole` into, or nullptr.
+const TileChoice* choose_split(const GemmArgs& a, const TileChoice& whole, const SharedScratch& shared, int* splits) {
+  const TileChoice* best = nullptr;
+  float best_cost = 0.95f * tile_cost(whole, a);
+  for (const TileChoice& c : kTiles) {
+    if (c.split == nullptr || a.k % c.tk != 0) continue;
+    const int64_t tiles = static_cast<int64_t>((a.n + c.tn - 1) / c.tn) * ((a.m + c.tm - 1) / c.tm);
+    if (tiles > shared.n_counters) continue;
+    for (int s = 2; s <= 8 && tiles * s <= 256 && a.k / c.tk / s >= 16 && tiles * s * c.tn * c.tm * 4 <= shared.bytes; ++s) {
+      const float cost = split_cost(c, a, s);
+      if (cost < best_cost) {
+        best = &c;
+        best_cost = cost;
+        *splits = s;
+      }
+    }
+  }
+  return best;
 }
 
 // Up to 8 tokens (16 where there are fewer than 8192 weight rows) the direct kernel is the fastest: at 1 token 8.4 / 19.1 /
@@ -936,6 +1046,9 @@ void linear_args(const void* x, const void* w, const void* w2, const void* resid
   a.rope = 0;
   a.rotated = 0;
   a.angles = nullptr;
+  a.splits = 1;
+  a.scratch = nullptr;
+  a.counters = nullptr;
   a.m = static_cast<int>(m);
   a.n = static_cast<int>(a.dual ? 2 * n_out : n_out);
   a.k = static_cast<int>(k);
@@ -945,11 +1058,20 @@ void linear_args(const void* x, const void* w, const void* w2, const void* resid
 
 int launch_linear(const void* x, const void* w, const void* w2, const void* residual,
                   void* const* out, const int* seg_cols, int n_seg,
-                  int64_t m, int64_t n_out, int64_t k, hipStream_t stream) {
+                  int64_t m, int64_t n_out, int64_t k, hipStream_t stream, const SharedScratch* shared) {
   GemmArgs a;
   linear_args(x, w, w2, residual, out, seg_cols, n_seg, m, n_out, k, &a);
   if (takes_rows(a)) return a.dual ? launch_rows<kRowsDual, false>(a, stream) : launch_rows<kRowsPlain, false>(a, stream);
-  return choose_tile(a)->launch(a, stream);
+  const TileChoice* const whole = choose_tile(a);
+  if (shared != nullptr && !a.dual) {
+    const TileChoice* const c = choose_split(a, *whole, *shared, &a.splits);
+    if (c != nullptr) {
+      a.scratch = shared->data;
+      a.counters = shared->counters;
+      return c->split(a, stream);
+    }
+  }
+  return whole->launch(a, stream);
 }
 
 int launch_norm_qkv_append(const void* x, const void* gain, float eps, void* h, float* angles, const void* wqkv, void* const* out,

@@ -27,6 +27,16 @@ int launch_attn_rows(const void* q, const void* k_cache, const void* v_cache, in
                      int n_q_heads, int n_kv_heads, int head_dim, float scale, void* out, int splits, float* scratch,
                      int* counters, hipStream_t stream);
 int64_t attn_rows_slot_bytes(int head_dim);
+// The scratch buffer of the current device, if a kvra_chunk_attn launch of this shape on this stream would use it (what else the
+// same stream does before or after that launch may then use it too): zero counters, put back to zero by whoever counts.
+struct SharedScratch {
+  float* data;
+  int64_t bytes;
+  int* counters;
+  int n_counters;
+};
+bool attn_scratch_in_use(int64_t prefix_len, int64_t chunk_len, int n_q_heads, int n_kv_heads, int head_dim, hipStream_t stream,
+                         SharedScratch* shared);
 int64_t attn_static_scratch_bytes();   // size of the fixed scratch array kvra_chunk_attn_noalloc uses
 
 // Launch shape of kvra_chunk_attn for a device with `cus` compute units (pure host arithmetic).
@@ -78,10 +88,11 @@ int list_chunk_attn_pieces(int64_t prefix_len, int64_t chunk_len, int n_q_heads,
                            int cus, int32_t* records, int64_t capacity, int64_t* count_out);
 
 // out[m, n_out] = x[m, k] . w[n_out, k]^T (+ residual), or silu(x . w^T) * (x . w2^T) when w2 is given.
+// With `shared`, launches of few tiles may share out k over workgroups that meet through that scratch.
 // The n_out output columns are split over n_seg (1..3) dense matrices of seg_cols[s] columns each.
 int launch_linear(const void* x, const void* w, const void* w2, const void* residual,
                   void* const* out, const int* seg_cols, int n_seg,
-                  int64_t m, int64_t n_out, int64_t k, hipStream_t stream);
+                  int64_t m, int64_t n_out, int64_t k, hipStream_t stream, const SharedScratch* shared = nullptr);
 // The first half of a layer's attention block: norm, projection onto `out` (Q, rows of the K cache, rows of the V cache), Q and
 // K rotated (rope_base > 0) for positions from `position` on.  h [m, k] and angles [m][head_dim] (cos of a token's head_dim / 2
 // angles, then their sin) are workspace that may or may not be used.
