@@ -64,6 +64,26 @@ def build(verbose: bool = False, extra_flags=(), trace: bool = False) -> str:
     return lib
 
 
+CALL_EXT = os.path.join(PKG, "_kvra_call.so")
+
+
+def build_binding() -> str:
+    """_kvra_call.so: the argument marshalling of the per-chunk calls (host code only)."""
+    import sysconfig
+
+    import torch
+    root = os.path.dirname(torch.__file__)
+    cxx = shutil.which("g++") or "c++"
+    cmd = [cxx, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-fvisibility=hidden",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-I", os.path.join(ROOT, "include"), "-I", sysconfig.get_paths()["include"],
+           "-isystem", os.path.join(root, "include"), "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"),
+           os.path.join(CSRC, "kvra_binding.cpp"), "-o", CALL_EXT,
+           "-L", os.path.join(root, "lib"), "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10"]
+    subprocess.run(cmd, check=True)
+    return CALL_EXT
+
+
 PROBE_LIB = os.path.join(PKG, "libkvra_probe.so")
 
 
@@ -80,4 +100,6 @@ if __name__ == "__main__":
     if "--probe" in sys.argv:
         print(build_probe())
     else:
+        if "--trace" not in sys.argv:
+            print(build_binding())
         print(build(verbose="-v" in sys.argv, trace="--trace" in sys.argv))

@@ -1,8 +1,9 @@
-"""ctypes binding of libkvra: the same entry points as include/kvra.h, argument marshalling only.
+"""Binding of libkvra: the same entry points as include/kvra.h, argument marshalling only (ctypes; the calls a program makes
+per chunk through a small native module, csrc/kvra_binding.cpp, which does the same with less ado).
 
 Tensor arguments may be torch tensors (their data_ptr() is passed; they must live on the GPU and
 be contiguous) or plain integer device addresses.  Every step of the path runs inside the library's
-HIP kernels; there is no Python or CPU fallback: if the shared library is missing, importing this
+HIP kernels; there is no Python or CPU fallback: if either shared library is missing, importing this
 module raises.
 """
 from __future__ import annotations
@@ -140,6 +141,19 @@ def _stream(stream):
     return stream.cuda_stream     # torch.cuda.Stream
 
 
+def _load_calls():
+    path = os.path.join(_PKG, "_kvra_call.so")
+    if not os.path.exists(path):
+        raise ImportError(f"{path} is missing: build it with `python -m paper_2405_05329_amd.build`")
+    from . import _kvra_call
+    names = ("kvra_append_kv", "kvra_chunk_attn", "kvra_rms_norm", "kvra_linear", "kvra_qkv_proj", "kvra_layer_chunk")
+    _kvra_call.bind(_ptr, *(ctypes.cast(getattr(_lib, n), ctypes.c_void_p).value for n in names))
+    return _kvra_call
+
+
+_call = _load_calls()
+
+
 def _cost(cost):
     if cost is None:
         return None, None
@@ -157,10 +171,8 @@ def kvra_version() -> int:
 
 def kvra_append_kv(k_in, v_in, q_inout, k_cache, v_cache, prefix_len, chunk_len, capacity,
                    n_q_heads, n_kv_heads, head_dim, rope_base, stream=None, check=True) -> int:
-    rc = _lib.kvra_append_kv(_ptr(k_in), _ptr(v_in), _ptr(q_inout), _ptr(k_cache), _ptr(v_cache),
-                             int(prefix_len), int(chunk_len), int(capacity),
-                             int(n_q_heads), int(n_kv_heads), int(head_dim), float(rope_base),
-                             _stream(stream))
+    rc = _call.append_kv(k_in, v_in, q_inout, k_cache, v_cache, prefix_len, chunk_len, capacity,
+                         n_q_heads, n_kv_heads, head_dim, rope_base, stream)
     if check and rc != KVRA_OK:
         raise KvraError(rc, "kvra_append_kv")
     return rc
@@ -168,9 +180,7 @@ def kvra_append_kv(k_in, v_in, q_inout, k_cache, v_cache, prefix_len, chunk_len,
 
 def kvra_chunk_attn(q, k_cache, v_cache, prefix_len, chunk_len, n_q_heads, n_kv_heads, head_dim,
                     scale, out, stream=None, check=True) -> int:
-    rc = _lib.kvra_chunk_attn(_ptr(q), _ptr(k_cache), _ptr(v_cache), int(prefix_len), int(chunk_len),
-                              int(n_q_heads), int(n_kv_heads), int(head_dim), float(scale),
-                              _ptr(out), _stream(stream))
+    rc = _call.chunk_attn(q, k_cache, v_cache, prefix_len, chunk_len, n_q_heads, n_kv_heads, head_dim, scale, out, stream)
     if check and rc != KVRA_OK:
         raise KvraError(rc, "kvra_chunk_attn")
     return rc
@@ -360,14 +370,13 @@ def kvra_table_predict(context_len, granularity, table):
 
 
 def kvra_rms_norm(x, gain, y, rows, hidden, eps, stream=None):
-    rc = _lib.kvra_rms_norm(_ptr(x), _ptr(gain), _ptr(y), int(rows), int(hidden), float(eps), _stream(stream))
+    rc = _call.rms_norm(x, gain, y, rows, hidden, eps, stream)
     if rc != KVRA_OK:
         raise KvraError(rc, "kvra_rms_norm")
 
 
 def kvra_linear(x, w, w2, residual, out, m, n, k, stream=None):
-    rc = _lib.kvra_linear(_ptr(x), _ptr(w), _ptr(w2), _ptr(residual), _ptr(out), int(m), int(n), int(k),
-                          _stream(stream))
+    rc = _call.linear(x, w, w2, residual, out, m, n, k, stream)
     if rc != KVRA_OK:
         raise KvraError(rc, "kvra_linear")
 
@@ -382,8 +391,7 @@ def kvra_linear_tile(m, n, k, swiglu) -> tuple:
 
 
 def kvra_qkv_proj(x, wqkv, q_out, k_out, v_out, m, n_q_heads, n_kv_heads, head_dim, k, stream=None):
-    rc = _lib.kvra_qkv_proj(_ptr(x), _ptr(wqkv), _ptr(q_out), _ptr(k_out), _ptr(v_out), int(m), int(n_q_heads),
-                            int(n_kv_heads), int(head_dim), int(k), _stream(stream))
+    rc = _call.qkv_proj(x, wqkv, q_out, k_out, v_out, m, n_q_heads, n_kv_heads, head_dim, k, stream)
     if rc != KVRA_OK:
         raise KvraError(rc, "kvra_qkv_proj")
 
@@ -405,8 +413,9 @@ def kvra_layer_workspace_bytes(layer: KvraLayer, chunk_len) -> int:
 
 def kvra_layer_chunk(layer: KvraLayer, x, y, k_cache, v_cache, prefix_len, chunk_len, capacity,
                      workspace, workspace_bytes, stream=None):
-    rc = _lib.kvra_layer_chunk(ctypes.byref(layer), _ptr(x), _ptr(y), _ptr(k_cache), _ptr(v_cache),
-                               int(prefix_len), int(chunk_len), int(capacity), _ptr(workspace),
-                               int(workspace_bytes), _stream(stream))
+    if not isinstance(layer, KvraLayer):
+        raise TypeError("a KvraLayer is expected")
+    rc = _call.layer_chunk(ctypes.addressof(layer), x, y, k_cache, v_cache, prefix_len, chunk_len, capacity, workspace,
+                           workspace_bytes, stream)
     if rc != KVRA_OK:
         raise KvraError(rc, "kvra_layer_chunk")
