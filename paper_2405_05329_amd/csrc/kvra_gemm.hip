@@ -56,6 +56,7 @@ struct GemmArgs {
   int rotated;             // output columns [0, rotated) are rotated (those of Q and K; 0: none)
   const float* angles;     // [m][rope]: cos of a token's rope / 2 angles, then their sin
   // Launches whose tiles leave CUs idle: `splits` workgroups share the k of a tile and meet through the scratch.
+  int stagger;             // stages between the starts of neighbouring weight tiles (0: all start at the first)
   int splits;
   float* scratch;          // a tile's sums per workgroup
   int* counters;           // pieces counted so far, one per tile; all zero between launches
@@ -115,7 +116,7 @@ __device__ __forceinline__ void gather_columns(const f32x4& lo, const f32x4& hi,
   }
 }
 
-template <class T, bool ROPE, bool SPLIT>
+template <class T, bool ROPE, bool SPLIT, bool STAGGER>
 __global__ __launch_bounds__(T::THREADS, T::PER_SIMD) void linear_kernel(GemmArgs a) {
   static_assert(!SPLIT || T::WK == 1, "either the waves of a workgroup share k or workgroups do");
   constexpr int NB = T::NB, MB = T::MB, L = T::L, ST = T::ST, TK = T::TK, KPW = T::KPW, PR = T::PR;
@@ -195,17 +196,34 @@ __global__ __launch_bounds__(T::THREADS, T::PER_SIMD) void linear_kernel(GemmArg
     }
   };
   const unsigned lds0 = static_cast<unsigned>(reinterpret_cast<uintptr_t>((lds_void*)smem));
-  int load_t = t_first, load_kt = 0;
+  // STAGGER: the walk along k starts somewhere else for every weight tile and wraps around (a form of its own: the two extra scalar
+  // values cost the others 0.3 %)
+  auto k_start = [&](int t) __attribute__((always_inline)) -> int {
+    if constexpr (!STAGGER) return 0;
+    int n0, m0;
+    place(t, &n0, &m0);
+    return n0 / T::TN * a.stagger % KT;
+  };
+  int load_t = t_first, load_from = k_start(t_first), load_kt = load_from, load_end = KT;
   auto send = [&](int i, unsigned slot_base, unsigned long long on) __attribute__((always_inline)) {
     const int idx = T::LOADS % T::NW == 0 ? i * T::NW + wave : min(i * T::NW + wave, T::LOADS - 1);
     gemm_lds_dma16_if(on, src[i] + static_cast<long long>(SPLIT ? kt_first + load_kt : load_kt) * TK, off[i], slot_base + idx * 1024);
   };
   auto sent = [&]() {   // the stage under load_t / load_kt is on its way: on to the next one
     --loads_left;
-    if (++load_kt == KT) {
-      load_kt = 0;
-      load_t += t_step;
-      if (load_t < t_end) aim(load_t);
+    if (++load_kt == (STAGGER ? load_end : KT)) {
+      if (STAGGER && load_end == KT && load_from != 0) {   // wraps around
+        load_kt = 0;
+        load_end = load_from;
+      } else {
+        load_kt = 0;
+        load_t += t_step;
+        if (load_t < t_end) {
+          aim(load_t);
+          load_from = load_kt = k_start(load_t);
+          load_end = KT;
+        }
+      }
     }
   };
 
@@ -865,8 +883,14 @@ int launch_tile(GemmArgs& a, hipStream_t stream) {
   const int per = (a.tiles_n * a.tiles_m + 7) / 8;
   constexpr int PER_CU = T::PER_SIMD * 4 / T::NW;
   const unsigned grid = 8u * static_cast<unsigned>(std::min(per, 32 * PER_CU));
-  if (a.rope != 0) return launch_kernel(linear_kernel<T, true, false>, dim3(grid), dim3(T::THREADS), a, stream, T::LDS);
-  return launch_kernel(linear_kernel<T, false, false>, dim3(grid), dim3(T::THREADS), a, stream, T::LDS);
+  const dim3 g(grid), b(T::THREADS);
+  if constexpr (T::TN * T::TM <= 128 * 256) {   // (few tokens do not get the larger ones)
+    if (a.stagger != 0)
+      return a.rope != 0 ? launch_kernel(linear_kernel<T, true, false, true>, g, b, a, stream, T::LDS)
+                         : launch_kernel(linear_kernel<T, false, false, true>, g, b, a, stream, T::LDS);
+  }
+  return a.rope != 0 ? launch_kernel(linear_kernel<T, true, false, false>, g, b, a, stream, T::LDS)
+                     : launch_kernel(linear_kernel<T, false, false, false>, g, b, a, stream, T::LDS);
 }
 
 // a.splits workgroups per tile, all of them in one round
@@ -875,7 +899,8 @@ int launch_split(GemmArgs& a, hipStream_t stream) {
   a.tiles_n = (a.n + T::TN - 1) / T::TN;
   a.tiles_m = (a.m + T::TM - 1) / T::TM;
   const unsigned pieces = 8u * static_cast<unsigned>((a.tiles_n * a.tiles_m * a.splits + 7) / 8);
-  return launch_kernel(linear_kernel<T, false, true>, dim3(pieces), dim3(T::THREADS), a, stream, T::LDS);
+  return launch_kernel(a.stagger != 0 ? linear_kernel<T, false, true, true> : linear_kernel<T, false, true, false>, dim3(pieces),
+                       dim3(T::THREADS), a, stream, T::LDS);
 }
 
 template <RowsKind KIND, bool NORM, class Args>
@@ -1052,6 +1077,13 @@ void linear_args(const void* x, const void* w, const void* w2, const void* resid
   a.m = static_cast<int>(m);
   a.n = static_cast<int>(a.dual ? 2 * n_out : n_out);
   a.k = static_cast<int>(k);
+  // Few tokens on deep rows is a pass over the weights.  When all workgroups walk the rows in step, they ask for the same columns of
+  // rows that lie a power of two (or nearly) apart, which is only part of the memory channels at a time; weight tiles that start
+  // three stages apart ask for more of them.  Weights from memory, in step -> apart: 4096 x 11008, 40 / 77 / 250 tokens 26.5 ->
+  // 24.6 / 33.0 -> 30.1 / 50.7 -> 49.2 us; 11008 x 4096 SwiGLU, 77 tokens 44.1 -> 42.2; 12288 x 4096 29.0 -> 28.7.  Eight apart is worse
+  // (12288 x 4096, 40 tokens 23.8 -> 29.7), rows of 2048 and less gain nothing, and from 500 tokens on the
+  // tiles that share an operand in the L2 lose more by it (11008 x 4096 SwiGLU, 1000 tokens 166 -> 172).
+  a.stagger = m <= 256 && k >= 4096 ? 3 : 0;
 }
 
 }  // namespace

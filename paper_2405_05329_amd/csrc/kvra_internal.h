@@ -125,7 +125,7 @@ inline bool grant_lds(const void* kernel, unsigned bytes) {
     int device;
     unsigned bytes;
   };
-  constexpr int kGrants = 32;   // more than there are such kernels
+  constexpr int kGrants = 64;   // more than there are such kernels
   static thread_local Grant grants[kGrants] = {};
   static thread_local int next = 0;
   int device = 0;

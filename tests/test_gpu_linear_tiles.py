@@ -55,6 +55,18 @@ def test_tiles_in_turn(m, n, k, mode, tile):
     check_linear(m, n, k, mode)
 
 
+@pytest.mark.parametrize("m,n,k,mode,tile", [
+    (26, 32, 4224, "plain", (32, 32, 128, 1)), (35, 32, 4288, "swiglu", (64, 64, 64, 1)), (33, 4192, 4224, "residual", (32, 64, 128, 1)),
+    (129, 10400, 4096, "plain", (64, 64, 128, 2)), (67, 8224, 4224, "swiglu", (128, 128, 64, 1)),
+    (129, 8608, 4096, "swiglu", (128, 192, 64, 1)),
+])
+def test_weight_tiles_that_start_apart(m, n, k, mode, tile):
+    """Up to 256 tokens on rows of 4096 and more, where every weight tile starts its walk along k elsewhere and wraps around:
+    stages of 64 and 128, an odd number of them, several tiles per workgroup."""
+    assert kvra.kvra_linear_tile(m, n, k, mode == "swiglu") == tile
+    check_linear(m, n, k, mode)
+
+
 @pytest.mark.parametrize("m,n,k", [(17, 32, 448), (63, 96, 576), (400, 256, 704), (1000, 256, 704), (33, 4096, 960), (300, 800, 832)])
 @pytest.mark.parametrize("mode", ["plain", "residual"])
 def test_blocks_of_32_tokens(m, n, k, mode):
