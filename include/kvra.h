@@ -342,7 +342,8 @@ int kvra_linear(const void* x, const void* w, const void* w2, const void* residu
 /*
  * The tile kvra_linear (swiglu != 0: with w2) takes for a shape (host arithmetic only), as 4 ints: [0] weight rows (swiglu:
  * of both weights together) and [1] tokens of a workgroup's tile, [2] depth of its k stages (0: the kernel for few tokens, which
- * has none), [3] the largest number of tiles a workgroup walks.
+ * has none), [3] the largest number of tiles a workgroup walks.  (Long calls whose tiles would leave the last round of workgroups
+ * nearly empty are two launches, the second for the columns left over: the figures are the first's.)
  */
 int kvra_linear_tile(int64_t m, int64_t n, int64_t k, int swiglu, int* tile_out);
 

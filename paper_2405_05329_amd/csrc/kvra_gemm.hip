@@ -964,6 +964,20 @@ float tile_cost(const TileChoice& c, const GemmArgs& a) {
   return c.fixed + a.k / 64 * (rounds * c.step + full * c.step_full) + rounds * c.per_round;
 }
 
+const TileChoice* choose_tile(const GemmArgs& a) {
+  const TileChoice* best = nullptr;
+  float best_cost = 0.0f;
+  for (const TileChoice& c : kTiles) {
+    if ((a.dual && !c.dual) || a.k % c.tk != 0) continue;
+    const float cost = tile_cost(c, a);
+    if (best == nullptr || cost < best_cost) {
+      best = &c;
+      best_cost = cost;
+    }
+  }
+  return best;
+}
+
 // With k shared out over `splits` workgroups per tile, all in one round: the loop is that much shorter, and the merge costs 3.5 us and
 // 0.024 us per KB that the last piece reads back (a tile's sums, once per share).  Pays where k is deep and the tiles are few.  The down
 // projection of a 4096-wide layer (4096 x 11008, weights from memory), tokens: time before -> after: 77: 31.8 -> 28.2 us
@@ -992,6 +1006,43 @@ const TileChoice* choose_split(const GemmArgs& a, const TileChoice& whole, const
         best_cost = cost;
         *splits = s;
       }
+    }
+  }
+  return best;
+}
+
+// A long launch whose tiles leave its last round nearly empty goes out as two: one of the four large tiles on as many columns as fill
+// whole rounds, and whatever is best on the columns left over (the same sums in the same order: no result changes).  22016 x 4096 SwiGLU rows
+// are 86 tiles of 256, so 3072 tokens are 4.03 rounds: 432 -> 395 us; 700 tokens 125 -> 115, 1500 236 -> 212, 3712 537 -> 487;
+// 11264 x 2048 at 6000 tokens 226 -> 209; 4096 x 11008, 2304 / 4800 tokens: 206 -> 189 / 394 -> 360.  The two
+// have to promise 4 % together, and are only looked for where that is more than the search (1 us) and the second launch.  Short rows
+// without SwiGLU stay whole: the fit is pessimistic there (4096 x 4096, 4800 tokens: 152 us expected, 137 measured, 143 in two).
+struct TwoParts {
+  const TileChoice* first;   // nullptr: one launch
+  const TileChoice* second;
+  int columns;               // weight rows walked by the first
+};
+
+TwoParts choose_two(const GemmArgs& a, const TileChoice& whole) {
+  TwoParts best = {nullptr, nullptr, 0};
+  if (a.k < (a.dual ? 1024 : 8192)) return best;
+  float best_cost = 0.96f * tile_cost(whole, a);
+  if (best_cost < 60.0f) return best;
+  for (const TileChoice& c : kTiles) {
+    if (c.tn * c.tm < 128 * 256 || c.per_cu != 1 || (a.dual && !c.dual) || a.k % c.tk != 0) continue;
+    const int64_t tiles_m = (a.m + c.tm - 1) / c.tm, tiles = static_cast<int64_t>((a.n + c.tn - 1) / c.tn) * tiles_m;
+    const int64_t columns = tiles / 256 * 256 / tiles_m * c.tn;
+    if (columns <= 0 || columns >= a.n) continue;
+    GemmArgs part = a;
+    part.n = static_cast<int>(columns);
+    const float first = tile_cost(c, part) + 1.0f;
+    if (first >= best_cost) continue;
+    part.n = a.n - part.n;
+    const TileChoice* const rest = choose_tile(part);
+    const float cost = first + tile_cost(*rest, part);
+    if (cost < best_cost) {
+      best = TwoParts{&c, rest, static_cast<int>(columns)};
+      best_cost = cost;
     }
   }
   return best;
@@ -1027,20 +1078,6 @@ bool takes_normed_rows(const GemmArgs& a) {
     return (one_round_of_blocks(a) && a.k <= 1024) || workgroups * (a.k + 256) <= 330000;
   }
   return a.dual ? a.n < 16384 : a.m <= (a.n < 8192 ? 16 : 8);
-}
-
-const TileChoice* choose_tile(const GemmArgs& a) {
-  const TileChoice* best = nullptr;
-  float best_cost = 0.0f;
-  for (const TileChoice& c : kTiles) {
-    if ((a.dual && !c.dual) || a.k % c.tk != 0) continue;
-    const float cost = tile_cost(c, a);
-    if (best == nullptr || cost < best_cost) {
-      best = &c;
-      best_cost = cost;
-    }
-  }
-  return best;
 }
 
 }  // namespace
@@ -1095,6 +1132,7 @@ int launch_linear(const void* x, const void* w, const void* w2, const void* resi
   linear_args(x, w, w2, residual, out, seg_cols, n_seg, m, n_out, k, &a);
   if (takes_rows(a)) return a.dual ? launch_rows<kRowsDual, false>(a, stream) : launch_rows<kRowsPlain, false>(a, stream);
   const TileChoice* const whole = choose_tile(a);
+  if (n_seg > 1) return whole->launch(a, stream);
   if (shared != nullptr && !a.dual) {
     const TileChoice* const c = choose_split(a, *whole, *shared, &a.splits);
     if (c != nullptr) {
@@ -1103,7 +1141,18 @@ int launch_linear(const void* x, const void* w, const void* w2, const void* resi
       return c->split(a, stream);
     }
   }
-  return whole->launch(a, stream);
+  const TwoParts two = choose_two(a, *whole);
+  if (two.first == nullptr) return whole->launch(a, stream);
+  const int columns = a.dual ? two.columns / 2 : two.columns;   // of the output
+  GemmArgs rest = a;
+  a.n = two.columns;
+  rest.n -= two.columns;
+  rest.w += static_cast<int64_t>(columns) * k;
+  if (a.dual) rest.w2 += static_cast<int64_t>(columns) * k;
+  if (rest.res != nullptr) rest.res += columns;
+  rest.seg[0].ptr += columns;
+  const int rc = two.first->launch(a, stream);
+  return rc != KVRA_OK ? rc : two.second->launch(rest, stream);
 }
 
 int launch_norm_qkv_append(const void* x, const void* gain, float eps, void* h, float* angles, const void* wqkv, void* const* out,
@@ -1156,6 +1205,11 @@ int linear_plan(int64_t m, int64_t n_out, int64_t k, bool dual, LinearPlan* plan
     return KVRA_OK;
   }
   const TileChoice* c = choose_tile(a);
+  const TwoParts two = choose_two(a, *c);
+  if (two.first != nullptr) {
+    c = two.first;
+    a.n = two.columns;
+  }
   const int64_t per_xcd = tiles_per_xcd(*c, a);
   const int64_t workgroups = std::min<int64_t>(per_xcd, 32 * c->per_cu);   // of an XCD
   *plan = LinearPlan{c->tn, c->tm, c->tk, static_cast<int>((per_xcd + workgroups - 1) / workgroups)};

@@ -67,6 +67,17 @@ def test_weight_tiles_that_start_apart(m, n, k, mode, tile):
     check_linear(m, n, k, mode)
 
 
+@pytest.mark.parametrize("m,n,k,mode,tile", [
+    (1355, 10912, 1024, "swiglu", (256, 256, 64, 2)), (776, 9984, 2048, "swiglu", (192, 192, 64, 2)),
+    (787, 9824, 8192, "residual", (192, 192, 64, 1)), (982, 8256, 8192, "plain", (128, 256, 64, 1)),
+])
+def test_launches_in_two(m, n, k, mode, tile):
+    """Calls whose tiles would leave their last round nearly empty: whole rounds of one tile, then another on the columns left."""
+    got = kvra.kvra_linear_tile(m, n, k, mode == "swiglu")
+    assert got == tile and -(-n * (2 if mode == "swiglu" else 1) // got[0]) * -(-m // got[1]) > 256 * got[3]   # not all of it
+    check_linear(m, n, k, mode)
+
+
 @pytest.mark.parametrize("m,n,k", [(17, 32, 448), (63, 96, 576), (400, 256, 704), (1000, 256, 704), (33, 4096, 960), (300, 800, 832)])
 @pytest.mark.parametrize("mode", ["plain", "residual"])
 def test_blocks_of_32_tokens(m, n, k, mode):
