@@ -1,7 +1,7 @@
 // Linear layers of the decoder layer a KV-Runahead process runs around its attention block
 // (App. C listing: q/k/v projections before, output projection after the attention; the SwiGLU MLP
 // of the LLaMA models of Sec. 5) for gfx950:  out[m, n] = sum_k x[m, k] * w[n, k], bf16 in, fp32
-// accumulate, bf16 out, with three fused epilogues (plain / + residual / silu(gate) * up).
+// accumulate, bf16 out, with four fused epilogues (plain / + residual / silu(gate) * up / rotary embedding of Q and K).
 //
 // Orientation.  Both operands are contiguous along k, which is exactly what the two register
 // operands of v_mfma_f32_16x16x32_bf16 want (lane (r, kg) holds 8 consecutive k of row r).  The
