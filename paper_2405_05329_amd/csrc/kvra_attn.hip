@@ -1335,7 +1335,8 @@ bool attn_scratch_in_use(int64_t prefix_len, int64_t chunk_len, int n_q_heads, i
   float* const p = device_scratch(stream, &cus, &slots);
   AttnPlan plan;
   if (p == nullptr || cached_plan(prefix_len, chunk_len, n_q_heads, n_kv_heads, head_dim, cus, true, &plan) != KVRA_OK ||
-      plan.partial_pieces == 0)
+      plan.partial_pieces == 0 || plan.scratch_slots > slots ||
+      rows_splits(plan, prefix_len, chunk_len, n_q_heads, n_kv_heads, head_dim, cus, slots * attn_partial_bytes(128)) == 1)
     return false;
   *shared = SharedScratch{p, slots * attn_partial_bytes(128), reinterpret_cast<int*>(p + static_cast<size_t>(slots) * kPartialFloats(128)),
                           kCounterInts};

@@ -12,9 +12,9 @@ from paper_2405_05329_amd import kvra, synth
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("m,ffn", [(77, 11008), (250, 11008), (333, 11072), (500, 8256), (1000, 11008)])
-def test_layer_with_a_split_down_projection(m, ffn):
-    hidden, H, Hkv, d, prefix, scale = 4096, 8, 8, 128, 2048, synth.default_scale(128)
+@pytest.mark.parametrize("m,ffn,H", [(77, 11008, 8), (250, 11008, 8), (333, 11072, 8), (500, 8256, 8), (1000, 11008, 32)])
+def test_layer_with_a_split_down_projection(m, ffn, H):
+    hidden, Hkv, d, prefix, scale = 4096, H, 128, 2048, synth.default_scale(128)
     gen = torch.Generator(device="cuda")
     gen.manual_seed(m)
 
@@ -29,6 +29,7 @@ def test_layer_with_a_split_down_projection(m, ffn):
     kc, vc = normal(prefix + m, Hkv, d), normal(prefix + m, Hkv, d)
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     assert kvra.kvra_chunk_attn_plan(prefix, m, H, Hkv, d, cus)["partial_pieces"] > 0
+    assert kvra.kvra_chunk_attn_row_splits(prefix, m, H, Hkv, d, cus) != 1   # the attention uses the scratch
     nbytes = kvra.kvra_layer_workspace_bytes(layer, m)
     ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
     ys = []
