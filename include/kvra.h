@@ -12,7 +12,9 @@
  *   - Tensors are dense, token-major: [tokens, heads, head_dim], head_dim contiguous.
  *   - `stream` is a hipStream_t passed as void* (NULL = the default stream).  GPU entry points
  *     only enqueue work on it and return; they never synchronise.
- *   - Return value: KVRA_OK, or a negative code; on error nothing was enqueued.
+ *   - Return value: KVRA_OK, or a negative code; on error nothing was enqueued.  (One exception: where a call is
+ *     several launches - kvra_layer_chunk, and kvra_linear on long inputs - and the HIP runtime refuses to launch a
+ *     later one, KVRA_ELAUNCH comes back with the earlier ones enqueued.)
  *   - head_dim must be 64 or 128; n_q_heads must be a multiple of n_kv_heads; query head h
  *     reads key/value head h / (n_q_heads / n_kv_heads).
  *   - The only state the library keeps is one scratch buffer per device (about 100 MB, hipMalloc'ed

@@ -877,20 +877,27 @@ __global__ __launch_bounds__(64 * WAVES, NORM ? (TB > 1 ? 4 : 8) : WAVES / 4) vo
 namespace {
 
 template <class T>
+auto tile_kernel(const GemmArgs& a) -> void (*)(GemmArgs) {
+  if constexpr (T::TN * T::TM <= 128 * 256) {   // (few tokens do not get the larger ones)
+    if (a.stagger != 0) return a.rope != 0 ? linear_kernel<T, true, false, true> : linear_kernel<T, false, false, true>;
+  }
+  return a.rope != 0 ? linear_kernel<T, true, false, false> : linear_kernel<T, false, false, false>;
+}
+
+// Whatever the runtime may refuse before a launch: asked for ahead where a call is two launches, so that it enqueues both or none.
+template <class T>
+bool tile_ready(const GemmArgs& a) {
+  return T::LDS <= 64 * 1024 || grant_lds(reinterpret_cast<const void*>(tile_kernel<T>(a)), T::LDS);
+}
+
+template <class T>
 int launch_tile(GemmArgs& a, hipStream_t stream) {
   a.tiles_n = (a.n + T::TN - 1) / T::TN;
   a.tiles_m = (a.m + T::TM - 1) / T::TM;
   const int per = (a.tiles_n * a.tiles_m + 7) / 8;
   constexpr int PER_CU = T::PER_SIMD * 4 / T::NW;
   const unsigned grid = 8u * static_cast<unsigned>(std::min(per, 32 * PER_CU));
-  const dim3 g(grid), b(T::THREADS);
-  if constexpr (T::TN * T::TM <= 128 * 256) {   // (few tokens do not get the larger ones)
-    if (a.stagger != 0)
-      return a.rope != 0 ? launch_kernel(linear_kernel<T, true, false, true>, g, b, a, stream, T::LDS)
-                         : launch_kernel(linear_kernel<T, false, false, true>, g, b, a, stream, T::LDS);
-  }
-  return a.rope != 0 ? launch_kernel(linear_kernel<T, true, false, false>, g, b, a, stream, T::LDS)
-                     : launch_kernel(linear_kernel<T, false, false, false>, g, b, a, stream, T::LDS);
+  return launch_kernel(tile_kernel<T>(a), dim3(grid), dim3(T::THREADS), a, stream, T::LDS);
 }
 
 // a.splits workgroups per tile, all of them in one round
@@ -931,25 +938,30 @@ struct TileChoice {
   bool dual;
   float fixed, per_round, step, step_full;
   int (*launch)(GemmArgs&, hipStream_t);
-  int (*split)(GemmArgs&, hipStream_t) = nullptr;
+  bool (*ready)(const GemmArgs&);
+  int (*split)(GemmArgs&, hipStream_t);   // nullptr: none
 };
 
+template <class T, bool SPLIT = false>
+constexpr TileChoice choice(int per_cu, bool dual, float fixed, float per_round, float step, float step_full) {
+  TileChoice c = {T::TN, T::TM, T::TK, per_cu, dual, fixed, per_round, step, step_full, launch_tile<T>, tile_ready<T>, nullptr};
+  if constexpr (SPLIT) c.split = launch_split<T>;
+  return c;
+}
+
 const TileChoice kTiles[] = {
-    {256, 256, 64, 1, true, 6.59f, 0.00f, 1.245f, 0.208f, launch_tile<GemmTile<256, 256, 64, 2, 4, 2, 1, 2>>},
-    {256, 192, 64, 1, true, 5.44f, 0.00f, 1.084f, 0.137f, launch_tile<GemmTile<256, 192, 64, 2, 4, 2, 1, 2>>},
-    {192, 256, 64, 1, false, 5.84f, 0.00f, 1.012f, 0.202f, launch_tile<GemmTile<192, 256, 64, 2, 2, 4, 1, 2>>},
-    {192, 192, 64, 1, true, 3.76f, 1.97f, 0.714f, 0.173f, launch_tile<GemmTile<192, 192, 64, 3, 3, 4, 1, 3>>},
-    {128, 256, 64, 1, true, 4.29f, 1.28f, 0.679f, 0.155f, launch_tile<GemmTile<128, 256, 64, 3, 2, 4, 1, 2>>,
-     launch_split<GemmTile<128, 256, 64, 3, 2, 4, 1, 2>>},
-    {128, 192, 64, 1, true, 4.04f, 0.83f, 0.536f, 0.155f, launch_tile<GemmTile<128, 192, 64, 4, 2, 4, 1, 2>>},
-    {128, 128, 64, 1, true, 4.73f, 0.00f, 0.420f, 0.106f, launch_tile<GemmTile<128, 128, 64, 5, 2, 4, 1, 2, true>>,
-     launch_split<GemmTile<128, 128, 64, 5, 2, 4, 1, 2, true>>},
-    {64, 128, 64, 1, true, 3.51f, 0.85f, 0.303f, 0.042f, launch_tile<GemmTile<64, 128, 64, 6, 1, 8, 1, 2, true>>,
-     launch_split<GemmTile<64, 128, 64, 6, 1, 8, 1, 2, true>>},
-    {64, 64, 64, 2, true, 4.16f, 0.00f, 0.241f, 0.205f, launch_tile<GemmTile<64, 64, 64, 5, 1, 4, 1, 2, true>>},
-    {64, 64, 128, 1, true, 3.48f, 0.89f, 0.179f, 0.029f, launch_tile<GemmTile<64, 64, 128, 4, 2, 2, 2, 2, true>>},
-    {32, 64, 128, 1, true, 3.32f, 0.79f, 0.137f, 0.023f, launch_tile<GemmTile<32, 64, 128, 5, 1, 4, 2, 2, true>>},
-    {32, 32, 128, 1, true, 3.28f, 0.78f, 0.112f, 0.001f, launch_tile<GemmTile<32, 32, 128, 8, 1, 2, 4, 2, true>>},
+    choice<GemmTile<256, 256, 64, 2, 4, 2, 1, 2>>(1, true, 6.59f, 0.00f, 1.245f, 0.208f),
+    choice<GemmTile<256, 192, 64, 2, 4, 2, 1, 2>>(1, true, 5.44f, 0.00f, 1.084f, 0.137f),
+    choice<GemmTile<192, 256, 64, 2, 2, 4, 1, 2>>(1, false, 5.84f, 0.00f, 1.012f, 0.202f),
+    choice<GemmTile<192, 192, 64, 3, 3, 4, 1, 3>>(1, true, 3.76f, 1.97f, 0.714f, 0.173f),
+    choice<GemmTile<128, 256, 64, 3, 2, 4, 1, 2>, true>(1, true, 4.29f, 1.28f, 0.679f, 0.155f),
+    choice<GemmTile<128, 192, 64, 4, 2, 4, 1, 2>>(1, true, 4.04f, 0.83f, 0.536f, 0.155f),
+    choice<GemmTile<128, 128, 64, 5, 2, 4, 1, 2, true>, true>(1, true, 4.73f, 0.00f, 0.420f, 0.106f),
+    choice<GemmTile<64, 128, 64, 6, 1, 8, 1, 2, true>, true>(1, true, 3.51f, 0.85f, 0.303f, 0.042f),
+    choice<GemmTile<64, 64, 64, 5, 1, 4, 1, 2, true>>(2, true, 4.16f, 0.00f, 0.241f, 0.205f),
+    choice<GemmTile<64, 64, 128, 4, 2, 2, 2, 2, true>>(1, true, 3.48f, 0.89f, 0.179f, 0.029f),
+    choice<GemmTile<32, 64, 128, 5, 1, 4, 2, 2, true>>(1, true, 3.32f, 0.79f, 0.137f, 0.023f),
+    choice<GemmTile<32, 32, 128, 8, 1, 2, 4, 2, true>>(1, true, 3.28f, 0.78f, 0.112f, 0.001f),
 };
 
 int64_t tiles_per_xcd(const TileChoice& c, const GemmArgs& a) {   // 64 bits: the query takes sizes that no memory holds
@@ -1151,6 +1163,7 @@ int launch_linear(const void* x, const void* w, const void* w2, const void* resi
   if (a.dual) rest.w2 += static_cast<int64_t>(columns) * k;
   if (rest.res != nullptr) rest.res += columns;
   rest.seg[0].ptr += columns;
+  if (!two.first->ready(a) || !two.second->ready(rest)) return KVRA_ELAUNCH;   // neither goes out
   const int rc = two.first->launch(a, stream);
   return rc != KVRA_OK ? rc : two.second->launch(rest, stream);
 }
