@@ -60,8 +60,12 @@ int chunk_attn_checked(const void* q, const void* k_cache, const void* v_cache,
   int rc = check_heads(n_q_heads, n_kv_heads, head_dim);
   if (rc != KVRA_OK) return rc;
   if (chunk_len > kMaxTokens || prefix_len > kMaxTokens) return KVRA_EUNSUPPORTED;
-  return kvra::launch_chunk_attn(q, k_cache, v_cache, prefix_len, chunk_len, n_q_heads, n_kv_heads,
-                                 head_dim, scale, out, static_cast<hipStream_t>(stream), static_scratch_only);
+  kvra::AttnLaunch launch;
+  rc = kvra::prepare_chunk_attn(prefix_len, chunk_len, n_q_heads, n_kv_heads, head_dim, static_cast<hipStream_t>(stream),
+                                static_scratch_only, &launch);
+  if (rc != KVRA_OK) return rc;
+  return kvra::launch_chunk_attn(launch, q, k_cache, v_cache, prefix_len, chunk_len, n_q_heads, n_kv_heads, head_dim, scale, out,
+                                 static_cast<hipStream_t>(stream));
 }
 
 }  // namespace
@@ -263,6 +267,9 @@ extern "C" int kvra_layer_chunk(const kvra_layer* L, const void* x, void* y, voi
   char* ws = static_cast<char*>(workspace);
   void *h = ws + w.h, *q = ws + w.q, *k = ws + w.k, *attn = ws + w.attn, *x2 = ws + w.x2, *act = ws + w.act;
   const hipStream_t st = static_cast<hipStream_t>(stream);
+  // what the attention may be refused for comes before the first launch, too
+  kvra::AttnLaunch attention;
+  if ((rc = kvra::prepare_chunk_attn(prefix_len, c, L->n_q_heads, L->n_kv_heads, L->head_dim, st, false, &attention)) != KVRA_OK) return rc;
   const int64_t kvd = static_cast<int64_t>(L->n_kv_heads) * L->head_dim;
   // The projection rotates Q and K and puts K and V into their cache rows; the angles stand where an unrotated K and V would
   // have been: chunk_len * head_dim floats, at most the room of one KV head's K and V.
@@ -271,12 +278,11 @@ extern "C" int kvra_layer_chunk(const kvra_layer* L, const void* x, void* y, voi
   if ((rc = kvra::launch_norm_qkv_append(x, L->norm1, L->rms_eps, h, static_cast<float*>(k), L->wqkv, outs, cols, prefix_len,
                                          L->rope_base, L->head_dim, c, L->hidden, st)) != KVRA_OK)
     return rc;
-  if ((rc = kvra_chunk_attn(q, k_cache, v_cache, prefix_len, c, L->n_q_heads, L->n_kv_heads, L->head_dim,
-                            L->scale, attn, stream)) != KVRA_OK) return rc;
+  if ((rc = kvra::launch_chunk_attn(attention, q, k_cache, v_cache, prefix_len, c, L->n_q_heads, L->n_kv_heads, L->head_dim,
+                                    L->scale, attn, st)) != KVRA_OK)
+    return rc;
   // Calls whose attention is in no need of the scratch may overlap with others on other streams: their projections keep off it too.
-  kvra::SharedScratch scratch;
-  const kvra::SharedScratch* const shared =
-      kvra::attn_scratch_in_use(prefix_len, c, L->n_q_heads, L->n_kv_heads, L->head_dim, st, &scratch) ? &scratch : nullptr;
+  const kvra::SharedScratch* const shared = attention.scratch.data != nullptr ? &attention.scratch : nullptr;
   const int hidden_cols[1] = {L->hidden};
   if ((rc = kvra::launch_linear(attn, L->wo, nullptr, x, &x2, hidden_cols, 1, c, L->hidden, hd, st, shared)) != KVRA_OK) return rc;
   if ((rc = kvra::launch_norm_swiglu(x2, L->norm2, L->rms_eps, h, L->w_gate, L->w_up, act, c, L->ffn, L->hidden, st)) != KVRA_OK)

@@ -1328,24 +1328,8 @@ int attn_row_splits(int64_t prefix_len, int64_t chunk_len, int n_q_heads, int n_
   return KVRA_OK;
 }
 
-bool attn_scratch_in_use(int64_t prefix_len, int64_t chunk_len, int n_q_heads, int n_kv_heads, int head_dim, hipStream_t stream,
-                         SharedScratch* shared) {
-  int cus = 0;
-  int64_t slots = 0;
-  float* const p = device_scratch(stream, &cus, &slots);
-  AttnPlan plan;
-  if (p == nullptr || cached_plan(prefix_len, chunk_len, n_q_heads, n_kv_heads, head_dim, cus, true, &plan) != KVRA_OK ||
-      plan.partial_pieces == 0 || plan.scratch_slots > slots ||
-      rows_splits(plan, prefix_len, chunk_len, n_q_heads, n_kv_heads, head_dim, cus, slots * attn_partial_bytes(128)) == 1)
-    return false;
-  *shared = SharedScratch{p, slots * attn_partial_bytes(128), reinterpret_cast<int*>(p + static_cast<size_t>(slots) * kPartialFloats(128)),
-                          kCounterInts};
-  return true;
-}
-
-int launch_chunk_attn(const void* q, const void* k_cache, const void* v_cache,
-                      int64_t prefix_len, int64_t chunk_len, int n_q_heads, int n_kv_heads, int head_dim,
-                      float scale, void* out, hipStream_t stream, bool static_scratch_only) {
+int prepare_chunk_attn(int64_t prefix_len, int64_t chunk_len, int n_q_heads, int n_kv_heads, int head_dim, hipStream_t stream,
+                       bool static_scratch_only, AttnLaunch* l) {
   // the scratch buffer is looked up by the current device: a stream of another device would get the wrong one
   if (stream != nullptr) {
     hipDevice_t stream_dev = 0;
@@ -1358,32 +1342,39 @@ int launch_chunk_attn(const void* q, const void* k_cache, const void* v_cache,
   }
   int cus = 0;
   int64_t slots_owned = kStaticSlots;
-  float* scratch_ptr = static_scratch_only ? static_scratch(&cus) : device_scratch(stream, &cus, &slots_owned);
-  if (static_scratch_only && scratch_ptr == nullptr) return KVRA_ENODEVICE;
-  int* const counters = scratch_ptr != nullptr
-      ? reinterpret_cast<int*>(scratch_ptr + static_cast<size_t>(slots_owned) * kPartialFloats(128)) : nullptr;
-  AttnPlan plan;
-  const int rc0 = cached_plan(prefix_len, chunk_len, n_q_heads, n_kv_heads, head_dim, cus, scratch_ptr != nullptr, &plan);
-  if (rc0 != KVRA_OK) return rc0;
-  if (plan.scratch_slots > slots_owned) return KVRA_ESCRATCH;   // only the fixed array can be too small
-  int splits = rows_splits(plan, prefix_len, chunk_len, n_q_heads, n_kv_heads, head_dim, cus,
-                           scratch_ptr != nullptr ? slots_owned * attn_partial_bytes(128) : 0);
+  float* const scratch = static_scratch_only ? static_scratch(&cus) : device_scratch(stream, &cus, &slots_owned);
+  if (static_scratch_only && scratch == nullptr) return KVRA_ENODEVICE;
+  const int rc = cached_plan(prefix_len, chunk_len, n_q_heads, n_kv_heads, head_dim, cus, scratch != nullptr, &l->plan);
+  if (rc != KVRA_OK) return rc;
+  if (l->plan.scratch_slots > slots_owned) return KVRA_ESCRATCH;   // only the fixed array can be too small
+  l->splits = rows_splits(l->plan, prefix_len, chunk_len, n_q_heads, n_kv_heads, head_dim, cus,
+                          scratch != nullptr ? slots_owned * attn_partial_bytes(128) : 0);
 #ifdef KVRA_TRACE
-  if (g_trace_buf != nullptr) splits = 0;   // only the tiled kernel leaves stamps
+  if (g_trace_buf != nullptr) l->splits = 0;   // only the tiled kernel leaves stamps
 #endif
-  if (splits > 0)
-    return launch_attn_rows(q, k_cache, v_cache, prefix_len, chunk_len, n_q_heads, n_kv_heads, head_dim, scale, out, splits,
-                            scratch_ptr, counters, stream);
+  l->scratch = SharedScratch{};
+  if (scratch != nullptr && (l->splits > 0 ? l->splits > 1 : l->plan.partial_pieces > 0))
+    l->scratch = SharedScratch{scratch, slots_owned * attn_partial_bytes(128),
+                               reinterpret_cast<int*>(scratch + static_cast<size_t>(slots_owned) * kPartialFloats(128)), kCounterInts};
+  return KVRA_OK;
+}
+
+int launch_chunk_attn(const AttnLaunch& l, const void* q, const void* k_cache, const void* v_cache,
+                      int64_t prefix_len, int64_t chunk_len, int n_q_heads, int n_kv_heads, int head_dim,
+                      float scale, void* out, hipStream_t stream) {
+  if (l.splits > 0)
+    return launch_attn_rows(q, k_cache, v_cache, prefix_len, chunk_len, n_q_heads, n_kv_heads, head_dim, scale, out, l.splits,
+                            l.scratch.data, l.scratch.counters, stream);
   AttnArgs a;
-  schedule_args(plan, prefix_len, chunk_len, n_q_heads, n_kv_heads, &a);
+  schedule_args(l.plan, prefix_len, chunk_len, n_q_heads, n_kv_heads, &a);
   a.q = static_cast<const __bf16*>(q);
   a.k = static_cast<const __bf16*>(k_cache);
   a.v = static_cast<const __bf16*>(v_cache);
   a.out = static_cast<__bf16*>(out);
   a.c_log2 = scale * 1.4426950408889634f;
-  a.scratch = plan.partial_pieces > 0 ? scratch_ptr : nullptr;
-  a.counters = counters;
-  const int workgroups = plan.groups * plan.slots;
+  a.scratch = l.scratch.data;
+  a.counters = l.scratch.counters;
+  const int workgroups = l.plan.groups * l.plan.slots;
 #ifdef KVRA_TRACE
   a.trace = workgroups <= g_trace_groups ? g_trace_buf : nullptr;
 #endif

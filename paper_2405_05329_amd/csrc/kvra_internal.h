@@ -18,25 +18,12 @@ int launch_append_kv(const void* k_in, const void* v_in, void* q_inout, void* k_
 // base^(-2i/d), i < d/2, in fp64 (64 entries; zeros before the first base > 0): the calling thread's, until its next call.
 const double* rope_frequencies(float rope_base, int head_dim);
 
-int launch_chunk_attn(const void* q, const void* k_cache, const void* v_cache,
-                      int64_t prefix_len, int64_t chunk_len, int n_q_heads, int n_kv_heads, int head_dim,
-                      float scale, void* out, hipStream_t stream, bool static_scratch_only);
 // The kernel for few rows (kvra_attn_rows.hip), `splits` workgroups per slice of 32 virtual rows.  splits > 1 needs scratch:
 // attn_rows_slot_bytes(head_dim) and, zero between launches, one counter per slice (times splits for the slots).
 int launch_attn_rows(const void* q, const void* k_cache, const void* v_cache, int64_t prefix_len, int64_t chunk_len,
                      int n_q_heads, int n_kv_heads, int head_dim, float scale, void* out, int splits, float* scratch,
                      int* counters, hipStream_t stream);
 int64_t attn_rows_slot_bytes(int head_dim);
-// The scratch buffer of the current device, if a kvra_chunk_attn launch of this shape on this stream would use it (what else the
-// same stream does before or after that launch may then use it too): zero counters, put back to zero by whoever counts.
-struct SharedScratch {
-  float* data;
-  int64_t bytes;
-  int* counters;
-  int n_counters;
-};
-bool attn_scratch_in_use(int64_t prefix_len, int64_t chunk_len, int n_q_heads, int n_kv_heads, int head_dim, hipStream_t stream,
-                         SharedScratch* shared);
 int64_t attn_static_scratch_bytes();   // size of the fixed scratch array kvra_chunk_attn_noalloc uses
 
 // Launch shape of kvra_chunk_attn for a device with `cus` compute units (pure host arithmetic).
@@ -74,6 +61,24 @@ struct AttnPlan {
   unsigned fill_seg[kMaxSlots + 1];
   unsigned fill_off[kMaxSlots + 1];
 };
+// Scratch that a launch meets through: partial results, and counters that are zero between launches (put back by whoever counts).
+struct SharedScratch {
+  float* data = nullptr;
+  int64_t bytes = 0;
+  int* counters = nullptr;
+  int n_counters = 0;
+};
+// A kvra_chunk_attn launch, decided (and allowed, its scratch allocated) but not yet enqueued.
+struct AttnLaunch {
+  AttnPlan plan;
+  int splits;              // 0: the tiled kernel with `plan`; else the one for few rows with so many workgroups per slice
+  SharedScratch scratch;   // null if the launch does not use any; where it does, so may what the same call enqueues around it
+};
+int prepare_chunk_attn(int64_t prefix_len, int64_t chunk_len, int n_q_heads, int n_kv_heads, int head_dim, hipStream_t stream,
+                       bool static_scratch_only, AttnLaunch* launch);
+int launch_chunk_attn(const AttnLaunch& launch, const void* q, const void* k_cache, const void* v_cache,
+                      int64_t prefix_len, int64_t chunk_len, int n_q_heads, int n_kv_heads, int head_dim,
+                      float scale, void* out, hipStream_t stream);
 int64_t attn_partial_bytes(int head_dim);   // scratch bytes per partial-result slot
 int64_t attn_counter_bytes();               // scratch bytes of the merge counters, behind the slots
 int plan_chunk_attn(int64_t prefix_len, int64_t chunk_len, int n_q_heads, int n_kv_heads, int head_dim,
