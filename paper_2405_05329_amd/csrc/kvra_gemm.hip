@@ -876,10 +876,47 @@ __global__ __launch_bounds__(64 * WAVES, NORM ? (TB > 1 ? 4 : 8) : WAVES / 4) vo
 
 namespace {
 
+// Stages between the starts of neighbouring weight tiles, 0: all start at the first.  A pass of few tokens over deep rows is bound by
+// the weights' way from memory, and its workgroups walk the rows in step: they ask for the same columns of all rows at a time.
+// Memory is dealt out in pieces of 256 bytes over 128 channels (rows 32 KB apart lie on one), so where that is a few channels only,
+// tiles that start three stages apart and wrap around keep the others busy.  Weights from memory, in step -> apart:
+//   rows a multiple of 4 KB apart: 12288 x 8192, 20 / 77 tokens 44.5 -> 38.4 / 53.9 -> 49.5 us; 22016 x 4096, 77 tokens 47.7 ->
+//   40.9; 16384-deep rows 0.76 to 0.95 of the time; 4096 x 4096 the same;
+//   one, two or three rows within 256 bytes (three: 512 above) of a multiple of 32 KB: 4096 x 11008, 20 / 77 tokens 29.9 -> 27.5 /
+//   33.7 -> 30.4; 12288 x 5504, 20 tokens 35.9 -> 27.8; 12288 x 16320, 20 tokens 121 -> 74.
+// Elsewhere it gains nothing and costs up to a fifth (of all k from 4096 to 18432 in steps of 128: 12288 x 16000, 20 tokens 1.22, 4096 x
+// 16896, 77 tokens 1.17, 12288 x 5120 1.02 of the time), and so does k = 12288 in the 64 x 64 tile with 128-deep stages (1.07 to 1.11,
+// alone among the multiples of 2048).  With fewer weight rows too few workgroups share the memory: at the distances above 256 / 512
+// rows take 0.99 to 1.02 / 0.99 to 1.01 of the time, 1024 0.97 to 1.00.  (Weights that are in the last-level cache gain less and less
+// often: 4096 x 11008 0.92 of the time, most others 0.97 to 1.03.  A model's weights are not, from one use to the next.)  64 x 64 tiles
+// of 64-deep stages with three and more token tiles gain nothing at the multiples of 2048 (and lose up to 1.10 from the cache).
+// From 257 tokens on the tiles that share an operand in the L2 lose more by it (11008 x 4096 SwiGLU, 1000 tokens 166 -> 172).
+// Starts eight stages apart are worse.
+// One more class gains, whatever its rows' distance: a weight larger than the last-level cache (256 MB) whose last token tile is at
+// most five eighths full (the workgroups of that tile read the last token again and again): 12288 x 14080, 144 tokens 135.7 ->
+// 105.6; 200 / 250 tokens 0.99 / 1.00 of the time.
+template <class T>
+int stagger_of(const GemmArgs& a) {
+  if (T::TN * T::TM > 128 * 256 || a.m > 256 || a.k < 4096 || a.n < 1024) return 0;   // (few tokens do not get the larger tiles)
+  const int tiles_m = (a.m + T::TM - 1) / T::TM, apart = static_cast<int>(2ll * a.k % 32768);
+  auto one_channel = [&](int rows, int above) {
+    const int distance = rows * apart % 32768;
+    return distance <= above || distance >= 32768 - 256;
+  };
+  if (a.k % 2048 == 0) {
+    const bool gains = !(T::TN == 64 && T::TM == 64) || (T::TK == 64 ? tiles_m <= 2 : a.k != 12288);
+    if (gains) return 3;
+  } else if (one_channel(1, 256) || one_channel(2, 256) || one_channel(3, 512)) {
+    return 3;
+  }
+  const int in_last = a.m - (tiles_m - 1) * T::TM;
+  return tiles_m > 1 && 8 * in_last <= 5 * T::TM && 2ll * a.n * a.k > 256ll << 20 ? 3 : 0;
+}
+
 template <class T>
 auto tile_kernel(const GemmArgs& a) -> void (*)(GemmArgs) {
-  if constexpr (T::TN * T::TM <= 128 * 256) {   // (few tokens do not get the larger ones)
-    if (a.stagger != 0) return a.rope != 0 ? linear_kernel<T, true, false, true> : linear_kernel<T, false, false, true>;
+  if constexpr (T::TN * T::TM <= 128 * 256) {
+    if (stagger_of<T>(a) != 0) return a.rope != 0 ? linear_kernel<T, true, false, true> : linear_kernel<T, false, false, true>;
   }
   return a.rope != 0 ? linear_kernel<T, true, false, false> : linear_kernel<T, false, false, false>;
 }
@@ -892,6 +929,7 @@ bool tile_ready(const GemmArgs& a) {
 
 template <class T>
 int launch_tile(GemmArgs& a, hipStream_t stream) {
+  a.stagger = stagger_of<T>(a);
   a.tiles_n = (a.n + T::TN - 1) / T::TN;
   a.tiles_m = (a.m + T::TM - 1) / T::TM;
   const int per = (a.tiles_n * a.tiles_m + 7) / 8;
@@ -903,6 +941,7 @@ int launch_tile(GemmArgs& a, hipStream_t stream) {
 // a.splits workgroups per tile, all of them in one round
 template <class T>
 int launch_split(GemmArgs& a, hipStream_t stream) {
+  a.stagger = stagger_of<T>(a);
   a.tiles_n = (a.n + T::TN - 1) / T::TN;
   a.tiles_m = (a.m + T::TM - 1) / T::TM;
   const unsigned pieces = 8u * static_cast<unsigned>((a.tiles_n * a.tiles_m * a.splits + 7) / 8);
@@ -1126,13 +1165,7 @@ void linear_args(const void* x, const void* w, const void* w2, const void* resid
   a.m = static_cast<int>(m);
   a.n = static_cast<int>(a.dual ? 2 * n_out : n_out);
   a.k = static_cast<int>(k);
-  // Few tokens on deep rows is a pass over the weights.  When all workgroups walk the rows in step, they ask for the same columns of
-  // rows that lie a power of two (or nearly) apart, which is only part of the memory channels at a time; weight tiles that start
-  // three stages apart ask for more of them.  Weights from memory, in step -> apart: 4096 x 11008, 40 / 77 / 250 tokens 26.5 ->
-  // 24.6 / 33.0 -> 30.1 / 50.7 -> 49.2 us; 11008 x 4096 SwiGLU, 77 tokens 44.1 -> 42.2; 12288 x 4096 29.0 -> 28.7.  Eight apart is worse
-  // (12288 x 4096, 40 tokens 23.8 -> 29.7), rows of 2048 and less gain nothing, and from 500 tokens on the
-  // tiles that share an operand in the L2 lose more by it (11008 x 4096 SwiGLU, 1000 tokens 166 -> 172).
-  a.stagger = m <= 256 && k >= 4096 ? 3 : 0;
+  a.stagger = 0;   // (for the tile to decide)
 }
 
 }  // namespace

@@ -69,14 +69,22 @@ def layer(hidden, ffn, H, Hkv, d, prefix, m, rope_base=10000.0):
     return {"fn": "layer", "hidden": hidden, "ffn": ffn, "H": H, "Hkv": Hkv, "d": d, "prefix": prefix, "m": m, "rope_base": rope_base}
 
 
-def record(calls, refuse_launch=0, refuse_attribute=0, refuse_malloc=0):
-    with tempfile.TemporaryDirectory() as tmp:
-        src, so = os.path.join(tmp, "stand_in.cpp"), os.path.join(tmp, "stand_in.so")
+_stand_in = {}
+
+
+def _built():
+    if not _stand_in:
+        tmp = _stand_in["folder"] = tempfile.TemporaryDirectory()   # goes with the process
+        src, _stand_in["so"] = os.path.join(tmp.name, "stand_in.cpp"), os.path.join(tmp.name, "stand_in.so")
         with open(src, "w") as f:
             f.write(STAND_IN)
-        subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", src, "-o", so, "-ldl"], check=True)
-        job = {"so": so, "calls": calls, "refuse": [refuse_launch, refuse_attribute, refuse_malloc]}
-        r = subprocess.run([sys.executable, os.path.abspath(__file__)], input=json.dumps(job), capture_output=True, text=True, timeout=120)
+        subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", src, "-o", _stand_in["so"], "-ldl"], check=True)
+    return _stand_in["so"]
+
+
+def record(calls, refuse_launch=0, refuse_attribute=0, refuse_malloc=0):
+    job = {"so": _built(), "calls": calls, "refuse": [refuse_launch, refuse_attribute, refuse_malloc]}
+    r = subprocess.run([sys.executable, os.path.abspath(__file__)], input=json.dumps(job), capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stderr[-2000:]
     return json.loads(r.stdout)
 

@@ -85,3 +85,18 @@ def test_layer_against_its_operators(m, H, Hkv, d, hidden, tile, rope_base):
         assert rel <= bar and worst <= 0.05, f"{label}: {rel:.2e}, worst element {worst:.3f}"
     rel, worst = _rel(y, want)
     assert rel <= 1.2e-2, f"y: {rel:.2e}"
+
+
+# weight tiles that start along k apart: every tile up to 256 tokens, with stages of 64 and 128 and odd numbers of them
+STARTS_APART = [
+    (20, 30, 5, 64, 4096, (32, 32, 128)), (33, 6, 1, 128, 5504, (32, 32, 128)), (33, 60, 15, 64, 5504, (32, 64, 128)),
+    (33, 25, 5, 128, 4096, (32, 64, 128)), (33, 14, 1, 64, 5440, (64, 64, 64)), (33, 6, 1, 128, 5440, (64, 64, 64)),
+    (193, 25, 5, 64, 4096, (64, 64, 128)), (20, 32, 32, 128, 5504, (64, 64, 128)), (193, 60, 15, 64, 5504, (64, 128, 64)),
+    (77, 32, 32, 128, 4096, (64, 128, 64)), (129, 140, 28, 64, 5504, (128, 128, 64)), (129, 32, 32, 128, 4096, (128, 128, 64)),
+]
+
+
+@pytest.mark.parametrize("m,H,Hkv,d,hidden,tile", STARTS_APART)
+def test_layer_whose_projection_starts_its_tiles_apart(m, H, Hkv, d, hidden, tile):
+    """(That these calls get that form is asserted in tests/test_launches.py, by the same list.)"""
+    test_layer_against_its_operators(m, H, Hkv, d, hidden, tile, synth.ROPE_BASE)

@@ -61,8 +61,23 @@ def test_tiles_in_turn(m, n, k, mode, tile):
     (129, 8608, 4096, "swiglu", (128, 192, 64, 1)),
 ])
 def test_weight_tiles_that_start_apart(m, n, k, mode, tile):
-    """Up to 256 tokens on rows of 4096 and more, where every weight tile starts its walk along k elsewhere and wraps around:
-    stages of 64 and 128, an odd number of them, several tiles per workgroup."""
+    """Up to 256 tokens on rows of 4096 and more: the range in which weight tiles may start their walk along k apart (those of 4096
+    do, the others' rows lie on many memory channels)."""
+    assert kvra.kvra_linear_tile(m, n, k, mode == "swiglu") == tile
+    check_linear(m, n, k, mode)
+
+
+STARTS_APART = [
+    (26, 1024, 5504, "plain", (32, 32, 128, 1)), (35, 1024, 5440, "swiglu", (64, 64, 64, 1)), (33, 4192, 5504, "residual", (32, 64, 128, 1)),
+    (67, 8224, 5504, "swiglu", (128, 128, 64, 1)), (100, 12288, 5504, "plain", (64, 128, 64, 1)),
+    (200, 11008, 4096, "swiglu", (128, 256, 64, 1)), (256, 1056, 16320, "residual", (64, 64, 64, 1)),
+]
+
+
+@pytest.mark.parametrize("m,n,k,mode,tile", STARTS_APART)
+def test_weight_tiles_that_do_start_apart(m, n, k, mode, tile):
+    """Every weight tile starts its walk along k elsewhere and wraps around: stages of 64 and 128, an odd number of them.  (That
+    these calls get that form is asserted in tests/test_launches.py, by the same list.)"""
     assert kvra.kvra_linear_tile(m, n, k, mode == "swiglu") == tile
     check_linear(m, n, k, mode)
 

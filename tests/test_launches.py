@@ -1,8 +1,18 @@
 """What the calls enqueue, read off a stand-in for the HIP runtime (launch_recorder.py): no GPU."""
+import re
+
 import pytest
 
+import test_gpu_layer_append
+import test_gpu_linear_tiles
 from paper_2405_05329_amd import kvra
 from launch_recorder import layer, linear, record
+
+
+def _ring(kernel):
+    """(tile, rotates, k shared out, starts apart) of a launch of the ring kernel, else None."""
+    m = re.match(r"void kvra::linear_kernel<kvra::GemmTile<([^>]*)>, (\w+), (\w+), (\w+)>", kernel)
+    return m and (tuple(int(x) for x in m[1].split(",")[:3]), *(x == "true" for x in m.groups()[1:]))
 
 
 TWO = [(1355, 10912, 1024, "swiglu"), (776, 9984, 2048, "swiglu"), (787, 9824, 8192, "residual"), (982, 8256, 8192, "plain")]
@@ -17,7 +27,8 @@ def test_a_linear_call_in_two_launches_enqueues_both_or_none(shape):
 
 
 def _split(kernel):
-    return kernel.startswith("void kvra::linear_kernel<") and kernel.split(">")[1].split(",")[2].strip() == "true"
+    ring = _ring(kernel)
+    return ring is not None and ring[2]
 
 
 def _attention_uses_scratch(prefix, m, H, Hkv, d, cus=256):
@@ -47,3 +58,34 @@ def test_projections_keep_off_a_scratch_that_the_attention_was_refused():
     assert _attention_uses_scratch(5824, 77, 32, 32, 128)
     r, = record([layer(4096, 11008, 32, 32, 128, 5824, 77)], refuse_malloc=1)
     assert r["rc"] == kvra.KVRA_OK and not any(_split(x["kernel"]) for x in r["launches"])
+
+
+@pytest.mark.parametrize("m,n,k,mode,apart", [
+    # rows a multiple of 4 KB apart, one or three rows within 256 (512 above) of a multiple of 32 KB
+    (20, 12288, 8192, "plain", True), (77, 11008, 4096, "swiglu", True), (77, 4096, 11008, "residual", True),
+    (40, 4096, 5440, "plain", True), (256, 4096, 16320, "plain", True), (20, 4096, 16384, "plain", True),
+    (60, 4096, 8128, "plain", True),
+    # rows that lie on many channels: nothing to gain, and up to a fifth to lose
+    (20, 12288, 16000, "plain", False), (77, 4096, 16896, "plain", False), (77, 4544, 4544, "residual", False),
+    (160, 6144, 5120, "plain", False), (20, 12288, 8064, "plain", False), (77, 4096, 10752, "plain", False),
+    # the edges: tokens, depth, weight rows
+    (257, 4096, 4096, "plain", False), (20, 4096, 3968, "plain", False), (20, 1024, 8192, "plain", True), (20, 992, 8192, "plain", False),
+    (20, 512, 8192, "swiglu", True), (20, 480, 8192, "swiglu", False),
+    # forms of the 64 x 64 tiles
+    (20, 12288, 12288, "plain", False), (20, 12288, 24576, "plain", True), (160, 6144, 6144, "plain", False), (77, 10240, 6144, "plain", True),
+    # weights beyond the last-level cache and a last token tile that is at most five eighths full
+    (144, 12288, 13312, "plain", True), (208, 12288, 13312, "plain", True), (209, 12288, 13312, "plain", False),
+    (144, 11264, 11776, "plain", False), (128, 12288, 13312, "plain", False),
+])
+def test_weight_tiles_start_apart_where_rows_lie_on_few_memory_channels(m, n, k, mode, apart):
+    r, = record([linear(m, n, k, mode)])
+    assert r["rc"] == kvra.KVRA_OK and [_ring(x["kernel"])[3] for x in r["launches"]] == [apart]
+
+
+def test_the_gpu_tests_of_tiles_that_start_apart_meet_them():
+    shapes = test_gpu_linear_tiles.STARTS_APART
+    for shape, r in zip(shapes, record([linear(*s[:4]) for s in shapes])):
+        assert [_ring(x["kernel"]) for x in r["launches"]] == [(shape[4][:3], False, False, True)], shape
+    shapes = test_gpu_layer_append.STARTS_APART
+    for shape, r in zip(shapes, record([layer(hidden, 128, H, Hkv, d, 37, m) for m, H, Hkv, d, hidden, _ in shapes])):
+        assert (shape[5], True, False, True) in [_ring(x["kernel"]) for x in r["launches"]], shape
