@@ -639,9 +639,13 @@ __global__ __launch_bounds__(T::THREADS, T::PER_SIMD) void linear_kernel(GemmArg
 // 22.9), two sets of four or of two chunks in turn (24.8, 22.1; 12288 x 4096 19.5 -> 26, 23); lanes without a token asking for
 // nothing (no difference); rows as whole 1 KiB loads with fp32 multiply-adds on the vector ALU (29.1, and slower with every
 // further token).
-// Waves: 16 where a row holds at least four chunks for each of them, else 8 (one token, 8 -> 16 waves: 12288 x 4096 19.5 ->
-// 18.2 us, 5.5 TB/s; 11008 x 4096 SwiGLU 34.4 -> 32.1, 5.6; 4096 x 11008 22.2 -> 21.6; 2048 x 5632 10.0 -> 9.5; but 1024 x 2816
-// 5.1 -> 5.3, 2816 x 1024 SwiGLU 4.6 -> 4.8).
+// Waves: 16 where a row holds at least four chunks for each of them and there are 512 weight rows, else 8 (one token, 8 -> 16 waves:
+// 12288 x 4096 19.5 -> 18.2 us, 5.5 TB/s; 11008 x 4096 SwiGLU 34.4 -> 32.1, 5.6; 4096 x 11008 22.2 -> 21.6; 2048 x 5632 10.0 -> 9.5;
+// but 1024 x 2816 5.1 -> 5.3, 2816 x 1024 SwiGLU 4.6 -> 4.8).  The second eight cost a launch 0.15 us; what they gain is requests
+// under way to memory.  Time with 16 over time with 8, 1 to 16 tokens on 4096 / 4544 / 5632 / 8192 / 11008 columns, weights from
+// memory: 256 rows 1.02 / 0.99 / 1.02 / 1.01 / 0.99, 512 1.02 / 0.94 / 0.96 / 1.00 / 0.98, 1024 1.00 / 0.93 / 0.95 / 1.00 / 0.97,
+// 2048 0.98 / 0.92 / 0.94 / 0.97 / 0.95, 4096 and more 0.88 to 0.95.  (From the last-level cache they pay from 5632 rows on: 0.90 to 1.00;
+// fewer 0.91 to 1.03.  A model's weights are not there when they are used again.)
 // NORM: the tokens come before their RMSNorm; the waves add up the squares of the chunks they multiply anyway, and the norm launch
 // and the wait behind it go.  Up to 16 tokens x * gain is what is multiplied, and the factor 1 / rms, which belongs to a token, is
 // applied to the sums: as many roundings as with a norm of its own (x * gain instead of x * gain / rms).  Few registers, so that
@@ -959,7 +963,7 @@ int launch_rows(Args& a, hipStream_t stream) {
       return launch_kernel(linear_rows_kernel<KIND, NORM, 16, 2, 2>, grid, dim3(1024), a, stream);
     }
   }
-  if (a.k >= 4096) return launch_kernel(linear_rows_kernel<KIND, NORM, 16, 1, 1>, dim3(blocks), dim3(1024), a, stream);
+  if (a.k >= 4096 && a.n >= 512) return launch_kernel(linear_rows_kernel<KIND, NORM, 16, 1, 1>, dim3(blocks), dim3(1024), a, stream);
   return launch_kernel(linear_rows_kernel<KIND, NORM, 8, 1, 1>, dim3(blocks), dim3(512), a, stream);
 }
 

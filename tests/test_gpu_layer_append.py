@@ -100,3 +100,13 @@ STARTS_APART = [
 def test_layer_whose_projection_starts_its_tiles_apart(m, H, Hkv, d, hidden, tile):
     """(That these calls get that form is asserted in tests/test_launches.py, by the same list.)"""
     test_layer_against_its_operators(m, H, Hkv, d, hidden, tile, synth.ROPE_BASE)
+
+
+# few tokens on deep rows and enough of them: the norm inside, 16 waves (below 1024 rows, as above, 8)
+SIXTEEN_WAVES = [(1, 14, 1, 64, 4160), (16, 6, 1, 128, 4096), (5, 20, 5, 64, 5504)]
+
+
+@pytest.mark.parametrize("m,H,Hkv,d,hidden", SIXTEEN_WAVES)
+@pytest.mark.parametrize("rope_base", [synth.ROPE_BASE, 0.0])
+def test_layer_whose_projection_takes_sixteen_waves(m, H, Hkv, d, hidden, rope_base):
+    test_layer_against_its_operators(m, H, Hkv, d, hidden, (16, 16, 0), rope_base)

@@ -124,3 +124,12 @@ def check_linear(m, n, k, mode):
     err = np.abs(got[pad:pad + m] - want)
     worst = np.max(err - (2.0 ** -8 * np.abs(want) + 1e-4))
     assert worst <= 0, f"{mode} {m}x{n}x{k}: exceeds the one-rounding bound by {worst:.3e} (max err {err.max():.3e})"
+
+
+SIXTEEN_WAVES = [(1, 1024, 4096, "plain"), (16, 1056, 5632, "residual"), (3, 544, 4608, "swiglu"), (8, 12288, 4160, "plain")]
+
+
+@pytest.mark.parametrize("m,n,k,mode", SIXTEEN_WAVES)
+def test_few_tokens_on_many_deep_rows(m, n, k, mode):
+    """The direct kernel with 16 waves: chunks that come out even over them and ones that do not."""
+    check_linear(m, n, k, mode)

@@ -89,3 +89,24 @@ def test_the_gpu_tests_of_tiles_that_start_apart_meet_them():
     shapes = test_gpu_layer_append.STARTS_APART
     for shape, r in zip(shapes, record([layer(hidden, 128, H, Hkv, d, 37, m) for m, H, Hkv, d, hidden, _ in shapes])):
         assert (shape[5], True, False, True) in [_ring(x["kernel"]) for x in r["launches"]], shape
+
+
+def _waves(launch):
+    return launch["block"][0] // 64 if "linear_rows_kernel" in launch["kernel"] else None
+
+
+@pytest.mark.parametrize("m,n,k,mode,waves", [
+    (1, 512, 4096, "plain", 16), (1, 480, 4096, "plain", 8), (1, 1024, 4032, "plain", 8), (16, 512, 11008, "residual", 16),
+    (16, 64, 11008, "residual", 8), (4, 256, 4096, "swiglu", 16), (4, 224, 4096, "swiglu", 8), (8, 12288, 4096, "plain", 16),
+])
+def test_deep_rows_get_sixteen_waves_where_there_are_enough_of_them(m, n, k, mode, waves):
+    r, = record([linear(m, n, k, mode)])
+    assert r["rc"] == kvra.KVRA_OK and [_waves(x) for x in r["launches"]] == [waves]
+
+
+def test_the_gpu_tests_of_sixteen_waves_meet_them():
+    assert [[_waves(x) for x in r["launches"]] for r in record([linear(*s) for s in test_gpu_linear_tiles.SIXTEEN_WAVES])] == \
+        [[16]] * len(test_gpu_linear_tiles.SIXTEEN_WAVES)
+    for shape, r in zip(test_gpu_layer_append.SIXTEEN_WAVES,
+                        record([layer(hidden, 128, H, Hkv, d, 37, m) for m, H, Hkv, d, hidden in test_gpu_layer_append.SIXTEEN_WAVES])):
+        assert _waves(r["launches"][0]) == 16 and "(kvra::RowsKind)2, true" in r["launches"][0]["kernel"], shape
