@@ -5,6 +5,7 @@ import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -64,24 +65,26 @@ def build(verbose: bool = False, extra_flags=(), trace: bool = False) -> str:
     return lib
 
 
-CALL_EXT = os.path.join(PKG, "_kvra_call.so")
+def binding_path() -> str:
+    """Where the native module of the per-chunk calls for this Python and torch lies (kvra.py loads it if it is there)."""
+    import torch
+    return os.path.join(PKG, f"_kvra_call.torch-{torch.__version__}{sysconfig.get_config_var('EXT_SUFFIX')}")
 
 
 def build_binding() -> str:
-    """_kvra_call.so: the argument marshalling of the per-chunk calls (host code only)."""
-    import sysconfig
-
+    """The argument marshalling of the per-chunk calls (host code only)."""
     import torch
     root = os.path.dirname(torch.__file__)
     cxx = shutil.which("g++") or "c++"
+    out = binding_path()
     cmd = [cxx, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-fvisibility=hidden",
            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
            "-I", os.path.join(ROOT, "include"), "-I", sysconfig.get_paths()["include"],
            "-isystem", os.path.join(root, "include"), "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"),
-           os.path.join(CSRC, "kvra_binding.cpp"), "-o", CALL_EXT,
+           os.path.join(CSRC, "kvra_binding.cpp"), "-o", out,
            "-L", os.path.join(root, "lib"), "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10"]
     subprocess.run(cmd, check=True)
-    return CALL_EXT
+    return out
 
 
 PROBE_LIB = os.path.join(PKG, "libkvra_probe.so")

@@ -2,7 +2,8 @@
 // tensors (three method calls each) and 0.6 us on the call itself, of 4.7 to 5.0 us in all; with two calls per chunk and a GPU
 // that needs 4 us for each, that is what a short prompt waits for.  Here the same checks and conversions read the tensor
 // object directly.  What is not a plain tensor, None or an int goes through the Python function that does the same
-// (kvra._ptr), so that subclasses and look-alikes are treated as before.
+// (kvra._ptr), so that subclasses and look-alikes are treated as before.  The module is tied to the torch and the Python it is
+// compiled against; kvra.py does without it where there is none for those in use.
 //
 // Before -> after: kvra_append_kv 4.95 -> 2.72 us, kvra_chunk_attn 4.72 -> 2.72 us (2.5 of them in the runtime).
 #define PY_SSIZE_T_CLEAN

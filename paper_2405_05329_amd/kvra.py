@@ -1,15 +1,19 @@
-"""Binding of libkvra: the same entry points as include/kvra.h, argument marshalling only (ctypes; the calls a program makes
-per chunk through a small native module, csrc/kvra_binding.cpp, which does the same with less ado).
+"""Binding of libkvra: the same entry points as include/kvra.h, argument marshalling only.  That is ctypes; the calls a program
+makes per chunk go through a small native module where there is one built for this Python and torch (csrc/kvra_binding.cpp), which
+does the same in less time.
 
 Tensor arguments may be torch tensors (their data_ptr() is passed; they must live on the GPU and
 be contiguous) or plain integer device addresses.  Every step of the path runs inside the library's
-HIP kernels; there is no Python or CPU fallback: if either shared library is missing, importing this
-module raises.
+HIP kernels; there is no Python or CPU fallback: if libkvra.so is missing, importing this module raises.
 """
 from __future__ import annotations
 
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
+
+from .build import binding_path
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "libkvra.so")
@@ -141,14 +145,54 @@ def _stream(stream):
     return stream.cuda_stream     # torch.cuda.Stream
 
 
+class _CtypesCalls:
+    """The calls of csrc/kvra_binding.cpp, with the same arguments, through ctypes."""
+
+    @staticmethod
+    def append_kv(k_in, v_in, q_inout, k_cache, v_cache, prefix_len, chunk_len, capacity, n_q_heads, n_kv_heads, head_dim,
+                  rope_base, stream):
+        return _lib.kvra_append_kv(_ptr(k_in), _ptr(v_in), _ptr(q_inout), _ptr(k_cache), _ptr(v_cache), int(prefix_len),
+                                   int(chunk_len), int(capacity), int(n_q_heads), int(n_kv_heads), int(head_dim),
+                                   float(rope_base), _stream(stream))
+
+    @staticmethod
+    def chunk_attn(q, k_cache, v_cache, prefix_len, chunk_len, n_q_heads, n_kv_heads, head_dim, scale, out, stream):
+        return _lib.kvra_chunk_attn(_ptr(q), _ptr(k_cache), _ptr(v_cache), int(prefix_len), int(chunk_len), int(n_q_heads),
+                                    int(n_kv_heads), int(head_dim), float(scale), _ptr(out), _stream(stream))
+
+    @staticmethod
+    def rms_norm(x, gain, y, rows, hidden, eps, stream):
+        return _lib.kvra_rms_norm(_ptr(x), _ptr(gain), _ptr(y), int(rows), int(hidden), float(eps), _stream(stream))
+
+    @staticmethod
+    def linear(x, w, w2, residual, out, m, n, k, stream):
+        return _lib.kvra_linear(_ptr(x), _ptr(w), _ptr(w2), _ptr(residual), _ptr(out), int(m), int(n), int(k), _stream(stream))
+
+    @staticmethod
+    def qkv_proj(x, wqkv, q_out, k_out, v_out, m, n_q_heads, n_kv_heads, head_dim, k, stream):
+        return _lib.kvra_qkv_proj(_ptr(x), _ptr(wqkv), _ptr(q_out), _ptr(k_out), _ptr(v_out), int(m), int(n_q_heads),
+                                  int(n_kv_heads), int(head_dim), int(k), _stream(stream))
+
+    @staticmethod
+    def layer_chunk(layer, x, y, k_cache, v_cache, prefix_len, chunk_len, capacity, workspace, workspace_bytes, stream):
+        return _lib.kvra_layer_chunk(ctypes.cast(layer, ctypes.POINTER(KvraLayer)), _ptr(x), _ptr(y), _ptr(k_cache), _ptr(v_cache),
+                                     int(prefix_len), int(chunk_len), int(capacity), _ptr(workspace), int(workspace_bytes),
+                                     _stream(stream))
+
+
 def _load_calls():
-    path = os.path.join(_PKG, "_kvra_call.so")
+    # The module is compiled against torch's C++ headers and this Python's: its file is named after both (one for another torch or
+    # Python is not looked at), and without it ctypes, which is tied to neither, does the same.
+    path = binding_path()
     if not os.path.exists(path):
-        raise ImportError(f"{path} is missing: build it with `python -m paper_2405_05329_amd.build`")
-    from . import _kvra_call
+        return _CtypesCalls
+    name = __package__ + "._kvra_call"
+    loader = importlib.machinery.ExtensionFileLoader(name, path)
+    calls = importlib.util.module_from_spec(importlib.util.spec_from_file_location(name, path, loader=loader))
+    loader.exec_module(calls)
     names = ("kvra_append_kv", "kvra_chunk_attn", "kvra_rms_norm", "kvra_linear", "kvra_qkv_proj", "kvra_layer_chunk")
-    _kvra_call.bind(_ptr, *(ctypes.cast(getattr(_lib, n), ctypes.c_void_p).value for n in names))
-    return _kvra_call
+    calls.bind(_ptr, *(ctypes.cast(getattr(_lib, n), ctypes.c_void_p).value for n in names))
+    return calls
 
 
 _call = _load_calls()

@@ -1,10 +1,15 @@
 """The native argument marshalling of the per-chunk calls against the Python functions it stands for (no launch: the library
 refuses these calls, or the arguments never reach it)."""
+import os
+import shutil
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 import torch
 
-from paper_2405_05329_amd import kvra
+from paper_2405_05329_amd import build, kvra
 
 
 class Strange(torch.Tensor):
@@ -71,3 +76,33 @@ def test_every_entry_point_reads_its_arguments_in_order():
     assert code(kvra.kvra_layer_chunk, layer, a[0], a[1], a[2], a[3], 0, 1, 5, a[4], 8) == kvra.KVRA_EINVAL
     with pytest.raises(TypeError):
         kvra.kvra_layer_chunk(4096, a[0], a[1], a[2], a[3], 0, 1, 5, a[4], 1 << 20)
+
+
+def test_the_native_module_is_the_one_in_use():
+    assert os.path.exists(build.binding_path()), "build it with `python -m paper_2405_05329_amd.build`"
+    assert kvra._call.__name__.endswith("._kvra_call") and kvra._call.__file__ == build.binding_path()
+
+
+def test_ctypes_does_the_same(monkeypatch):
+    monkeypatch.setattr(kvra, "_call", kvra._CtypesCalls)
+    for make in (lambda: torch.zeros(4, 4), lambda: torch.zeros(4, 4).t()[1:], lambda: torch.zeros(4).as_subclass(Strange)):
+        test_tensors_that_may_not_be_passed_are_refused_as_by_the_python_function(make)
+    test_numbers_addresses_and_streams()
+    test_every_entry_point_reads_its_arguments_in_order()
+
+
+def test_a_package_without_a_module_for_this_torch_works_through_ctypes(tmp_path):
+    """libkvra.so alone is enough, and a module that was built for another torch or Python is not loaded."""
+    package = tmp_path / "paper_2405_05329_amd"
+    package.mkdir()
+    here = os.path.dirname(kvra.__file__)
+    for name in ("__init__.py", "build.py", "kvra.py", "libkvra.so"):
+        shutil.copy(os.path.join(here, name), package / name)
+    for other in ("_kvra_call.so", os.path.basename(build.binding_path()).replace("torch-", "torch-9."),
+                  os.path.basename(build.binding_path()).replace("cpython-3", "cpython-9")):
+        (package / other).write_bytes(b"not for this interpreter")
+    code = ("from paper_2405_05329_amd import kvra; print(kvra.__file__, kvra._call.__name__, "
+            "kvra.kvra_append_kv(4096, 4096, None, 4096, 4096, 0, 1, 1, 1, 1, 63, 1e4, check=False))")
+    r = subprocess.run([sys.executable, "-c", code], cwd=tmp_path, capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stderr[-2000:]
+    assert r.stdout.split() == [str(package / "kvra.py"), "_CtypesCalls", str(kvra.KVRA_EUNSUPPORTED)]
