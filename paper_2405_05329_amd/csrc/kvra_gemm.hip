@@ -1123,14 +1123,21 @@ bool takes_rows(const GemmArgs& a) {
 // 22.3 us; 1024 29.5 -> 23.8 / 35.6 -> 29.3; 2048 47.4 -> 42.2 / 56.9 -> 53.3 (the append launch that is saved
 // included).  Wide SwiGLU layers are better off with the norm apart: 11008 x 4096 at 1 token 4.8 + 32.5 us against 39.6; and wide
 // projections beyond 8 tokens with the tiles (12288 x 4096 at 1 token inside: 23.4 us; apart 4.8 + 18.5, and 4.8 for the append).
-// Beyond 16 tokens, with blocks of 32 rows x 32 tokens, as long as that is one round of short rows, or where reading
-// both operands again for every block costs less than the launch.  Whole layers, norms apart -> inside: hidden 256, 17 / 256
-// tokens 30.4 -> 23.4 / 32.3 -> 26.2 us (the down projection's share of it as above); 1024, 17 / 160 tokens 38.0 -> 35.6 / 44.1 -> 42.5, 256
-// tokens of either projection alone +1.8 and +20; 2048, 32 tokens 56.7 -> 57.3.
+// Beyond 16 tokens the direct kernel takes blocks of 32 rows x 32 tokens, and every block reads and squares its tokens itself: it pays
+// while rows are short and the blocks fill few rounds of the chip.  A projection alone, norm apart -> inside, us per call, over 17 to
+// 256 tokens and 192 to 8192 rows that are one round: 256 columns -2.2 to -2.9, 768 -1.4 to -3.0, 1024 -0.6 to -2.3, 1152 +0.1 to
+// -1.8; then q/k/v and SwiGLU of 1024 rows and more: 1280 +0.2 to -1.4 and -0.5 to -1.8, 1408 +0.3 to -1.2 and -0.2 to -1.6, 1536
+// +0.8 to -0.8 and 0.0 to -1.5, 1792 +1.2 to -0.7 and +0.3 to -1.0, 2048 +2.1 to -1.0 and +1.4 to -0.8; fewer rows: 1280 +0.5 to
+// -0.8, 1536 +1.2 to 0.0, 4096 +8.4 to +4.1.  Rows of an odd number of 64-column chunks would otherwise go to the one tile that can
+// walk them: 1344 -1.0 to -3.2, 1984 -0.3 to -3.3, 3264 -0.1 to -3.8, 4032 +1.7 to -3.2.  Two rounds: 512 columns -0.4 to -1.7, 768
+// +0.5 to -0.7, 896 +0.4 to +1.9; three: 128 columns -0.1 to -1.1, 256 0.0 to -0.6, 512 +0.6 to +1.5.  Whole layers: hidden 256, 17 /
+// 256 tokens 30.4 -> 23.4 / 32.3 -> 26.2 us (the down projection's share of it as above); 1024, 17 / 160 tokens 38.0 -> 35.6 /
+// 44.1 -> 42.5.
 bool takes_normed_rows(const GemmArgs& a) {
   if (a.m > 16) {
-    const int64_t workgroups = static_cast<int64_t>(a.n / 32) * ((a.m + 31) / 32);
-    return (one_round_of_blocks(a) && a.k <= 1024) || workgroups * (a.k + 256) <= 330000;
+    const int64_t blocks = static_cast<int64_t>(a.n / 32) * ((a.m + 31) / 32);
+    if (blocks > 256) return a.k <= (blocks <= 512 ? 832 : blocks <= 768 ? 128 : 0);
+    return a.k <= (a.k % 128 != 0 ? 3264 : a.n < 1024 ? 1152 : a.dual ? 1792 : 1408);
   }
   return a.dual ? a.n < 16384 : a.m <= (a.n < 8192 ? 16 : 8);
 }

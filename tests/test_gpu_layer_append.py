@@ -23,7 +23,7 @@ def _rel(got, want):
 @pytest.mark.parametrize("m,H,Hkv,d,hidden,tile", [
     (1, 1, 1, 64, 384, (16, 16, 0)), (7, 6, 2, 128, 128, (16, 16, 0)), (16, 71, 1, 64, 192, (16, 16, 0)),
     (1, 3, 1, 64, 4160, (16, 16, 0)), (16, 1, 1, 128, 4096, (16, 16, 0)), (8, 40, 40, 128, 64, (16, 16, 0)),
-    # the norm inside, in blocks of 32 rows and 32 tokens (8 and 16 waves); the tile is what the projection alone would get
+    # most of these with the norm inside, in blocks of 32 rows and 32 tokens; the tile is what the projection alone would get
     (17, 1, 1, 64, 384, (32, 32, 128)), (17, 1, 1, 128, 128, (32, 32, 128)), (65, 35, 5, 64, 128, (32, 64, 128)),
     (132, 35, 5, 64, 384, (64, 64, 128)), (17, 1, 1, 128, 320, (64, 64, 64)), (31, 4, 2, 64, 2048, (32, 32, 128)),
     (65, 2, 1, 128, 704, (32, 32, 0)), (32, 5, 5, 128, 960, (32, 32, 0)), (20, 1, 1, 64, 4160, (64, 64, 64)),
@@ -110,3 +110,18 @@ SIXTEEN_WAVES = [(1, 14, 1, 64, 4160), (16, 6, 1, 128, 4096), (5, 20, 5, 64, 550
 @pytest.mark.parametrize("rope_base", [synth.ROPE_BASE, 0.0])
 def test_layer_whose_projection_takes_sixteen_waves(m, H, Hkv, d, hidden, rope_base):
     test_layer_against_its_operators(m, H, Hkv, d, hidden, (16, 16, 0), rope_base)
+
+
+# the norm inside, in blocks of 32 rows and 32 tokens, at the edges of its rule: one round of blocks to three, the deepest rows (of which
+# the waves keep two chunks each and read the others again), 8 waves and 16
+NORM_IN_BLOCKS = [
+    (17, 1, 1, 64, 64), (127, 30, 1, 64, 1024), (33, 60, 2, 64, 1152), (31, 4, 2, 64, 1088), (100, 14, 1, 128, 2112), (17, 3, 3, 128, 3264),
+    (125, 60, 2, 64, 832), (113, 26, 1, 128, 448), (32, 14, 1, 64, 1408), (132, 24, 6, 128, 128),
+]
+
+
+@pytest.mark.parametrize("m,H,Hkv,d,hidden", NORM_IN_BLOCKS)
+def test_layer_with_the_norm_in_blocks(m, H, Hkv, d, hidden):
+    """(That these calls get that form is asserted in tests/test_launches.py, by the same list.)"""
+    tile = kvra.kvra_linear_tile(m, (H + 2 * Hkv) * d, hidden, False)[:3]
+    test_layer_against_its_operators(m, H, Hkv, d, hidden, tile, synth.ROPE_BASE)

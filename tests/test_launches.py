@@ -110,3 +110,38 @@ def test_the_gpu_tests_of_sixteen_waves_meet_them():
     for shape, r in zip(test_gpu_layer_append.SIXTEEN_WAVES,
                         record([layer(hidden, 128, H, Hkv, d, 37, m) for m, H, Hkv, d, hidden in test_gpu_layer_append.SIXTEEN_WAVES])):
         assert _waves(r["launches"][0]) == 16 and "(kvra::RowsKind)2, true" in r["launches"][0]["kernel"], shape
+
+
+def _normed(launch):
+    """(projection, waves, rows and tokens of a block in sixteens) of a launch with the norm inside, else None."""
+    m = re.match(r"void kvra::linear_rows_kernel<\(kvra::RowsKind\)(\d), true, (\d+), (\d), (\d)>", launch["kernel"])
+    return m and (["plain", "swiglu", "rope"][int(m[1])], int(m[2]), int(m[3]), int(m[4]))
+
+
+@pytest.mark.parametrize("m,hidden,H,Hkv,d,ffn,qkv,swiglu", [
+    # deep rows and few of them, which the norm inside made up to a third slower
+    (64, 4096, 1, 1, 64, 256, False, False), (32, 4096, 6, 1, 64, 128, False, False), (128, 3072, 2, 1, 64, 128, False, False),
+    (17, 2048, 8, 2, 64, 512, False, False), (48, 1536, 2, 1, 64, 64, False, False), (64, 1280, 2, 1, 64, 64, False, False),
+    # the edges of one round of blocks: 1152 columns, 1408 and 1792 from 1024 rows on, 3264 of an odd number of chunks
+    (64, 1152, 2, 1, 64, 64, True, True), (64, 1408, 14, 1, 64, 448, True, False), (64, 1792, 14, 1, 64, 512, False, True),
+    (64, 1920, 14, 1, 64, 512, False, False), (64, 3264, 2, 1, 64, 64, True, True), (64, 3392, 2, 1, 64, 64, False, False),
+    # two rounds up to 832 columns, three up to 128
+    (256, 1024, 14, 1, 64, 512, True, True), (257, 1024, 14, 1, 64, 512, False, False), (256, 832, 30, 1, 64, 1024, True, True),
+    (257, 832, 30, 1, 64, 1024, False, False), (256, 896, 30, 1, 64, 1024, False, False),
+    (384, 128, 30, 1, 64, 1024, True, True), (385, 128, 30, 1, 64, 1024, False, False), (384, 192, 30, 1, 64, 1024, False, False),
+    (187, 256, 4, 2, 64, 704, True, True), (160, 1024, 16, 4, 64, 2816, True, False),
+])
+def test_which_projections_take_the_norm_in_beyond_16_tokens(m, hidden, H, Hkv, d, ffn, qkv, swiglu):
+    r, = record([layer(hidden, ffn, H, Hkv, d, 0, m)])
+    assert r["rc"] == kvra.KVRA_OK
+    inside = {_normed(x)[0] for x in r["launches"] if _normed(x)}
+    assert (("rope" in inside), ("swiglu" in inside)) == (qkv, swiglu)
+
+
+def test_the_gpu_tests_of_the_norm_in_blocks_meet_it():
+    shapes = test_gpu_layer_append.NORM_IN_BLOCKS
+    met = set()
+    for shape, r in zip(shapes, record([layer(hidden, 128, H, Hkv, d, 37, m) for m, H, Hkv, d, hidden in shapes])):
+        assert _normed(r["launches"][0])[0] == "rope" and _normed(r["launches"][0])[2:] == (2, 2), shape
+        met.add(_normed(r["launches"][0])[1])
+    assert met == {8, 16}
