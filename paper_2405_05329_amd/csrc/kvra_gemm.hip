@@ -893,7 +893,8 @@ namespace {
 // alone among the multiples of 2048).  With fewer weight rows too few workgroups share the memory: at the distances above 256 / 512
 // rows take 0.99 to 1.02 / 0.99 to 1.01 of the time, 1024 0.97 to 1.00.  (Weights that are in the last-level cache gain less and less
 // often: 4096 x 11008 0.92 of the time, most others 0.97 to 1.03.  A model's weights are not, from one use to the next.)  64 x 64 tiles
-// of 64-deep stages with three and more token tiles gain nothing at the multiples of 2048 (and lose up to 1.10 from the cache).
+// of 64-deep stages with three and more token tiles gain at the multiples of 8192 (two channels: 8192 x 8192, 182 tokens 67.9 -> 64.6)
+// but not at the others (6144 x 6144, 160 tokens 1.00, and up to 1.10 with the weights in the last-level cache).
 // From 257 tokens on the tiles that share an operand in the L2 lose more by it (11008 x 4096 SwiGLU, 1000 tokens 166 -> 172).
 // Starts eight stages apart are worse.
 // One more class gains, whatever its rows' distance: a weight larger than the last-level cache (256 MB) whose last token tile is at
@@ -908,7 +909,7 @@ int stagger_of(const GemmArgs& a) {
     return distance <= above || distance >= 32768 - 256;
   };
   if (a.k % 2048 == 0) {
-    const bool gains = !(T::TN == 64 && T::TM == 64) || (T::TK == 64 ? tiles_m <= 2 : a.k != 12288);
+    const bool gains = !(T::TN == 64 && T::TM == 64) || (T::TK == 64 ? tiles_m <= 2 || a.k % 8192 == 0 : a.k != 12288);
     if (gains) return 3;
   } else if (one_channel(1, 256) || one_channel(2, 256) || one_channel(3, 512)) {
     return 3;

@@ -73,6 +73,7 @@ def test_projections_keep_off_a_scratch_that_the_attention_was_refused():
     (20, 512, 8192, "swiglu", True), (20, 480, 8192, "swiglu", False),
     # forms of the 64 x 64 tiles
     (20, 12288, 12288, "plain", False), (20, 12288, 24576, "plain", True), (160, 6144, 6144, "plain", False), (77, 10240, 6144, "plain", True),
+    (182, 8192, 8192, "plain", True),
     # weights beyond the last-level cache and a last token tile that is at most five eighths full
     (144, 12288, 13312, "plain", True), (208, 12288, 13312, "plain", True), (209, 12288, 13312, "plain", False),
     (144, 11264, 11776, "plain", False), (128, 12288, 13312, "plain", False),
