@@ -812,9 +812,14 @@ __global__ __launch_bounds__(64 * WAVES, NORM ? (TB > 1 ? 4 : 8) : WAVES / 4) vo
 #pragma unroll
       for (int u = 0; u < COUNT; ++u) multiply(fw[u], fx[u]);
     };
-    constexpr int AHEAD = 64 / WAVES;   // chunks of a wave in one go: all of a 4096-deep row
     int c = wave;
-    for (; c + (AHEAD - 1) * WAVES < chunks; c += AHEAD * WAVES) steps(c, std::integral_constant<int, AHEAD>{});
+    if constexpr (RB * TB == 1) {
+      constexpr int AHEAD = 64 / WAVES;   // chunks of a wave in one go: all of a 4096-deep row
+      for (; c + (AHEAD - 1) * WAVES < chunks; c += AHEAD * WAVES) steps(c, std::integral_constant<int, AHEAD>{});
+    } else {                              // short rows: one chunk per wave, some have two (in a loop alone 1.06 of the time)
+      if (c < chunks) steps(c, std::integral_constant<int, 1>{});
+      c += WAVES;
+    }
     for (; c < chunks; c += WAVES) steps(c, std::integral_constant<int, 1>{});
   }
 #pragma unroll
