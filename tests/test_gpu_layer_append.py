@@ -1,5 +1,6 @@
 """The projection that rotates and appends on its way out (inside kvra_layer_chunk): every tile shape of the linear kernel and
-the kernel for few tokens (which takes in the norm as well; with 8 and 16 waves), both head sizes, with and without rotation, against the public operators called one by one.
+the kernel for few tokens (which takes in the norm as well; with 8 and 16 waves), both head sizes, with and without rotation, against the
+public operators called one by one.
 
 Bars.  Both sides see the same inputs; they differ where a tensor is rounded to bf16 on one side and not on the other, or
 before and after another factor.  rho = 1.66e-3 is the root mean square relative rounding error of bf16.  V: two roundings of
@@ -125,3 +126,14 @@ def test_layer_with_the_norm_in_blocks(m, H, Hkv, d, hidden):
     """(That these calls get that form is asserted in tests/test_launches.py, by the same list.)"""
     tile = kvra.kvra_linear_tile(m, (H + 2 * Hkv) * d, hidden, False)[:3]
     test_layer_against_its_operators(m, H, Hkv, d, hidden, tile, synth.ROPE_BASE)
+
+
+# 96 weight rows to a wave, three units of 32: with head_dim 64 a tile spans three heads, and the two waves' third units are the halves
+# of the middle one; rows that fill the last tile, and that leave it a third and two thirds full
+THREE_UNITS = [(1925, 64, 16, 64, 256), (3651, 35, 7, 64, 256), (1737, 99, 1, 64, 320)]
+
+
+@pytest.mark.parametrize("m,H,Hkv,d,hidden", THREE_UNITS)
+@pytest.mark.parametrize("rope_base", [synth.ROPE_BASE, 0.0])
+def test_layer_whose_tiles_span_three_heads(m, H, Hkv, d, hidden, rope_base):
+    test_layer_against_its_operators(m, H, Hkv, d, hidden, (192, 256, 64), rope_base)

@@ -1,5 +1,7 @@
 """Down projections whose k is shared out over workgroups (inside kvra_layer_chunk, where the attention of the call uses the
-scratch): 64 x 128, 128 x 128 and 128 x 256 tiles with two to four shares, ragged tokens, and k stages that do not divide evenly.
+scratch): 64 x 128, 128 x 128 and 128 x 256 tiles with two to eight shares (even and odd numbers, and more than the merge adds in one
+go), ragged tokens, and k stages that do not divide evenly.  That the calls are split so is asserted in tests/test_launches.py, by the
+same lists; here, that the device is the one those numbers are for.
 
 Against the public operators one by one, which never split: y differs by roundings of stored tensors (1.2e-2 relative, as for
 a whole layer; a lost or doubled share is of order 1).  The pieces of a tile may finish in any order; the sums are taken in
@@ -14,7 +16,31 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("m,ffn,H", [(77, 11008, 8), (250, 11008, 8), (333, 11072, 8), (500, 8256, 8), (1000, 11008, 32)])
 def test_layer_with_a_split_down_projection(m, ffn, H):
-    hidden, Hkv, d, prefix, scale = 4096, H, 128, 2048, synth.default_scale(128)
+    check_split(m, 4096, ffn, H, H)
+
+
+PREFIX = 2048
+# tokens, hidden, ffn, heads, tile, shares, whether the weight tiles start apart
+SPLITS = [
+    (77, 4096, 11008, 8, 8, (64, 128, 64), 4, True), (250, 4096, 11008, 8, 8, (128, 128, 64), 4, True),
+    (333, 4096, 11072, 8, 8, (128, 128, 64), 2, False), (500, 4096, 8256, 8, 8, (128, 128, 64), 2, False),
+    (1000, 4096, 11008, 32, 32, (128, 256, 64), 2, False),
+]
+MORE_SPLITS = [
+    (77, 1024, 11008, 8, 8, (64, 128, 64), 8, True), (40, 2048, 8256, 8, 8, (64, 128, 64), 7, True),
+    (100, 3072, 8192, 8, 8, (64, 128, 64), 5, True), (77, 5120, 13824, 8, 8, (64, 128, 64), 3, False),
+    (333, 1024, 8192, 8, 2, (64, 128, 64), 5, False), (300, 2048, 8256, 8, 8, (128, 128, 64), 5, False),
+    (333, 3072, 8192, 8, 8, (128, 128, 64), 3, False), (1200, 2048, 11008, 16, 16, (128, 256, 64), 3, False),
+]
+
+
+@pytest.mark.parametrize("m,hidden,ffn,H,Hkv,tile,shares,apart", MORE_SPLITS)
+def test_layer_with_other_numbers_of_shares(m, hidden, ffn, H, Hkv, tile, shares, apart):
+    check_split(m, hidden, ffn, H, Hkv)
+
+
+def check_split(m, hidden, ffn, H, Hkv):
+    d, prefix, scale = 128, PREFIX, synth.default_scale(128)
     gen = torch.Generator(device="cuda")
     gen.manual_seed(m)
 
@@ -28,6 +54,7 @@ def test_layer_with_a_split_down_projection(m, ffn, H):
     layer = kvra.make_layer(hidden, ffn, H, Hkv, d, synth.RMS_EPS, synth.ROPE_BASE, scale, n1, wqkv, wo, n2, wg, wu, wd)
     kc, vc = normal(prefix + m, Hkv, d), normal(prefix + m, Hkv, d)
     cus = torch.cuda.get_device_properties(0).multi_processor_count
+    assert cus == 256
     assert kvra.kvra_chunk_attn_plan(prefix, m, H, Hkv, d, cus)["partial_pieces"] > 0
     assert kvra.kvra_chunk_attn_row_splits(prefix, m, H, Hkv, d, cus) != 1   # the attention uses the scratch
     nbytes = kvra.kvra_layer_workspace_bytes(layer, m)

@@ -4,6 +4,7 @@ import re
 import pytest
 
 import test_gpu_layer_append
+import test_gpu_layer_split
 import test_gpu_linear_tiles
 from paper_2405_05329_amd import kvra
 from launch_recorder import layer, linear, record
@@ -146,3 +147,22 @@ def test_the_gpu_tests_of_the_norm_in_blocks_meet_it():
         assert _normed(r["launches"][0])[0] == "rope" and _normed(r["launches"][0])[2:] == (2, 2), shape
         met.add(_normed(r["launches"][0])[1])
     assert met == {8, 16}
+
+
+def test_the_gpu_tests_of_split_projections_meet_them():
+    """Tile, number of shares (off the grid: one workgroup per share and tile, rounded up to eight) and form of the down projection."""
+    shapes = test_gpu_layer_split.SPLITS + test_gpu_layer_split.MORE_SPLITS
+    results = record([layer(hidden, ffn, H, Hkv, 128, test_gpu_layer_split.PREFIX, m) for m, hidden, ffn, H, Hkv, *_ in shapes])
+    for shape, r in zip(shapes, results):
+        m, hidden, _, _, _, tile, shares, apart = shape
+        down, tiles = r["launches"][-1], -(-hidden // tile[0]) * -(-m // tile[1])
+        assert _ring(down["kernel"]) == (tile, False, True, apart), shape
+        assert [s for s in range(2, 9) if -(-tiles * s // 8) * 8 == down["grid"][0]] == [shares], shape
+    assert {s[6] for s in shapes} == {2, 3, 4, 5, 7, 8}
+
+
+def test_the_gpu_tests_of_tiles_that_span_three_heads_meet_them():
+    shapes = test_gpu_layer_append.THREE_UNITS
+    assert {(H + 2 * Hkv) * d % 192 for _, H, Hkv, d, _ in shapes} == {0, 64, 128}
+    for shape, r in zip(shapes, record([layer(hidden, 128, H, Hkv, d, 37, m) for m, H, Hkv, d, hidden in shapes])):
+        assert ((192, 256, 64), True, False, False) in [_ring(x["kernel"]) for x in r["launches"]], shape
