@@ -3,6 +3,7 @@ import re
 
 import pytest
 
+import test_gpu_layer
 import test_gpu_layer_append
 import test_gpu_layer_split
 import test_gpu_linear_tiles
@@ -166,3 +167,13 @@ def test_the_gpu_tests_of_tiles_that_span_three_heads_meet_them():
     assert {(H + 2 * Hkv) * d % 192 for _, H, Hkv, d, _ in shapes} == {0, 64, 128}
     for shape, r in zip(shapes, record([layer(hidden, 128, H, Hkv, d, 37, m) for m, H, Hkv, d, hidden in shapes])):
         assert ((192, 256, 64), True, False, False) in [_ring(x["kernel"]) for x in r["launches"]], shape
+
+
+def test_the_gpu_test_of_few_tokens_meets_the_norm_inside():
+    met = set()
+    for hidden, ffn, H, Hkv, d, _, bounds, swiglu_inside in test_gpu_layer.FEW_TOKENS:
+        for r in record([layer(hidden, ffn, H, Hkv, d, lo, hi - lo) for lo, hi in zip(bounds, bounds[1:])]):
+            forms = [_normed(x) for x in r["launches"] if _normed(x)]
+            assert [f[0] for f in forms] == ["rope"] + ["swiglu"] * swiglu_inside and all(f[2:] == (1, 1) for f in forms), (hidden, ffn)
+            met.update(f[:2] for f in forms)
+    assert met == {("rope", 8), ("rope", 16), ("swiglu", 8), ("swiglu", 16)}
