@@ -377,7 +377,7 @@ int64_t kvra_layer_workspace_bytes(const kvra_layer* layer, int64_t chunk_len);
 /*
  * One layer over one chunk: RMSNorm, q/k/v projections with what kvra_append_kv does on their way out (rotary
  * embedding, cache rows [prefix_len, prefix_len + chunk_len)), kvra_chunk_attn, output projection + residual,
- * RMSNorm, SwiGLU MLP + residual; five to nine launches on `stream`.  Where its attention cuts units (and so uses the scratch
+ * RMSNorm, SwiGLU MLP + residual; five to ten launches on `stream`.  Where its attention cuts units (and so uses the scratch
  * buffer, see the top of the file), the projections behind it may use that buffer as well.
  *   x, y        [chunk_len, hidden]; y may not alias x
  *   workspace   caller-owned device memory, 256-byte aligned, at least

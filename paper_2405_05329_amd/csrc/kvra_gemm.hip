@@ -1072,8 +1072,9 @@ const TileChoice* choose_split(const GemmArgs& a, const TileChoice& whole, const
   return best;
 }
 
-// A long launch whose tiles leave its last round nearly empty goes out as two: one of the four large tiles on as many columns as fill
-// whole rounds, and whatever is best on the columns left over (the same sums in the same order: no result changes).  22016 x 4096 SwiGLU rows
+// A long launch whose tiles leave its last round nearly empty goes out as two: one of the large tiles (128 x 256 and more) on as many
+// columns as fill whole rounds, and whatever is best on the columns left over.  (The sums of those columns may be taken in another order
+// than the whole launch would take them, where the second tile's waves share k.)  22016 x 4096 SwiGLU rows
 // are 86 tiles of 256, so 3072 tokens are 4.03 rounds: 432 -> 395 us; 700 tokens 125 -> 115, 1500 236 -> 212, 3712 537 -> 487;
 // 11264 x 2048 at 6000 tokens 226 -> 209; 4096 x 11008, 2304 / 4800 tokens: 206 -> 189 / 394 -> 360.  The two
 // have to promise 4 % together, and are only looked for where that is more than the search (1 us) and the second launch.  Short rows
@@ -1116,8 +1117,10 @@ TwoParts choose_two(const GemmArgs& a, const TileChoice& whole) {
 // 11008 x 4096 at 1 / 4 / 8 tokens 34.7 / 38.3 / 43.3 us (5.2 TB/s at 1) against 41.2 / 41.2 / 41.5; 5632 x 2048 at 1 / 8 / 12
 // 10.4 / 12.5 / 13.7 against 12.7 / 13.1 / 13.1; 2816 x 1024 at 1 / 16 4.9 / 6.0 against 6.2 / 6.2.
 // Beyond that, one round of workgroups of 32 rows x 32 tokens where k has an odd number of 64-column chunks, which only the tiles
-// with 64-deep stages can walk, and few of them: 256 columns of 17 / 400 tokens, k = 704: 6.0 / 6.3 -> 4.4 / 4.8 us.  (k = 256: 4.6
-// -> 4.3, 1024: the same, 2816: 8.2 -> 12.0.)
+// with 64-deep stages can walk, and few of them.  Time in blocks over time in tiles, 32 to 8192 columns, 17 to 4000 tokens: k = 448 0.68 to
+// 0.76, 576 0.70 to 0.76, 704 0.74 to 0.78, 832 0.74 to 0.80, 960 0.75 to 0.81 (256 columns of 17 / 400 tokens, k = 704: 6.0 / 6.3 -> 4.4
+// / 4.8 us); 64 to 320 0.58 to 1.42.  (Deeper rows would gain as well, 1088 0.70 to 0.83, 1984 0.73 to 0.93, 3008 0.74 to 0.96; the rule
+// has not been carried there.)  Rows of an even number of chunks have better tiles: 256 4.6 -> 4.3 us, 1024 the same, 2816 8.2 -> 12.0.
 bool one_round_of_blocks(const GemmArgs& a) { return static_cast<int64_t>(a.n / 32) * ((a.m + 31) / 32) <= 256; }
 bool takes_rows(const GemmArgs& a) {
   if (a.m > 16) return !a.dual && a.k % 128 != 0 && a.k > 384 && a.k < 1024 && one_round_of_blocks(a);

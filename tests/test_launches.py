@@ -177,3 +177,10 @@ def test_the_gpu_test_of_few_tokens_meets_the_norm_inside():
             assert [f[0] for f in forms] == ["rope"] + ["swiglu"] * swiglu_inside and all(f[2:] == (1, 1) for f in forms), (hidden, ffn)
             met.update(f[:2] for f in forms)
     assert met == {("rope", 8), ("rope", 16), ("swiglu", 8), ("swiglu", 16)}
+
+
+def test_a_layer_is_five_to_ten_launches():
+    """Norms inside the projections, nothing cut in two; and everything apart, with all three of the long projections in two."""
+    few, many = record([layer(256, 704, 4, 2, 64, 0, 16), layer(8192, 28672, 64, 64, 128, 0, 1036)])
+    assert [len(r["launches"]) for r in (few, many)] == [5, 10]
+    assert sum("norm" in x["kernel"] for x in many["launches"]) == 2 and sum(_ring(x["kernel"]) is not None for x in many["launches"]) == 7
