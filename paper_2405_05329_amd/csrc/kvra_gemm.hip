@@ -1132,6 +1132,8 @@ bool takes_rows(const GemmArgs& a) {
 // 22.3 us; 1024 29.5 -> 23.8 / 35.6 -> 29.3; 2048 47.4 -> 42.2 / 56.9 -> 53.3 (the append launch that is saved
 // included).  Wide SwiGLU layers are better off with the norm apart: 11008 x 4096 at 1 token 4.8 + 32.5 us against 39.6; and wide
 // projections beyond 8 tokens with the tiles (12288 x 4096 at 1 token inside: 23.4 us; apart 4.8 + 18.5, and 4.8 for the append).
+// (Both lines are coarse in the depth, us of a projection, apart -> inside: SwiGLU of 12288 rows, 1 / 8 / 16 tokens: 1024 columns -1.5 /
+// -1.2 / -2.4, 4096 +0.8 / +1.7 / +3.6, 8192 +2.0 / +4.8 / +11; q/k/v of 4096 rows -2.4 to -5.0 up to 8192 columns, of 6144 +4.7 to +8.8 there.)
 // Beyond 16 tokens the direct kernel takes blocks of 32 rows x 32 tokens, and every block reads and squares its tokens itself: it pays
 // while rows are short and the blocks fill few rounds of the chip.  A projection alone, norm apart -> inside, us per call, over 17 to
 // 256 tokens and 192 to 8192 rows that are one round: 256 columns -2.2 to -2.9, 768 -1.4 to -3.0, 1024 -0.6 to -2.3, 1152 +0.1 to
